@@ -21,7 +21,10 @@
 //    error below about 8 u^2 (|a| + |r||q|), the classical axpy bound.
 // qd numbers use level-structured sums: terms of magnitude ~u^k |x| are
 // added at level k with TwoSum, the carries moved to level k+1, level 3 is
-// summed in plain FP64, and a two-pass TwoSum distillation renormalises.
+// summed in plain FP64.  Sums of products (inner products, the column
+// update) stay in such level words until the end, with a fifth one for the
+// rounding of level 3: no renormalisation between terms, one two-pass TwoSum
+// distillation when the value is needed.
 // Error below a small multiple of 2^-209 relative to the operands.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -134,6 +137,22 @@ __device__ __forceinline__ qd qd_renorm(double a0, double a1, double a2, double 
   return {y0, y1, y2, y3};
 }
 
+// Five level words into four limbs: a third pass folds the fifth word in
+// below the third limb instead of rounding it into the fourth word.
+__device__ __forceinline__ qd qd_renorm5(double a0, double a1, double a2, double a3, double a4) {
+  double s, y0, y1, y2, e1, e2, e3, e4, f1, f2, f3, g1, g2;
+  two_sum(a3, a4, s, e4);
+  two_sum(a2, s, s, e3);
+  two_sum(a1, s, s, e2);
+  two_sum(a0, s, y0, e1);
+  two_sum(e3, e4, s, f3);
+  two_sum(e2, s, s, f2);
+  two_sum(e1, s, y1, f1);
+  two_sum(f2, f3, s, g2);
+  two_sum(f1, s, y2, g1);
+  return {y0, y1, y2, g1 + g2};
+}
+
 __device__ __forceinline__ qd qd_add(qd a, qd b) {
   double s0, e0, s1, e1, s2, e2, s3, e3;
   two_sum(a.x0, b.x0, s0, e0);
@@ -154,7 +173,25 @@ __device__ __forceinline__ qd qd_add(qd a, qd b) {
 __device__ __forceinline__ qd qd_neg(qd a) { return {-a.x0, -a.x1, -a.x2, -a.x3}; }
 __device__ __forceinline__ qd qd_sub(qd a, qd b) { return qd_add(a, qd_neg(b)); }
 
-__device__ __forceinline__ qd qd_mul(qd a, qd b) {
+// The sum of the level-3 terms of a b and of its level-4 products in plain
+// FP64, the smallest first.
+__device__ __forceinline__ double qd_low_products(const qd &a, const qd &b) {
+  double t = a.x1 * b.x3;
+  t = __fma_rn(a.x2, b.x2, t);
+  t = __fma_rn(a.x3, b.x1, t);
+  t = __fma_rn(a.x0, b.x3, t);
+  t = __fma_rn(a.x1, b.x2, t);
+  t = __fma_rn(a.x2, b.x1, t);
+  return __fma_rn(a.x3, b.x0, t);
+}
+
+// The level words of a product or of a b + c d, not renormalised.  Level 3
+// in up to three words (the products of two factors, the carries out of
+// level 2), each rounded at its own size, for sums that take them exactly.
+struct qdprod {
+  double x0, x1, x2, x3, y3, z3;
+};
+__device__ __forceinline__ qdprod qd_mul_levels(const qd &a, const qd &b) {
   // level 0 / 1 / 2 products split exactly
   double p00, q00, p01, q01, p10, q10, p02, q02, p11, q11, p20, q20;
   two_prod(a.x0, b.x0, p00, q00);
@@ -175,30 +212,150 @@ __device__ __forceinline__ qd qd_mul(qd a, qd b) {
   two_sum(s2, q10, s2, u4);
   two_sum(s2, r1, s2, u5);
   two_sum(s2, r2, s2, u6);
-  // level 3 (and the level-4 products) in FP64
-  double s3 = a.x1 * b.x3;
-  s3 = __fma_rn(a.x2, b.x2, s3);
-  s3 = __fma_rn(a.x3, b.x1, s3);
-  s3 = __fma_rn(a.x0, b.x3, s3);
-  s3 = __fma_rn(a.x1, b.x2, s3);
-  s3 = __fma_rn(a.x2, b.x1, s3);
-  s3 = __fma_rn(a.x3, b.x0, s3);
+  // level 3
+  double s3 = qd_low_products(a, b);
   s3 += (q02 + q11) + (q20 + u1);
-  s3 += (u2 + u3) + (u4 + (u5 + u6));
-  return qd_renorm(p00, s1, s2, s3);
+  return {p00, s1, s2, s3, (u2 + u3) + (u4 + (u5 + u6)), 0.0};
+}
+__device__ __forceinline__ qd qd_mul(const qd &a, const qd &b) {
+  const qdprod m = qd_mul_levels(a, b);
+  return qd_renorm(m.x0, m.x1, m.x2, m.x3 + m.y3);
+}
+
+// a b + c d, one part of a complex product: 190 operations.
+__device__ __forceinline__ qdprod qd_dot2(const qd &a, const qd &b, const qd &c, const qd &d) {
+  const qdprod m = qd_mul_levels(a, b);
+  double p00, q00, p01, q01, p10, q10, p02, q02, p11, q11, p20, q20, s0, s1, s2, c0, d1, d2, d3, d4;
+  two_prod(c.x0, d.x0, p00, q00);
+  two_prod(c.x0, d.x1, p01, q01);
+  two_prod(c.x1, d.x0, p10, q10);
+  two_prod(c.x0, d.x2, p02, q02);
+  two_prod(c.x1, d.x1, p11, q11);
+  two_prod(c.x2, d.x0, p20, q20);
+  two_sum(m.x0, p00, s0, c0);
+  // level 1
+  two_sum(m.x1, p01, s1, d1);
+  two_sum(s1, p10, s1, d2);
+  two_sum(s1, q00, s1, d3);
+  two_sum(s1, c0, s1, d4);
+  // level 2
+  double e1, e2, e3, e4, e5, e6, e7, e8, e9;
+  two_sum(m.x2, p02, s2, e1);
+  two_sum(s2, p11, s2, e2);
+  two_sum(s2, p20, s2, e3);
+  two_sum(s2, q01, s2, e4);
+  two_sum(s2, q10, s2, e5);
+  two_sum(s2, d1, s2, e6);
+  two_sum(s2, d2, s2, e7);
+  two_sum(s2, d3, s2, e8);
+  two_sum(s2, d4, s2, e9);
+  // level 3
+  double t = qd_low_products(c, d);
+  t += (q02 + q11) + q20;
+  return {s0, s1, s2, m.x3 + m.y3, t, (e1 + ((e2 + e3) + (e4 + e5))) + ((e6 + e7) + (e8 + e9))};
+}
+// The level words of a^2 (the symmetric products formed once from 2 a_i).
+__device__ __forceinline__ qd qd_sqr_levels(const qd &a) {
+  const double t0 = 2.0 * a.x0, t1 = 2.0 * a.x1;
+  double p00, q00, p01, q01, p02, q02, p11, q11, s1, r1, s2, u1, u2, u3;
+  two_prod(a.x0, a.x0, p00, q00);
+  two_prod(t0, a.x1, p01, q01);
+  two_prod(t0, a.x2, p02, q02);
+  two_prod(a.x1, a.x1, p11, q11);
+  two_sum(p01, q00, s1, r1);
+  two_sum(p02, p11, s2, u1);
+  two_sum(s2, q01, s2, u2);
+  two_sum(s2, r1, s2, u3);
+  double t = a.x2 * a.x2;
+  t = __fma_rn(t1, a.x3, t);
+  t = __fma_rn(t0, a.x3, t);
+  t = __fma_rn(t1, a.x2, t);
+  t += (q02 + q11) + (u1 + (u2 + u3));
+  return {p00, s1, s2, t};
+}
+
+// A sum of qd terms given by level words: one word per level, the carries
+// out of levels 0 to 3 exact, level 4 in plain FP64, never renormalised on
+// the way.  The next term only waits for one addition per level (a
+// renormalised sum is a chain of about 60).
+struct qdsum {
+  double x0, x1, x2, x3, x4;
+};
+__device__ __forceinline__ void qd_acc(qdsum &a, const qd &b) {
+  double c, d1, d2, e1, e2, e3, f, g;
+  two_sum(a.x0, b.x0, a.x0, c);
+  two_sum(a.x1, b.x1, a.x1, d1);
+  two_sum(a.x1, c, a.x1, d2);
+  two_sum(a.x2, b.x2, a.x2, e1);
+  two_sum(a.x2, d1, a.x2, e2);
+  two_sum(a.x2, d2, a.x2, e3);
+  two_sum(a.x3, b.x3, a.x3, f);
+  two_sum(a.x3, e1 + (e2 + e3), a.x3, g);
+  a.x4 += f + g;
+}
+__device__ __forceinline__ void qd_acc(qdsum &a, const qdprod &b) {
+  double f, g;
+  two_sum(a.x3, b.y3, a.x3, f);
+  two_sum(a.x3, b.z3, a.x3, g);
+  a.x4 += f + g;
+  qd_acc(a, qd{b.x0, b.x1, b.x2, b.x3});
+}
+// a += b, level by level (symmetric in a and b: the same bits either way).
+__device__ __forceinline__ void qd_merge(qdsum &a, const qdsum &b) {
+  const double l = a.x4 + b.x4;
+  a.x4 = 0.0;
+  qd_acc(a, qd{b.x0, b.x1, b.x2, b.x3});
+  a.x4 += l;
+}
+__device__ __forceinline__ qdsum qd_sum_from(const qd &v) { return {v.x0, v.x1, v.x2, v.x3, 0.0}; }
+// The sum's value in four limbs.  When whole levels cancelled against each
+// other the distillation leaves words of similar size; such a value (rare:
+// a cancellation of more than about 50 bits) is swept from the top, one
+// level per sweep, until its leading limb is the rounded value.
+__device__ __forceinline__ qd qd_value(const qdsum &s) {
+  qd y = qd_renorm5(s.x0, s.x1, s.x2, s.x3, s.x4);
+  if (fabs(y.x1) > 0x1p-53 * fabs(y.x0)) {
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i) {
+      two_sum(y.x0, y.x1, y.x0, y.x1);
+      two_sum(y.x1, y.x2, y.x1, y.x2);
+      two_sum(y.x2, y.x3, y.x2, y.x3);
+    }
+  }
+  return y;
 }
 __device__ __forceinline__ qd qd_from(double a) { return {a, 0.0, 0.0, 0.0}; }
 
-// 1/b: Newton iterations x <- x + x (1 - b x) from the FP64 reciprocal.
-__device__ __forceinline__ qd qd_recip(qd b) {
-  qd x = qd_from(1.0 / b.x0);
+// c - a b for a product within a relative 2^-50 of c, as three words: the
+// levels cancel exactly in the sum, what is left is good to about
+// 2^-214 |c|.
+struct td {
+  double h, l, ll;
+};
+__device__ __forceinline__ td qd_residual(const qd &c, const qd &a, const qd &b) {
+  qdsum r = qd_sum_from(c);
+  qd_acc(r, qd_mul_levels(qd_neg(a), b));
+  const qd v = qd_renorm5(r.x0, r.x1, r.x2, r.x3, r.x4);
+  // after the cancellation its leading words may overlap
+  td d;
+  double t;
+  two_sum(v.x0, v.x1, d.h, t);
+  two_sum(t, v.x2, d.l, t);
+  d.ll = t + v.x3;
+  return d;
+}
+
+// 1/b: the dd reciprocal (about 2^-104), one Newton step x + x (1 - b x)
+// to about 2^-208 (the correction only needs dd precision), and one more
+// whose correction only needs FP64.
+__device__ __forceinline__ qd qd_recip(const qd &b) {
+  const dd x = dd_recip({b.x0, b.x1});
   const qd one = qd_from(1.0);
-#pragma unroll 1
-  for (int it = 0; it < 3; ++it) {
-    qd r = qd_sub(one, qd_mul(b, x));
-    x = qd_add(x, qd_mul(x, r));
-  }
-  return x;
+  const td e = qd_residual(one, b, {x.h, x.l, 0.0, 0.0});
+  const dd h = dd_mul(x, {e.h, e.l});
+  const qd y = qd_renorm(x.h, x.l, h.h, h.l);
+  const td r = qd_residual(one, b, y);
+  return qd_renorm5(y.x0, y.x1, y.x2, y.x3, y.x0 * r.h);
 }
 // Inverse square root of s > 0 to about 2^-103, as a dd: one Newton step
 // y + y (1 - s y^2) / 2 from the FP64 one, whose relative error (about
@@ -216,38 +373,35 @@ __device__ __forceinline__ dd qd_rsqrt_dd(const qd &s) {
   fast_two_sum(y, 0.5 * (y * r), out.h, out.l);
   return out;
 }
-// One Newton step of the inverse square root in qd, from the dd one: the
-// relative error goes from about 2^-103 to about 2^-206.
-__device__ __forceinline__ qd qd_rsqrt(const qd &s) {
+// v + v c for a correction c of at most about 2^-100.
+__device__ __forceinline__ qd qd_correct(const qd &v, const td &c) {
+  double p, q, p1, q1, p2, q2;
+  two_prod(v.x0, c.h, p, q);
+  two_prod(v.x0, c.l, p1, q1);
+  two_prod(v.x1, c.h, p2, q2);
+  qdsum r = qd_sum_from(v);
+  qd_acc(r, qdprod{0.0, 0.0, p, q, p1, p2});
+  r.x4 += __fma_rn(v.x0, c.ll, __fma_rn(v.x1, c.l, __fma_rn(v.x2, c.h, q1 + q2)));
+  return qd_renorm5(r.x0, r.x1, r.x2, r.x3, r.x4);
+}
+// sqrt(s) and 1/sqrt(s) together, s > 0, from the dd inverse square root y
+// and x = s y: with e = 1 - x y (about 2^-102, formed once) both are their
+// first values times (1 - e)^(-1/2) = 1 + e/2 + 3 e^2 / 8 + O(e^3), so one
+// residual serves the two and the chain is one product, one residual and
+// one correction long.
+__device__ __forceinline__ void qd_sqrt_recip(const qd &s, qd &root, qd &inv) {
   const dd y1 = qd_rsqrt_dd(s);
   const qd y = {y1.h, y1.l, 0.0, 0.0};
-  const qd r = qd_sub(qd_from(1.0), qd_mul(s, qd_mul(y, y)));
-  const qd h = qd_mul(y, r);
-  return qd_add(y, {0.5 * h.x0, 0.5 * h.x1, 0.5 * h.x2, 0.5 * h.x3});
+  const qd x = qd_mul(s, y);
+  const td e = qd_residual(qd_from(1.0), x, y);
+  const td c = {0.5 * e.h, 0.5 * e.l, __fma_rn(0.375 * e.h, e.h, 0.5 * e.ll)};
+  root = qd_correct(x, c);
+  inv = qd_correct(y, c);
 }
-// sqrt(s) for s > 0: the inverse square root y (qd_rsqrt), then x = s y
-// corrected once by y (s - x^2) / 2, which squares the error of y again.
-__device__ __forceinline__ qd qd_sqrt(qd s) {
-  const qd y = qd_rsqrt(s);
-  qd x = qd_mul(s, y);
-  qd d = qd_sub(s, qd_mul(x, x));
-  qd h = qd_mul(y, d);
-  return qd_add(x, {0.5 * h.x0, 0.5 * h.x1, 0.5 * h.x2, 0.5 * h.x3});
-}
-
-// sqrt(s) and 1/sqrt(s) together: the inverse square root y of qd_sqrt
-// is the reciprocal of the root up to its last bits; one Newton step of the
-// reciprocal from y, y + y (1 - root y), takes it to full accuracy, in
-// place of the three iterations of qd_recip started from the FP64
-// reciprocal.
-__device__ __forceinline__ void qd_sqrt_recip(qd s, qd &root, qd &inv) {
-  const qd y = qd_rsqrt(s);
-  const qd one = qd_from(1.0);
-  qd x = qd_mul(s, y);
-  qd d = qd_sub(s, qd_mul(x, x));
-  qd h = qd_mul(y, d);
-  root = qd_add(x, {0.5 * h.x0, 0.5 * h.x1, 0.5 * h.x2, 0.5 * h.x3});
-  inv = qd_add(y, qd_mul(y, qd_sub(one, qd_mul(root, y))));
+__device__ __forceinline__ qd qd_sqrt(const qd &s) {
+  qd root, inv;
+  qd_sqrt_recip(s, root, inv);
+  return root;
 }
 
 // --------------------------------------------------------- precisions ----
@@ -446,7 +600,9 @@ struct PrecQD {
   static constexpr int L = 4;
   using R = qd;
   using C = cqd;
-  using Acc = cqd;
+  struct Acc {
+    qdsum re, im;
+  };
 
   __device__ static __forceinline__ C load(const double *p, size_t plane) {
     C v;
@@ -474,19 +630,20 @@ struct PrecQD {
   __device__ static __forceinline__ R rfrom(double v) { return {v, 0.0, 0.0, 0.0}; }
   __device__ static __forceinline__ R rone() { return {1.0, 0.0, 0.0, 0.0}; }
   __device__ static __forceinline__ C czero() { return {rzero(), rzero()}; }
-  __device__ static __forceinline__ void acc_zero(Acc &a) { a = czero(); }
+  __device__ static __forceinline__ void acc_zero(Acc &a) { a = {{0.0, 0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0, 0.0}}; }
   __device__ static __forceinline__ void acc_cmulc(Acc &acc, const C &q, const C &a) {
-    acc.re = qd_add(acc.re, qd_add(qd_mul(q.re, a.re), qd_mul(q.im, a.im)));
-    acc.im = qd_add(acc.im, qd_sub(qd_mul(q.re, a.im), qd_mul(q.im, a.re)));
+    qd_acc(acc.re, qd_dot2(q.re, a.re, q.im, a.im));
+    qd_acc(acc.im, qd_dot2(q.re, a.im, qd_neg(q.im), a.re));
   }
   __device__ static __forceinline__ void acc_abs2(Acc &acc, const C &a) {
-    acc.re = qd_add(acc.re, qd_add(qd_mul(a.re, a.re), qd_mul(a.im, a.im)));
+    qd_acc(acc.re, qd_sqr_levels(a.re));
+    qd_acc(acc.re, qd_sqr_levels(a.im));
   }
   __device__ static __forceinline__ void acc_cmul(Acc &acc, const C &a, const C &b) {
-    acc.re = qd_add(acc.re, qd_sub(qd_mul(a.re, b.re), qd_mul(a.im, b.im)));
-    acc.im = qd_add(acc.im, qd_add(qd_mul(a.re, b.im), qd_mul(a.im, b.re)));
+    qd_acc(acc.re, qd_dot2(a.re, b.re, qd_neg(a.im), b.im));
+    qd_acc(acc.im, qd_dot2(a.re, b.im, a.im, b.re));
   }
-  __device__ static __forceinline__ void acc_set(Acc &acc, const C &v) { acc = v; }
+  __device__ static __forceinline__ void acc_set(Acc &acc, const C &v) { acc = {qd_sum_from(v.re), qd_sum_from(v.im)}; }
   __device__ static __forceinline__ C conj(const C &v) { return {v.re, qd_neg(v.im)}; }
   __device__ static __forceinline__ void add_cd(C &v, double dr, double di) {
     v.re = qd_add(v.re, qd_from(dr));
@@ -494,26 +651,29 @@ struct PrecQD {
   }
   __device__ static __forceinline__ C cneg(const C &v) { return {qd_neg(v.re), qd_neg(v.im)}; }
   __device__ static __forceinline__ void acc_merge(Acc &a, const Acc &b) {
-    a.re = qd_add(a.re, b.re);
-    a.im = qd_add(a.im, b.im);
+    qd_merge(a.re, b.re);
+    qd_merge(a.im, b.im);
   }
-  __device__ static __forceinline__ void acc_merge_re(Acc &a, const Acc &b) { a.re = qd_add(a.re, b.re); }
-  __device__ static __forceinline__ qd shfl_qd(const qd &a, int mask) {
-    return {__shfl_xor(a.x0, mask), __shfl_xor(a.x1, mask), __shfl_xor(a.x2, mask), __shfl_xor(a.x3, mask)};
+  __device__ static __forceinline__ void acc_merge_re(Acc &a, const Acc &b) { qd_merge(a.re, b.re); }
+  __device__ static __forceinline__ qdsum shfl_sum(const qdsum &a, int mask) {
+    return {__shfl_xor(a.x0, mask), __shfl_xor(a.x1, mask), __shfl_xor(a.x2, mask), __shfl_xor(a.x3, mask),
+            __shfl_xor(a.x4, mask)};
   }
   __device__ static __forceinline__ Acc acc_shfl_xor(const Acc &a, int mask) {
-    return {shfl_qd(a.re, mask), shfl_qd(a.im, mask)};
+    return {shfl_sum(a.re, mask), shfl_sum(a.im, mask)};
   }
   __device__ static __forceinline__ Acc acc_shfl_xor_re(const Acc &a, int mask) {
-    return {shfl_qd(a.re, mask), rzero()};
+    return {shfl_sum(a.re, mask), {0.0, 0.0, 0.0, 0.0, 0.0}};
   }
-  __device__ static __forceinline__ C acc_value(const Acc &a) { return a; }
-  __device__ static __forceinline__ R acc_value_re(const Acc &a) { return a.re; }
+  __device__ static __forceinline__ C acc_value(const Acc &a) { return {qd_value(a.re), qd_value(a.im)}; }
+  __device__ static __forceinline__ R acc_value_re(const Acc &a) { return qd_value(a.re); }
   __device__ static __forceinline__ void upd(C &a, const C &r, const C &q) {
-    qd tr = qd_sub(qd_mul(r.re, q.re), qd_mul(r.im, q.im));
-    qd ti = qd_add(qd_mul(r.re, q.im), qd_mul(r.im, q.re));
-    a.re = qd_sub(a.re, tr);
-    a.im = qd_sub(a.im, ti);
+    const qd nr = qd_neg(r.re), ni = qd_neg(r.im);
+    qdsum sr = qd_sum_from(a.re), si = qd_sum_from(a.im);
+    qd_acc(sr, qd_dot2(nr, q.re, r.im, q.im));
+    qd_acc(si, qd_dot2(nr, q.im, ni, q.re));
+    a.re = qd_value(sr);
+    a.im = qd_value(si);
   }
   __device__ static __forceinline__ C scale(const C &a, const R &s) { return {qd_mul(a.re, s), qd_mul(a.im, s)}; }
   __device__ static __forceinline__ R sqrt_(const R &s) { return qd_sqrt(s); }
