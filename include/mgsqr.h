@@ -105,9 +105,8 @@ int mgs_workspace_size(int m, int n, int prec, int op, size_t *bytes);
  *   info      device int, see above.
  * prec 1, 2 or 4.  Requires 1 <= n <= m <= MGS_MAX_ROWS_{DD,QD}.
  * Schedule: in dd and double with m <= 64 and at most 64 columns of [A b],
- * one workgroup (a column per wave slot, q vectors through LDS; for double
- * the kernel of mgs_lstsq_batched on one system; qd takes it only when
- * mgs_qr_schedule asks for it, within 159 KiB of q vectors: 64 m n bytes);
+ * one workgroup (the kernel of mgs_lstsq_batched on one system; qd takes it
+ * only when mgs_qr_schedule asks for it, for 64 m n <= 162816);
  * in dd and double when
  * every column fits in the register file of the device (dd: m <= 1024 and
  * at most 5 columns per compute unit, 8 when m <= 512, e.g. 1024 x 1024
@@ -273,8 +272,8 @@ int mgs_qr64(int m, int n, const double *A, int lda, const double *b, double *Q,
  * completion is unspecified and each system's results are the same as for a
  * batch of one.
  *   prec 1, 2 or 4.  Requires 1 <= n <= m <= 64, at most 64 columns of
- *   [A b], and 16 prec m n <= 162816 (the q vectors of a system in LDS;
- *   binding for qd only: e.g. m = n = 50).  batch >= 0 (0: nothing to do,
+ *   [A b], and 16 prec m n <= 162816 (binding for qd only: e.g.
+ *   m = n = 50).  batch >= 0 (0: nothing to do,
  *   pointers not examined).
  *   A  [in]  batch systems back to back: system s at A + s*2*prec*lda*n,
  *            each m x n planar with leading dimension lda >= m (a torch view
@@ -330,8 +329,8 @@ int mgs_poly_eval(int batch, int neq, int nvar, int nmon, int nvpm, int prec, co
 /*
  * mgs_newton_workspace_size -- bytes of device workspace mgs_newton_batched
  * needs (J, -f, R and the correction of every point; for a single point in
- * dd or qd also Q^H b, a status word and the workspace of mgs_qr's
- * single-system schedule).
+ * qd also Q^H b, a status word and the workspace of mgs_qr's single-system
+ * schedule).
  */
 int mgs_newton_workspace_size(int batch, int neq, int nvar, int prec, size_t *bytes);
 
@@ -341,7 +340,7 @@ int mgs_newton_workspace_size(int batch, int neq, int nvar, int prec, size_t *by
  * as the least-squares solution of J d = -f by the MGS of Figure 1 on
  * [J -f] (Equation (1)) and the back substitution of Figure 3 (the
  * mgs_lstsq_batched kernel, one workgroup per point; for a single point in
- * dd or qd the single-system schedules of mgs_qr and ls_backsolve), then
+ * qd the single-system schedules of mgs_qr and ls_backsolve), then
  * x += d.
  *   Requires nvar <= neq <= 64 and 16 prec neq nvar <= 162816 (the MGS
  *   limits of mgs_lstsq_batched), iters >= 0.

@@ -417,6 +417,20 @@ struct PrecDD {
   struct Acc {
     double sr, cr, si, ci;  // exact leading sum and low-order word, re / im
   };
+  // One part of an Acc (the real part is its first half).
+  struct RAcc {
+    double s, c;
+  };
+  __device__ static __forceinline__ void racc_merge(RAcc &a, const RAcc &b) {
+    double t;
+    two_sum(a.s, b.s, a.s, t);
+    a.c = (a.c + b.c) + t;
+  }
+  __device__ static __forceinline__ R racc_value(const RAcc &a) {
+    R v;
+    two_sum(a.s, a.c, v.h, v.l);
+    return v;
+  }
 
   __device__ static __forceinline__ C load(const double *p, size_t plane) {
     C v;
@@ -603,6 +617,9 @@ struct PrecQD {
   struct Acc {
     qdsum re, im;
   };
+  using RAcc = qdsum;
+  __device__ static __forceinline__ void racc_merge(RAcc &a, const RAcc &b) { qd_merge(a, b); }
+  __device__ static __forceinline__ R racc_value(const RAcc &a) { return qd_value(a); }
 
   __device__ static __forceinline__ C load(const double *p, size_t plane) {
     C v;
@@ -703,6 +720,9 @@ struct PrecD {
   struct Acc {
     double re, im;
   };
+  using RAcc = double;
+  __device__ static __forceinline__ void racc_merge(RAcc &a, const RAcc &b) { a += b; }
+  __device__ static __forceinline__ R racc_value(const RAcc &a) { return a; }
   __device__ static __forceinline__ C load(const double *p, size_t plane) { return {p[0], p[plane]}; }
   __device__ static __forceinline__ void store(double *p, size_t plane, const C &v) {
     p[0] = v.re;

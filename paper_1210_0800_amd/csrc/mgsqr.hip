@@ -16,7 +16,6 @@
 #include "newton_kernels.hpp"
 #include "precision_kernels.hpp"
 #include "resident_kernels.hpp"
-#include "small_kernels.hpp"
 
 using namespace mgsq;
 
@@ -652,67 +651,62 @@ int res_launch(const StepArgs &s, void *sync, double *u, hipStream_t st) {
   return 1;
 }
 
-// dd systems of at most SMALL_MAX_ROWS rows and SMALL_MAX_COLS columns of
-// [A b]: one workgroup (returns 1 when the shape does not apply).
-int small_launch_dd(const StepArgs &s, hipStream_t st) {
-  if (s.m > SMALL_MAX_ROWS || s.ncols > SMALL_MAX_COLS) return 1;
-  DevInfo d;
-  if (!dev_info(d)) return 1;
-  SmallArgs a;
-  a.m = s.m;
-  a.n = s.n;
-  a.ncols = s.ncols;
-  a.A = s.A;
-  a.lda = s.lda;
-  a.planeA = s.planeA;
-  a.b = s.b;
-  a.Q = s.Q;
-  a.ldq = s.ldq;
-  a.planeQ = s.planeQ;
-  a.R = s.R;
-  a.ldr = s.ldr;
-  a.planeR = s.planeR;
-  a.y = s.y;
-  a.rho = s.rho;
-  a.info = s.info;
-  a.spin_ticks = d.wclk_khz * 2000;  // 2 s
-  a.jitter = g_jitter.load(std::memory_order_relaxed);
-  hipLaunchKernelGGL(mgs_small_kernel, dim3(1), dim3(64 * SMALL_WAVES), 0, st, a);
+// Small systems: one workgroup per system (returns MGS_ERR_DIMS when the
+// columns do not fit the shape's slots).
+template <class P, int RPL, int SL, int NW, int WPE>
+int batched_launch(const BatArgs &a, hipStream_t st) {
+  if (a.m > BAT_RG * RPL || a.ncols - 1 > BAT_CG * NW * SL) return MGS_ERR_DIMS;
+  if (a.batch == 0) return MGS_OK;
+  hipLaunchKernelGGL((mgs_batched_kernel<P, RPL, SL, NW, WPE>), dim3(a.batch), dim3(64 * NW), 0, st, a);
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
-
-// Batched systems: one workgroup per system (returns MGS_ERR_DIMS when one
-// system's q vectors do not fit in LDS).  Waves per system: 4 (FP64), 8
-// (dd), 16 (qd), so that a slot of every wave holds a column in registers
-// and several systems share a compute unit.
-template <class P, int NW, int CPW>
-int batched_launch(const BatArgs &a, hipStream_t st) {
-  static_assert(NW * CPW <= BAT_MAX_COLS, "slots beyond the flags");
-  if (a.ncols > NW * CPW) return MGS_ERR_DIMS;  // every column of [A b] needs a slot
-  const size_t shmem = sizeof(double) * 2 * P::L * (size_t)a.n * a.m;
-  if (shmem > BAT_LDS_BYTES) return MGS_ERR_DIMS;
-  if (a.batch == 0) return MGS_OK;
-  auto kern = mgs_batched_kernel<P, NW, CPW>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)shmem) != hipSuccess)
-    return MGS_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3(a.batch), dim3(64 * NW), shmem, st, a);
-  return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
+// The shape by batch size, all with the same results.  While the systems
+// alone do not fill the card, several waves each shorten a system's chain;
+// beyond, one wave per system does the least work (pairs of slots share a
+// sum, nothing is synchronised).  Measured, 32 x 32, us per call for 8
+// waves of 1 slot against 1 wave of 8: double 41 / 50 at 1 system, 53 / 56
+// at 512, 94 / 63 at 1024; dd 80 / 130, 117 / 141, 215 / 148.  qd (one
+// wave per SIMD), 4 waves of 2 slots, 2 of 4, 1 of 8: 447 / 631 / 1006 at 1,
+// 479 / 639 / 1048 at 256, 901 / 668 / 1088 at 512, 1796 / 1277 / 1134 at
+// 1024.  More than 32 slotted columns or rows: fewer slots per wave, as the
+// registers allow (64 x 63, 4000 systems: double 2 x 8 0.90 ms, 4 x 4 1.16,
+// 8 x 2 1.50; dd 3.92, 3.82 with scratch, 4.32).
+template <class P, int RPL>
+int batched_shape(const BatArgs &a, int cus, hipStream_t st) {
+  const int slotted = a.ncols - 1;  // column 1 has no slot
+  if constexpr (P::L == 4) {
+    if constexpr (RPL == 4) {
+      if (slotted > 32) return batched_launch<P, RPL, 4, 4, 1>(a, st);
+      if (a.batch <= cus) return batched_launch<P, RPL, 2, 4, 1>(a, st);
+      return batched_launch<P, RPL, 4, 2, 1>(a, st);
+    } else {
+      if (a.batch <= cus) return batched_launch<P, RPL, 2, 4, 1>(a, st);
+      if (a.batch <= 2 * cus) return batched_launch<P, RPL, 4, 2, 1>(a, st);
+      return batched_launch<P, RPL, 8, 1, 1>(a, st);
+    }
+  } else {
+    const bool few = a.batch <= 2 * cus;
+    if constexpr (RPL == 4) {
+      if (slotted > 32)
+        return few ? batched_launch<P, RPL, 2, 8, 2>(a, st) : batched_launch<P, RPL, 8, 2, 1>(a, st);
+      return few ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 1>(a, st);
+    } else {
+      return few ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 2>(a, st);
+    }
+  }
+}
+template <class P>
+int batched_dispatch(const BatArgs &a, hipStream_t st) {
+  DevInfo d;
+  const int cus = dev_info(d) && d.cus > 0 ? d.cus : 256;
+  if (a.m <= BAT_RG) return batched_shape<P, 1>(a, cus, st);
+  if (a.m <= 2 * BAT_RG) return batched_shape<P, 2>(a, cus, st);
+  return batched_shape<P, 4>(a, cus, st);
 }
 int batched_dispatch(int prec, const BatArgs &a, hipStream_t st) {
-  if (prec == 1) {
-    if (a.ncols <= 36) return batched_launch<PrecD, 12, 3>(a, st);
-    return batched_launch<PrecD, 16, 4>(a, st);
-  }
-  if (prec == 2) {
-    if (a.ncols <= 36) return batched_launch<PrecDD, 12, 3>(a, st);
-    return batched_launch<PrecDD, 16, 4>(a, st);
-  }
-  // qd: 16 waves of 4 slots cap a wave at 128 registers (four waves per
-  // SIMD), which spills; up to 36 columns, 12 waves of 3 slots (three
-  // waves per SIMD, 168 registers)
-  if (a.ncols <= 36) return batched_launch<PrecQD, 12, 3>(a, st);
-  return batched_launch<PrecQD, 16, 4>(a, st);
+  if (prec == 1) return batched_dispatch<PrecD>(a, st);
+  if (prec == 2) return batched_dispatch<PrecDD>(a, st);
+  return batched_dispatch<PrecQD>(a, st);
 }
 bool batched_fits(int m, int n, int ncols, int prec) {
   return m <= BAT_MAX_ROWS && ncols <= BAT_MAX_COLS && sizeof(double) * 2 * prec * (size_t)n * m <= BAT_LDS_BYTES;
@@ -742,7 +736,7 @@ void *scratch_address() {
 
 // Newton: J (batch systems of neq x nvar), b (batch x neq), R (batch x
 // nvar x nvar), d (batch x nvar), each in the working precision; for one
-// point in dd or qd also y (nvar), an int and the workspace of mgs_qr.
+// point in qd also y (nvar), an int and the workspace of mgs_qr.
 struct NewtonWork {
   double *A, *b, *R, *d, *y;
   int *info2;
@@ -767,7 +761,7 @@ NewtonWork newton_layout(int batch, int neq, int nvar, int prec, void *base) {
   w.info2 = nullptr;
   w.qrw = nullptr;
   w.qrw_bytes = 0;
-  if (batch == 1 && prec >= 2) {
+  if (batch == 1 && prec == 4) {
     w.y = take(NP * nvar);
     w.info2 = reinterpret_cast<int *>(take(1));
     w.qrw_bytes = qr_work_bytes(neq, nvar, prec);
@@ -789,10 +783,10 @@ int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *v
                        coef, x, w.A, w.b, true);
     if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
     if (w.qrw != nullptr) {
-      // One point (dd, qd): the single-system schedules of mgs_qr (dd: one
-      // workgroup of 16 waves; qd: one column per launch), quicker than a
-      // batch of one, then the back substitution (its own status word: a
-      // zero pivot is already reported by the factorisation).
+      // One point in qd: mgs_qr's single-system schedule (one column per
+      // launch), quicker than a batch of one, then the back substitution
+      // (its own status word: a zero pivot is already reported by the
+      // factorisation).
       int rc = mgs_qr_schedule(neq, nvar, P::L, w.A, neq, w.A, neq, w.R, nvar, w.b, w.y, nullptr, w.qrw, w.qrw_bytes,
                                info, MGS_SCHED_AUTO, reinterpret_cast<mgs_stream_t>(st));
       if (rc != MGS_OK) return rc;
@@ -912,13 +906,9 @@ int mgs_qr_schedule(int m, int n, int prec, const double *A, int lda, double *Q,
   const int mode = schedule;
   if (mode == MGS_SCHED_AUTO || mode == MGS_SCHED_SMALL) {
     int rc = 1;
-    if (prec == 2) {
-      rc = small_launch_dd(a, st);
-    } else if (batched_fits(m, n, a.ncols, prec) && (prec == 1 || mode == MGS_SCHED_SMALL)) {
-      // FP64 (and qd when asked for): the batched kernel on a batch of
-      // one.  A single qd system takes the per-panel schedule by default:
-      // the batched kernel's qd instantiation holds 16 waves per system and
-      // spills to scratch (0.94 ms for 32 x 32 against ~0.5 ms).
+    if (batched_fits(m, n, a.ncols, prec) && (prec <= 2 || mode == MGS_SCHED_SMALL)) {
+      // Double and dd (and qd when asked for): the batched kernel on a batch
+      // of one.
       DevInfo d;
       if (dev_info(d)) {
         BatArgs ba;

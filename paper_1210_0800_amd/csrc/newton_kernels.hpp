@@ -22,6 +22,24 @@ constexpr int NT_MAX_VARS = 63;  // variables (columns of [J -f] <= 64)
 constexpr int NT_MAX_VPM = 8;    // variables per monomial
 constexpr int NT_MAX_DEG = 16;   // exponent bound
 
+// Lane 63's accumulator, wave-uniform.
+template <class P>
+__device__ __forceinline__ typename P::Acc acc_lane63(const typename P::Acc &v) {
+  using Acc = typename P::Acc;
+  constexpr int NA = sizeof(Acc) / sizeof(double);
+  Acc r;
+  double *pr = reinterpret_cast<double *>(&r);
+  const double *pv = reinterpret_cast<const double *>(&v);
+#pragma unroll
+  for (int c = 0; c < NA; ++c) {
+    const long long bits = __double_as_longlong(pv[c]);
+    const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), 63);
+    const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), 63);
+    pr[c] = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+  }
+  return r;
+}
+
 template <class P>
 __device__ __forceinline__ typename P::C nt_mul(const typename P::C &a, const typename P::C &b) {
   typename P::Acc acc;
