@@ -345,17 +345,24 @@ __device__ __forceinline__ td qd_residual(const qd &c, const qd &a, const qd &b)
   return d;
 }
 
-// 1/b: the dd reciprocal (about 2^-104), one Newton step x + x (1 - b x)
-// to about 2^-208 (the correction only needs dd precision), and one more
-// whose correction only needs FP64.
+// v + v c for a correction c of at most about 2^-100.
+__device__ __forceinline__ qd qd_correct(const qd &v, const td &c) {
+  double p, q, p1, q1, p2, q2;
+  two_prod(v.x0, c.h, p, q);
+  two_prod(v.x0, c.l, p1, q1);
+  two_prod(v.x1, c.h, p2, q2);
+  qdsum r = qd_sum_from(v);
+  qd_acc(r, qdprod{0.0, 0.0, p, q, p1, p2});
+  r.x4 += __fma_rn(v.x0, c.ll, __fma_rn(v.x1, c.l, __fma_rn(v.x2, c.h, q1 + q2)));
+  return qd_renorm5(r.x0, r.x1, r.x2, r.x3, r.x4);
+}
+// 1/b from the dd reciprocal y (about 2^-104): with e = 1 - b y, formed
+// once, 1/b = y / (1 - e) = y (1 + e + e^2 + O(e^3)).
 __device__ __forceinline__ qd qd_recip(const qd &b) {
-  const dd x = dd_recip({b.x0, b.x1});
-  const qd one = qd_from(1.0);
-  const td e = qd_residual(one, b, {x.h, x.l, 0.0, 0.0});
-  const dd h = dd_mul(x, {e.h, e.l});
-  const qd y = qd_renorm(x.h, x.l, h.h, h.l);
-  const td r = qd_residual(one, b, y);
-  return qd_renorm5(y.x0, y.x1, y.x2, y.x3, y.x0 * r.h);
+  const dd r = dd_recip({b.x0, b.x1});
+  const qd y = {r.h, r.l, 0.0, 0.0};
+  const td e = qd_residual(qd_from(1.0), b, y);
+  return qd_correct(y, {e.h, e.l, __fma_rn(e.h, e.h, e.ll)});
 }
 // Inverse square root of s > 0 to about 2^-103, as a dd: one Newton step
 // y + y (1 - s y^2) / 2 from the FP64 one, whose relative error (about
@@ -372,17 +379,6 @@ __device__ __forceinline__ dd qd_rsqrt_dd(const qd &s) {
   dd out;
   fast_two_sum(y, 0.5 * (y * r), out.h, out.l);
   return out;
-}
-// v + v c for a correction c of at most about 2^-100.
-__device__ __forceinline__ qd qd_correct(const qd &v, const td &c) {
-  double p, q, p1, q1, p2, q2;
-  two_prod(v.x0, c.h, p, q);
-  two_prod(v.x0, c.l, p1, q1);
-  two_prod(v.x1, c.h, p2, q2);
-  qdsum r = qd_sum_from(v);
-  qd_acc(r, qdprod{0.0, 0.0, p, q, p1, p2});
-  r.x4 += __fma_rn(v.x0, c.ll, __fma_rn(v.x1, c.l, __fma_rn(v.x2, c.h, q1 + q2)));
-  return qd_renorm5(r.x0, r.x1, r.x2, r.x3, r.x4);
 }
 // sqrt(s) and 1/sqrt(s) together, s > 0, from the dd inverse square root y
 // and x = s y: with e = 1 - x y (about 2^-102, formed once) both are their
@@ -598,6 +594,7 @@ struct PrecDD {
   __device__ static __forceinline__ C scale(const C &a, const R &s) {
     return {dd_mul(a.re, s), dd_mul(a.im, s)};
   }
+  __device__ static __forceinline__ R rmul(const R &a, const R &b) { return dd_mul(a, b); }
   __device__ static __forceinline__ R sqrt_(const R &s) { return dd_sqrt(s); }
   __device__ static __forceinline__ R recip(const R &s) { return dd_recip(s); }
   __device__ static __forceinline__ void sqrt_recip(const R &s, R &root, R &inv) { dd_sqrt_recip(s, root, inv); }
@@ -693,6 +690,7 @@ struct PrecQD {
     a.im = qd_value(si);
   }
   __device__ static __forceinline__ C scale(const C &a, const R &s) { return {qd_mul(a.re, s), qd_mul(a.im, s)}; }
+  __device__ static __forceinline__ R rmul(const R &a, const R &b) { return qd_mul(a, b); }
   __device__ static __forceinline__ R sqrt_(const R &s) { return qd_sqrt(s); }
   __device__ static __forceinline__ R recip(const R &s) { return qd_recip(s); }
   __device__ static __forceinline__ void sqrt_recip(const R &s, R &root, R &inv) { qd_sqrt_recip(s, root, inv); }
@@ -774,6 +772,7 @@ struct PrecD {
     a.im = __fma_rn(-r.im, q.re, a.im);
   }
   __device__ static __forceinline__ C scale(const C &a, const R &s) { return {a.re * s, a.im * s}; }
+  __device__ static __forceinline__ R rmul(const R &a, const R &b) { return a * b; }
   __device__ static __forceinline__ R sqrt_(const R &s) { return sqrt(s); }
   __device__ static __forceinline__ R recip(const R &s) { return 1.0 / s; }
   __device__ static __forceinline__ bool ok_norm(const R &s) { return s > 0.0 && s < INFINITY; }

@@ -218,7 +218,8 @@ __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
 // Common end of a bounded wait: true (and the abort flag set, info
 // written) once the wall-clock limit has passed, or when another wave has
 // aborted.
-__device__ __forceinline__ bool res_give_up(const ResArgs &a, long long t0) {
+template <class Args>
+__device__ __forceinline__ bool res_give_up(const Args &a, long long t0) {
   if (__builtin_amdgcn_readfirstlane(
           (int)__hip_atomic_load(a.sync + RES_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0)
     return true;
@@ -233,7 +234,8 @@ __device__ __forceinline__ bool res_give_up(const ResArgs &a, long long t0) {
 // Waits until wave `wave` of the owners has published at least k+1
 // columns.  `seen` caches the last observed count (wave-uniform).
 // Returns false on abort or time-out.
-__device__ __forceinline__ bool res_wait(const ResArgs &a, int k, int wave, int &seen) {
+template <class Args>
+__device__ __forceinline__ bool res_wait(const Args &a, int k, int wave, int &seen) {
   if (seen > k) return true;
   const long long t0 = wall_clock64();
   unsigned int *cnt = a.sync + 16 * wave;
