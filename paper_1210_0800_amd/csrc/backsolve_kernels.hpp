@@ -1,36 +1,36 @@
-// Back substitution of Section 6, Figure 3 spread over workgroups: for
-// k = n..1, x_k = y_k / r_kk, then y_j -= r_jk x_k for j < k (and its
-// mirror image, the forward substitution R^H w = g of the adjoint).
+// Triangular solves: the back substitution of Section 6, Figure 3 (for
+// k = n..1, x_k = y_k / r_kk, then y_j -= r_jk x_k for j < k) and its mirror
+// image, the forward substitution R^H w = g of the adjoint.
 //
-// Workgroup j is one wave holding rows [64j, 64j + 64) of y, one row per
-// lane.  It applies r_ic x_c to its rows for every column c above its
-// block as soon as x_c is published, in descending c, then solves its own
-// diagonal block: the lane of row c forms x_c (times the reciprocal of
-// r_cc, formed up front), every lane gets it by readlane, the owner lane
-// publishes it, and the rows above c in the block receive r_ic x_c.  The
-// entries of R (and of x above the block) are loaded eight columns ahead,
-// so the loads stay off the serial chain.  So
-// every y_i receives r_ic x_c in the order c = n, n-1, ..., i+1 with the
-// operations of the column-oriented loop, and x is bitwise that of the
-// one-workgroup kernel; only the schedule differs: the blocks below are
-// already absorbed when a block's turn comes, and x_c reaches the block
-// above one entry at a time, so the serial chain is one multiply, one
-// broadcast and one update per column plus one hand-off per block.
+// A lane holds one part (real or imaginary) of one row of y, so a wave
+// holds 32 rows and a step costs it half the operations of a complex row
+// per lane; a workgroup is a block of up to 4 waves (128 rows), one per SIMD:
+// a wave that absorbs columns must keep up with the one that solves, and two
+// on a SIMD do not (dd n = 1024: 481 us with 8 waves, 320 with 4).  Each wave
+// applies r_ic x_c to its rows for every column c solved before its own, in
+// solve order, as x_c appears, then solves its own 32 columns: the lanes of
+// row c form x_c (times the reciprocal of r_cc, formed up front), all lanes
+// get it by readlane, and the rows it reaches receive r_ic x_c.  So every
+// y_i receives its products in the order of the column-oriented loop.
 //
-// Publication: x is filled with the empty marker (a signalling NaN, which
-// no arithmetic produces) by bs_mark_kernel before the launch; x_c is
-// written with device-scope stores and read with device-scope loads until
-// no marker is left.  Every wait is bounded by a wall-clock limit
-// (MGS_INFO_SYNC_TIMEOUT in info).  The launch is cooperative: every
-// workgroup resident.
+// What bounds it is that chain: one multiply, one broadcast and one update
+// per column.  x_c goes to the waves of the same workgroup through LDS and
+// to the other workgroups through x itself (device-scope stores), both
+// filled with the empty marker (a signalling NaN, which no arithmetic
+// produces) beforehand, so that readers poll the data.  The entries of R are
+// loaded RING columns ahead.  Every wait is bounded by a wall-clock limit
+// (MGS_INFO_SYNC_TIMEOUT in info).  A launch of several workgroups is
+// cooperative (all resident); one workgroup can also take all blocks in
+// turn.
 #pragma once
 #include "../../include/mgsqr.h"
 #include "resident_kernels.hpp"
 
 namespace mgsq {
 
-constexpr int BP_ROWS = 64;  // rows per workgroup (one wave)
-constexpr int BP_RING = 8;   // columns of R (and entries of x) loaded ahead
+constexpr int TS_ROWS = 32;   // rows of a wave
+constexpr int TS_WAVES = 4;   // waves of a workgroup, at most: one per SIMD
+constexpr int TS_BLOCK = TS_ROWS * TS_WAVES;
 
 // x := empty marker (all planes), info := 0; nothing when *skip != 0.
 template <int L>
@@ -44,189 +44,185 @@ __global__ __launch_bounds__(256) void bs_mark_kernel(int n, double *x, int *inf
   }
 }
 
-// True when any limb of v carries the empty marker.
-template <class P>
-__device__ __forceinline__ bool bs_empty(const typename P::C &v) {
-  bool miss = false;
-  const double *pv = reinterpret_cast<const double *>(&v);
-#pragma unroll
-  for (int q = 0; q < 2 * P::L; ++q) miss = miss || __double_as_longlong(pv[q]) == RES_EMPTY;
-  return miss;
-}
-
-// v when pick, else w, elementwise (selects, no branch).
-template <class P>
-__device__ __forceinline__ typename P::C bs_pick(bool pick, const typename P::C &v, const typename P::C &w) {
-  typename P::C r;
-  double *pr = reinterpret_cast<double *>(&r);
-  const double *pv = reinterpret_cast<const double *>(&v);
-  const double *pw = reinterpret_cast<const double *>(&w);
-#pragma unroll
-  for (int q = 0; q < 2 * P::L; ++q) pr[q] = pick ? pv[q] : pw[q];
-  return r;
-}
-
-// The triangular solve across workgroups.  FWD = false: R x = y (back
-// substitution, Figure 3: columns descending, rows above the pivot
-// updated).  FWD = true: R^H x = y (the adjoint's forward substitution:
-// columns ascending, entry (i, c) of R^H is conj(r_ci), rows below the
-// pivot updated), with the same operations per row as the one-workgroup
-// blocked kernels.
-//
-// Memory operations in the loops below are unconditional (addresses
-// clamped into the arrays, unused values discarded by selects) and the loops
-// run whole rings, so that the compiler can count the loads in flight and
-// wait only for the one a step consumes.
+// FWD = false: R x = y (columns descending, rows above the pivot updated).
+// FWD = true: R^H x = y (columns ascending, entry (i, c) of R^H is
+// conj(r_ci), rows below the pivot updated).  Workgroup g takes the blocks
+// g, g + G, ... of blockDim / 2 rows in solve order; marked: x holds the
+// empty marker (needed for more than one block), else the one block clears
+// info itself.
 template <class P, bool FWD>
-__global__ __launch_bounds__(BP_ROWS) void trsv_pipe_kernel(int n, const double *R, int ldr, size_t planeR,
-                                                            const double *y, size_t planeY, double *x, int *info,
-                                                            const int *skip, long long spin_ticks,
-                                                            long long *trace, unsigned jitter) {
+__global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double *R, int ldr, size_t planeR,
+                                                             const double *y, size_t planeY, double *x, int *info,
+                                                             const int *skip, int marked, long long spin_ticks,
+                                                             unsigned jitter) {
   if (skip != nullptr && *skip != 0) return;
   using C = typename P::C;
   using Rl = typename P::R;
-  constexpr int DIR = FWD ? 1 : -1;  // column order
-  const int lane = threadIdx.x;
-  const int r0 = blockIdx.x * BP_ROWS;
-#ifdef MGS_TRACE
-  // diagnostic builds: wall-clock stamps per workgroup (start, phase 1 done,
-  // phase 2 done)
-  if (trace != nullptr && lane == 0) trace[blockIdx.x * 4] = (long long)wall_clock64();
-#else
-  (void)trace;
-#endif
-  const int r1 = r0 + BP_ROWS < n ? r0 + BP_ROWS : n;
-  const int i = r0 + lane;
-  const bool mine = i < r1;
-  const int ic = mine ? i : n - 1;  // clamped row for loads
-  C yv = P::load(y + ic, planeY);
-  const C dg = P::load(R + (size_t)ic * ldr + ic, planeR);
-  Rl inv = P::recip(dg.re);
-  if (!mine) {
-    yv = P::czero();
-    inv = P::rzero();
-  }
-  if (mine && !P::ok_norm(dg.re) && info != nullptr) info_first_bad(info, i + 1);
-  // Entry (row i, column col) of the triangular matrix; col clamped.
-  auto rload = [&](int col) __attribute__((always_inline)) {
-    const int cl = col < 0 ? 0 : (col >= n ? n - 1 : col);
-    if constexpr (FWD)
-      return P::conj(P::load(R + (size_t)ic * ldr + cl, planeR));
-    else
-      return P::load(R + (size_t)cl * ldr + ic, planeR);
-  };
-  auto xload = [&](int col) __attribute__((always_inline)) {
-    bool m = false;
-    const int cl = col < 0 ? 0 : (col >= n ? n - 1 : col);
-    return res_coh_load<P>(x + cl, (size_t)n, m);
-  };
-  // The block's own columns in solve order in a ring (slot t: the t-th,
-  // (t+8)-th, ... column).
-  const int c2 = FWD ? r0 : r1 - 1;
-  C rb[BP_RING];
-#pragma unroll
-  for (int t = 0; t < BP_RING; ++t) rb[t] = rload(c2 + DIR * t);
-  // 1. The columns solved before the block (above it for R x = y, left of
-  // it for R^H x = y), in solve order, in chunks of CH columns: the entries
-  // and x values of the next chunk are loaded while the current one is
-  // applied (two buffers, so no register moves between chunks); at the
-  // front, where x arrives one entry at a time, each entry is applied as it
-  // comes.
-  const long long t0 = wall_clock64();
-  {
-    constexpr int CH = P::L == 4 ? 4 : 8;
-    const int ncol = FWD ? r0 : n - r1;  // columns of phase 1
-    const int c1 = FWD ? 0 : n - 1;      // the first of them
-    C ra0[CH], xa0[CH], ra1[CH], xa1[CH];
-    auto fetch = [&](int s0, C (&rr)[CH], C (&xx)[CH]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        rr[u] = rload(c1 + DIR * (s0 + u));
-        xx[u] = xload(c1 + DIR * (s0 + u));
-      }
+  constexpr int L = P::L, DIR = FWD ? 1 : -1;
+  constexpr int RING = L == 4 ? 4 : 8;  // columns of R loaded ahead
+  __shared__ double xs[2 * L][TS_BLOCK];  // the block's x, [plane][row], empty until solved
+  // the wave's number as a scalar, so that all addresses of a step but the
+  // lane's row are scalar arithmetic
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, part = lane & 1;
+  const int nwave = blockDim.x >> 6, rows = nwave * TS_ROWS;
+  const int nblk = (n + rows - 1) / rows;
+  if (!marked && tid == 0 && info != nullptr) *info = 0;
+  for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int r0 = (FWD ? b : nblk - 1 - b) * rows, r1 = min(r0 + rows, n);  // the block
+    __syncthreads();
+    for (int i = tid; i < 2 * L * TS_BLOCK; i += blockDim.x) (&xs[0][0])[i] = __longlong_as_double(RES_EMPTY);
+    __syncthreads();
+    const int w0 = r0 + wave * TS_ROWS, w1 = min(w0 + TS_ROWS, n);  // the wave's rows
+    if (w0 >= n) continue;
+    const int i = w0 + (lane >> 1);
+    const bool mine = i < w1;
+    const int ic = mine ? i : n - 1;  // clamped row for loads
+    // Column c's entry of row i as this lane's factors of Re x_c and Im x_c:
+    // (re, -im) for the real part, (im, re) for the imaginary one, of the
+    // conjugate when FWD.  Rows that a column does not reach
+    // (already solved) take the update too: their y is no longer used.
+    struct Entry {
+      Rl a, b;
     };
-    // Applies the chunk starting at step s0, in order, each entry as soon
-    // as it (and every earlier one) is out: the entries already applied are
-    // kept by the selects, the rest reloaded while waiting.  False on
-    // time-out.
-    auto consume = [&](int s0, const C (&rr)[CH], C (&xx)[CH]) __attribute__((always_inline)) {
-      int done = 0;
-      while (true) {
-        int avail = 0;
-        bool gap = false;
+    const double *pa = R + (size_t)part * planeR + (FWD ? (size_t)ic * ldr : (size_t)ic);
+    const double *pb = R + (size_t)(1 - part) * planeR + (FWD ? (size_t)ic * ldr : (size_t)ic);
+    const unsigned long long neg = 1ull << 63;
+    const unsigned long long na = FWD && part == 1 ? neg : 0, nb = !FWD && part == 0 ? neg : 0;
+    auto rload = [&](int c) __attribute__((always_inline)) {
+      const int cl = FWD ? min(c, n - 1) : max(c, 0);  // loads run past the last column
+      const size_t at = FWD ? (size_t)cl : (size_t)cl * ldr;
+      Entry e;
+      double *ea = reinterpret_cast<double *>(&e.a), *eb = reinterpret_cast<double *>(&e.b);
 #pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          const bool here = s0 + u >= ncol || __ballot(bs_empty<P>(xx[u])) == 0;
-          gap = gap || !here;
-          if (!gap) avail = u + 1;
-        }
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          C yn = yv;
-          P::upd(yn, rr[u], xx[u]);
-          yv = bs_pick<P>(mine && u >= done && u < avail && s0 + u < ncol, yn, yv);
-        }
-        done = avail;
-        if (done == CH) return true;
-        if (wall_clock64() - t0 > spin_ticks) {
-          if (lane == 0 && info != nullptr)
-            __hip_atomic_store(info, MGS_INFO_SYNC_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          return false;
-        }
-        __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-        for (int u = 0; u < CH; ++u) xx[u] = xload(c1 + DIR * (s0 + u));
+      for (int l = 0; l < L; ++l) {
+        ea[l] = pa[at + (size_t)(2 * l) * planeR];
+        eb[l] = pb[at + (size_t)(2 * l) * planeR];
       }
+      return e;
     };
-    const int nch = (ncol + CH - 1) / CH;
-    int s0 = 0;
-    fetch(s0, ra0, xa0);
-#pragma unroll 1
-    for (int k = 0; k < nch; k += 2) {
-      res_jitter(jitter, (unsigned)k);
-      fetch(s0 + CH, ra1, xa1);
-      if (!consume(s0, ra0, xa0)) return;
-      s0 += CH;
-      if (k + 1 >= nch) break;
-      fetch(s0 + CH, ra0, xa0);
-      if (!consume(s0, ra1, xa1)) return;
-      s0 += CH;
-    }
-  }
-#ifdef MGS_TRACE
-  if (trace != nullptr && lane == 0) trace[blockIdx.x * 4 + 1] = (long long)wall_clock64();
-#endif
-  // 2. The block itself: x_c from its lane, broadcast, applied to the rows
-  // it reaches (R from the ring, BP_RING columns ahead).  Each lane keeps
-  // its own x (the empty marker until solved) and every step all lanes
-  // store theirs, so x_c is out one step after it is formed, with no branch.
-  C xown;
-  {
-    double *po = reinterpret_cast<double *>(&xown);
+    auto flip = [&](const Rl &v, unsigned long long bits) __attribute__((always_inline)) {
+      Rl r;
+      double *pr = reinterpret_cast<double *>(&r);
+      const double *pv = reinterpret_cast<const double *>(&v);
 #pragma unroll
-    for (int q = 0; q < 2 * P::L; ++q) po[q] = __longlong_as_double(RES_EMPTY);
-  }
-  const int rounds2 = (r1 - r0 + BP_RING - 1) / BP_RING;
-  int cc = c2;
-#pragma unroll 1
-  for (int rd = 0; rd < rounds2; ++rd) {
-    res_jitter(jitter, 0x10000u + (unsigned)rd);
+      for (int l = 0; l < L; ++l) pr[l] = __longlong_as_double(__double_as_longlong(pv[l]) ^ bits);
+      return r;
+    };
+    auto update = [&](Rl &v, const Entry &e, const Rl &xr, const Rl &xi) __attribute__((always_inline)) {
+      P::upd_part(v, FWD ? flip(e.a, na) : e.a, xr, FWD ? e.b : flip(e.b, nb), xi);
+    };
+    Rl yv, xown;  // y_i and, once solved, x_i (the empty marker before)
+    {
+      double *pv = reinterpret_cast<double *>(&yv), *px = reinterpret_cast<double *>(&xown);
 #pragma unroll
-    for (int t = 0; t < BP_RING; ++t) {
-      const int k = cc - r0;  // lane of row cc (outside [0, 64) past the block)
-      const C xk = bs_readlane<P>(P::scale(yv, inv), k & 63);
-      xown = bs_pick<P>(lane == k, xk, xown);
-      C yn = yv;
-      P::upd(yn, rb[t], xk);
-      yv = bs_pick<P>(FWD ? lane > k : lane < k, yn, yv);
-      if (mine) res_coh_store<P>(x + i, (size_t)n, xown);
-      rb[t] = rload(cc + DIR * BP_RING);
-      cc += DIR;
+      for (int l = 0; l < L; ++l) {
+        pv[l] = y[ic + (size_t)(2 * l + part) * planeY];
+        px[l] = __longlong_as_double(RES_EMPTY);
+      }
     }
+    const Rl dg = P::load(R + (size_t)ic * ldr + ic, planeR).re;
+    Rl inv = P::recip(dg);
+    if (!mine) {
+      yv = P::rzero();
+      inv = P::rzero();
+    }
+    if (mine && part == 0 && !P::ok_norm(dg) && info != nullptr) info_first_bad(info, i + 1);
+    const int own = FWD ? w0 : w1 - 1;  // first own column
+    Entry rd[RING];
+#pragma unroll
+    for (int t = 0; t < RING; ++t) rd[t] = rload(own + DIR * t);
+
+    // Columns c1, c1 + DIR, ... (count of them), x from `at(column)`, the
+    // address of its first limb with planes `plane` apart; in chunks of 32:
+    // lane 2 j + p holds part p of the chunk's column j, once it is there.
+    auto absorb = [&](int c1, int count, auto at, size_t plane) __attribute__((always_inline)) {
+      if (count <= 0) return true;
+      Entry ra[RING];
+#pragma unroll
+      for (int t = 0; t < RING; ++t) ra[t] = rload(c1 + DIR * t);
+#pragma unroll 1
+      for (int s0 = 0; s0 < count; s0 += TS_ROWS) {
+        res_jitter(jitter, (unsigned)s0);
+        const int s = min(s0 + (lane >> 1), count - 1);
+        const double *src = at(c1 + DIR * s);
+        Rl v = P::rzero();
+        int avail = 0;  // columns of the chunk that are there
+        PollBound poll;
+        auto wait_col = [&](int j) __attribute__((always_inline)) {
+          while (avail <= j) {
+            double *pv = reinterpret_cast<double *>(&v);
+            bool miss = false;
+#pragma unroll
+            for (int l = 0; l < L; ++l) {
+              pv[l] = coh_load(src + (size_t)(2 * l + part) * plane);
+              miss = miss || __double_as_longlong(pv[l]) == RES_EMPTY;
+            }
+            const unsigned long long gone = __ballot(miss);
+            avail = gone == 0 ? TS_ROWS : (__ffsll((long long)gone) - 1) >> 1;
+            if (avail > j) return true;
+            if (poll.due() && poll.late(spin_ticks)) {
+              if (lane == 0 && info != nullptr)
+                __hip_atomic_store(info, MGS_INFO_SYNC_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              return false;
+            }
+            __builtin_amdgcn_s_sleep(1);
+          }
+          return true;
+        };
+#pragma unroll 1
+        for (int j0 = 0; j0 < TS_ROWS && s0 + j0 < count; j0 += RING) {
+#pragma unroll
+          for (int t = 0; t < RING; ++t) {
+            const int j = j0 + t;
+            if (s0 + j < count) {
+              if (!wait_col(j)) return false;
+              update(yv, ra[t], wave_readlane(v, 2 * j), wave_readlane(v, 2 * j + 1));
+            }
+            ra[t] = rload(c1 + DIR * (s0 + j + RING));
+          }
+        }
+      }
+      return true;
+    };
+    // 1. Columns solved by other blocks, then by the block's other waves.
+    if (!absorb(FWD ? 0 : n - 1, FWD ? r0 : n - r1,
+                [&](int c) __attribute__((always_inline)) { return (const double *)(x + c); }, (size_t)n))
+      return;
+    if (!absorb(FWD ? r0 : r1 - 1, FWD ? w0 - r0 : r1 - w1,
+                [&](int c) __attribute__((always_inline)) { return (const double *)(&xs[0][c - r0]); },
+                (size_t)TS_BLOCK))
+      return;
+    // 2. The wave's own columns, ahead of the waves that share its SIMD.
+    // Every lane writes its x, solved or not, every 4 columns (LDS) and every
+    // RING (x): no branch, so the loads in flight stay counted.
+    __builtin_amdgcn_s_setprio(3);
+    const int ncol = w1 - w0;
+    const double *px = reinterpret_cast<const double *>(&xown);
+#pragma unroll 1
+    for (int s0 = 0; s0 < ncol; s0 += RING) {
+      res_jitter(jitter, 0x10000u + (unsigned)s0);
+#pragma unroll
+      for (int t = 0; t < RING; ++t) {
+        const int c = own + DIR * (s0 + t), k = c - w0;  // k outside [0, ncol) past the block
+        const Rl xl = P::rmul(yv, inv);
+        const Rl xr = wave_readlane(xl, (2 * k) & 63), xi = wave_readlane(xl, (2 * k + 1) & 63);
+        update(yv, rd[t], xr, xi);
+        xown = lane_pick((lane >> 1) == k, xl, xown);
+        if (t % 4 == 3) {
+#pragma unroll
+          for (int l = 0; l < L; ++l)
+            __hip_atomic_store(&xs[2 * l + part][wave * TS_ROWS + (lane >> 1)], px[l], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        rd[t] = rload(c + DIR * RING);
+      }
+      if (mine) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) coh_store(x + i + (size_t)(2 * l + part) * n, px[l]);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
   }
-#ifdef MGS_TRACE
-  if (trace != nullptr && lane == 0) trace[blockIdx.x * 4 + 2] = (long long)wall_clock64();
-#endif
 }
 
 }  // namespace mgsq

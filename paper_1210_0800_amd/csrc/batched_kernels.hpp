@@ -206,10 +206,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   bool alive = true;
   // Bounded wait for `ready()`; false (and the status) on a time-out.
   auto wait_for = [&](auto ready) __attribute__((always_inline)) {
-    if (ready()) return true;
-    const long long t0 = wall_clock64();
+    PollBound poll;
     while (!ready()) {
-      if (wall_clock64() - t0 > a.spin_ticks) {
+      if (poll.due() && poll.late(a.spin_ticks)) {
         if (lane == 0) atomicExch(&status, MGS_INFO_SYNC_TIMEOUT);
         return false;
       }
@@ -394,7 +393,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll 1
   for (int k = n - 1; k >= 0; --k) {
     const C r2 = rcol(k - 2);
-    const C xk = bs_readlane<P>(P::scale(yv, inv), k);
+    const C xk = wave_readlane(P::scale(yv, inv), k);
     if (lane == k) P::store(x + k, (size_t)n, xk);
     if (lane < k) P::upd(yv, rc, xk);
     rc = rn;

@@ -595,6 +595,22 @@ struct PrecDD {
     return {dd_mul(a.re, s), dd_mul(a.im, s)};
   }
   __device__ static __forceinline__ R rmul(const R &a, const R &b) { return dd_mul(a, b); }
+  __device__ static __forceinline__ R rneg(const R &a) { return {-a.h, -a.l}; }
+  // a -= r x + s z, one part of upd with the same operations.
+  __device__ static __forceinline__ void upd_part(R &a, const R &r, const R &x, const R &s, const R &z) {
+    double p1, e1, p2, e2, t, t1, t2, c;
+    two_prod(-r.h, x.h, p1, e1);
+    two_prod(-s.h, z.h, p2, e2);
+    two_sum(a.h, p1, t, t1);
+    two_sum(t, p2, t, t2);
+    c = a.l;
+    c = __fma_rn(-r.h, x.l, c);
+    c = __fma_rn(-r.l, x.h, c);
+    c = __fma_rn(-s.h, z.l, c);
+    c = __fma_rn(-s.l, z.h, c);
+    c += (e1 + e2) + (t1 + t2);
+    fast_two_sum(t, c, a.h, a.l);
+  }
   __device__ static __forceinline__ R sqrt_(const R &s) { return dd_sqrt(s); }
   __device__ static __forceinline__ R recip(const R &s) { return dd_recip(s); }
   __device__ static __forceinline__ void sqrt_recip(const R &s, R &root, R &inv) { dd_sqrt_recip(s, root, inv); }
@@ -691,6 +707,13 @@ struct PrecQD {
   }
   __device__ static __forceinline__ C scale(const C &a, const R &s) { return {qd_mul(a.re, s), qd_mul(a.im, s)}; }
   __device__ static __forceinline__ R rmul(const R &a, const R &b) { return qd_mul(a, b); }
+  __device__ static __forceinline__ R rneg(const R &a) { return qd_neg(a); }
+  // a -= r x + s z, one part of upd with the same operations.
+  __device__ static __forceinline__ void upd_part(R &a, const R &r, const R &x, const R &s, const R &z) {
+    qdsum t = qd_sum_from(a);
+    qd_acc(t, qd_dot2(qd_neg(r), x, qd_neg(s), z));
+    a = qd_value(t);
+  }
   __device__ static __forceinline__ R sqrt_(const R &s) { return qd_sqrt(s); }
   __device__ static __forceinline__ R recip(const R &s) { return qd_recip(s); }
   __device__ static __forceinline__ void sqrt_recip(const R &s, R &root, R &inv) { qd_sqrt_recip(s, root, inv); }
@@ -773,6 +796,12 @@ struct PrecD {
   }
   __device__ static __forceinline__ C scale(const C &a, const R &s) { return {a.re * s, a.im * s}; }
   __device__ static __forceinline__ R rmul(const R &a, const R &b) { return a * b; }
+  __device__ static __forceinline__ R rneg(const R &a) { return -a; }
+  // a -= r x + s z, one part of upd with the same operations.
+  __device__ static __forceinline__ void upd_part(R &a, const R &r, const R &x, const R &s, const R &z) {
+    a = __fma_rn(-r, x, a);
+    a = __fma_rn(-s, z, a);
+  }
   __device__ static __forceinline__ R sqrt_(const R &s) { return sqrt(s); }
   __device__ static __forceinline__ R recip(const R &s) { return 1.0 / s; }
   __device__ static __forceinline__ bool ok_norm(const R &s) { return s > 0.0 && s < INFINITY; }

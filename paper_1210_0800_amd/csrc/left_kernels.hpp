@@ -133,14 +133,13 @@ mgs_left_kernel(LeftArgs a) {
   };
   auto wait_record = [&](int k, int which, Rl &v) __attribute__((always_inline)) {
     const double *pv = reinterpret_cast<const double *>(&v);
-    long long t0 = -1;
+    PollBound poll;
     while (true) {
       bool miss = false;
 #pragma unroll
       for (int i = 0; i < L; ++i) miss = miss || __double_as_longlong(pv[i]) == RES_EMPTY;
       if (__ballot(miss) == 0) return true;
-      if (t0 < 0) t0 = wall_clock64();
-      if (res_give_up(a, t0)) return false;
+      if (res_give_up(a, poll)) return false;
       __builtin_amdgcn_s_sleep(1);
       read_record(k, which, v);
     }
@@ -175,7 +174,7 @@ mgs_left_kernel(LeftArgs a) {
       res_jitter(a.jitter, step++);
       if (!a.marked && !res_wait(a, k, wave, seen)) return;
       const double *src = a.Q + (size_t)k * a.ldq;
-      long long t0 = -1;
+      PollBound poll;
       while (true) {
         bool miss = false;
 #pragma unroll
@@ -184,8 +183,7 @@ mgs_left_kernel(LeftArgs a) {
           u[r] = i < a.m ? res_coh_load<P>(src + i, a.planeQ, miss) : P::czero();
         }
         if (!a.marked || __ballot(miss) == 0) break;
-        if (t0 < 0) t0 = wall_clock64();
-        if (res_give_up(a, t0)) return;
+        if (res_give_up(a, poll)) return;
         __builtin_amdgcn_s_sleep(1);
       }
       Rl rec = P::rzero();

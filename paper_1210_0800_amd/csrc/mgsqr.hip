@@ -158,12 +158,6 @@ int dispatch_shape(const StepArgs &a, const Shape &sh, hipStream_t st) {
   return MGS_ERR_DIMS;
 }
 
-#ifdef MGS_TRACE
-// Diagnostic builds: stamps of the back substitution across workgroups
-// (4 per workgroup), set by mgs_set_trace_backsolve.
-long long *g_trace_bs = nullptr;
-#endif
-
 struct DevInfo {
   int cus;  // compute units when cooperative launches are supported, else 0
   long long wclk_khz;
@@ -174,62 +168,35 @@ bool dev_info(DevInfo &d);
 // synchronise across waves or workgroups (mgs_set_jitter; 0: none).
 std::atomic<unsigned> g_jitter{0};
 
-// Back substitution across workgroups (one wave per 64 rows, cooperative);
-// returns 1 when it does not apply (one block only, or the workgroups
-// cannot all be resident), so that the caller takes the one-workgroup
-// kernel.
+// R x = y, or R^H x = y with FWD.  Up to 128 rows one workgroup; beyond, one
+// per 128 rows in a cooperative launch, or, where that is refused, one
+// workgroup that takes the blocks in turn.
 template <class P, bool FWD = false>
-int backsolve_pipe_launch(int n, const double *R, int ldr, size_t planeR, const double *y, size_t planeY, double *x,
-                          int *info, const int *skip, hipStream_t st) {
-  if (n <= BP_ROWS) return 1;
-  DevInfo d;
-  if (!dev_info(d) || d.cus <= 0) return 1;
-  const int G = ceil_div(n, BP_ROWS);
-  auto kern = trsv_pipe_kernel<P, FWD>;
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern), BP_ROWS, 0) !=
-          hipSuccess ||
-      (long long)per_cu * d.cus < G)
-    return 1;
-  hipLaunchKernelGGL((bs_mark_kernel<P::L>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, x, info, skip);
-  if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
-  long long spin = d.wclk_khz * 2000;  // 2 s
-#ifdef MGS_TRACE
-  long long *trace = g_trace_bs;
-#else
-  long long *trace = nullptr;
-#endif
-  unsigned jitter = g_jitter.load(std::memory_order_relaxed);
-  void *args[] = {&n, &R, &ldr, &planeR, &y, &planeY, &x, &info, &skip, &spin, &trace, &jitter};
-  if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kern), dim3(G), dim3(BP_ROWS), args, 0, st) !=
-      hipSuccess) {
-    (void)hipGetLastError();
-    return 1;
-  }
-  return MGS_OK;
-}
-
-template <class P>
-int backsolve_launch(int n, const double *R, int ldr, const double *y, double *x, int *info, hipStream_t st,
-                     size_t planeR = 0, const int *skip = nullptr, size_t planeY = 0) {
-  const int ny = pow2_at_least(ceil_div(n, BS_T));
+int trsv_launch(int n, const double *R, int ldr, const double *y, double *x, int *info, hipStream_t st,
+                size_t planeR = 0, const int *skip = nullptr, size_t planeY = 0) {
   if (planeR == 0) planeR = (size_t)ldr * n;
   if (planeY == 0) planeY = (size_t)n;
-  const int rc = backsolve_pipe_launch<P>(n, R, ldr, planeR, y, planeY, x, info, skip, st);
-  if (rc != 1) return rc;
-#define MGS_NY_CASE(NYV)                                                                                    \
-  case NYV:                                                                                                 \
-    hipLaunchKernelGGL((backsolve_blocked_kernel<P, NYV>), dim3(1), dim3(BS_T), 0, st, n, R, ldr, planeR, y, \
-                       planeY, x, info, skip);                                                              \
-    break;
-  switch (ny) {
-    MGS_NY_CASE(1)
-    MGS_NY_CASE(2)
-    MGS_NY_CASE(4)
-    default:
-      return MGS_ERR_DIMS;
+  const int waves = ceil_div(n, TS_ROWS) < TS_WAVES ? ceil_div(n, TS_ROWS) : TS_WAVES;
+  const int G = ceil_div(n, TS_ROWS * waves);
+  DevInfo d;
+  const bool have = dev_info(d);
+  long long spin = (have ? d.wclk_khz : 100000) * 2000;  // 2 s
+  unsigned jitter = g_jitter.load(std::memory_order_relaxed);
+  int marked = G > 1 ? 1 : 0;
+  auto kern = trsv_kernel<P, FWD>;
+  if (marked) {
+    hipLaunchKernelGGL((bs_mark_kernel<P::L>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, x, info, skip);
+    if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
+    if (have && d.cus >= G) {
+      void *args[] = {&n, &R, &ldr, &planeR, &y, &planeY, &x, &info, &skip, &marked, &spin, &jitter};
+      if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kern), dim3(G), dim3(64 * waves), args, 0, st) ==
+          hipSuccess)
+        return MGS_OK;
+      (void)hipGetLastError();
+    }
   }
-#undef MGS_NY_CASE
+  hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, st, n, R, ldr, planeR, y, planeY, x, info, skip, marked, spin,
+                     jitter);
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
 
@@ -278,27 +245,6 @@ size_t adjoint_work_bytes(int m, int n, int prec) {
 }
 
 template <class P>
-int fwdsub_launch(int n, const double *R, int ldr, const double *g, double *w, int *info, hipStream_t st) {
-  const int ny = pow2_at_least(ceil_div(n, BS_T));
-  const size_t planeR = (size_t)ldr * n;
-  const int rc = backsolve_pipe_launch<P, true>(n, R, ldr, planeR, g, (size_t)n, w, info, nullptr, st);
-  if (rc != 1) return rc;
-#define MGS_FS_CASE(NYV)                                                                                       \
-  case NYV:                                                                                                    \
-    hipLaunchKernelGGL((fwdsub_blocked_kernel<P, NYV>), dim3(1), dim3(BS_T), 0, st, n, R, ldr, planeR, g, w, info); \
-    break;
-  switch (ny) {
-    MGS_FS_CASE(1)
-    MGS_FS_CASE(2)
-    MGS_FS_CASE(4)
-    default:
-      return MGS_ERR_DIMS;
-  }
-#undef MGS_FS_CASE
-  return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
-}
-
-template <class P>
 int adjoint_launch(int m, int n, const double *A, int lda, const double *b, const double *Q, int ldq,
                    const double *R, int ldr, const double *x, const double *gx, double *gA, int ldga, double *gb,
                    void *work, int *info, hipStream_t st) {
@@ -306,9 +252,9 @@ int adjoint_launch(int m, int n, const double *A, int lda, const double *b, cons
   double *z = w + round256(sizeof(double) * 2 * P::L * (size_t)n) / sizeof(double);
   double *r = z + round256(sizeof(double) * 2 * P::L * (size_t)n) / sizeof(double);
   auto *part = reinterpret_cast<typename P::Acc *>(r + round256(sizeof(double) * 2 * P::L * (size_t)m) / sizeof(double));
-  int rc = fwdsub_launch<P>(n, R, ldr, gx, w, info, st);
+  int rc = trsv_launch<P, true>(n, R, ldr, gx, w, info, st);
   if (rc != MGS_OK) return rc;
-  rc = backsolve_launch<P>(n, R, ldr, w, z, info, st);
+  rc = trsv_launch<P>(n, R, ldr, w, z, info, st);
   if (rc != MGS_OK) return rc;
   hipLaunchKernelGGL((adj_partial_kernel<P>), dim3(ceil_div(m, ADJ_T), ceil_div(n, ADJ_CH), 2), dim3(ADJ_T), 0, st,
                      m, n, Q, ldq, (size_t)ldq * n, A, lda, (size_t)lda * n, b, x, w, part);
@@ -435,7 +381,7 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   hipLaunchKernelGGL(refine_check_kernel, dim3(1), dim3(64), 0, st, info, w.ctl);
   const int *skip = &w.ctl->status;
   // x0: R x0 = y (the last column of R64)
-  rc = backsolve_launch<PrecD>(n, w.R64, n, w.R64 + (size_t)n * n, w.d64, nullptr, st, planeR, skip, planeR);
+  rc = trsv_launch<PrecD>(n, w.R64, n, w.R64 + (size_t)n * n, w.d64, nullptr, st, planeR, skip, planeR);
   if (rc != MGS_OK) return rc;
   hipLaunchKernelGGL((set_x_kernel<P>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, w.d64, x);
   const int nchunk = ceil_div(n, NBP);
@@ -481,7 +427,7 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
                            (size_t)n, w.r64, w.ctl);
       }
     }
-    rc = backsolve_launch<PrecD>(n, w.R64, n, w.y64, w.d64, nullptr, st, planeR, skip);
+    rc = trsv_launch<PrecD>(n, w.R64, n, w.y64, w.d64, nullptr, st, planeR, skip);
     if (rc != MGS_OK) return rc;
     hipLaunchKernelGGL((refine_update_kernel<P>), dim3(1), dim3(256), 0, st, n, w.d64, x, tol, it, w.ctl);
     if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
@@ -866,7 +812,7 @@ int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *v
       int rc = mgs_qr_schedule(neq, nvar, P::L, w.A, neq, w.A, neq, w.R, nvar, w.b, w.y, nullptr, w.qrw, w.qrw_bytes,
                                info, MGS_SCHED_AUTO, reinterpret_cast<mgs_stream_t>(st));
       if (rc != MGS_OK) return rc;
-      rc = backsolve_launch<P>(nvar, w.R, nvar, w.y, w.d, w.info2, st);
+      rc = trsv_launch<P>(nvar, w.R, nvar, w.y, w.d, w.info2, st);
       if (rc != MGS_OK) return rc;
       hipLaunchKernelGGL((newton_update_kernel<P>), dim3(batch), dim3(64), 0, st, nvar, x, w.d, info,
                          dnorm != nullptr ? dnorm + (size_t)k * batch : nullptr);
@@ -910,7 +856,6 @@ void mgs_set_jitter(unsigned seed) { g_jitter.store(seed, std::memory_order_rela
 #ifdef MGS_TRACE
 // Diagnostic builds only (not declared in the public header).
 void mgs_set_trace(long long *buf) { g_trace = buf; }
-void mgs_set_trace_backsolve(long long *buf) { g_trace_bs = buf; }
 #endif
 
 int mgs_abi_version(void) { return MGS_ABI_VERSION; }
@@ -1054,9 +999,9 @@ int ls_backsolve(int n, int prec, const double *R, int ldr, const double *y, dou
   if (!aligned8(R) || !aligned8(y) || !aligned8(x) || !aligned8(info)) return MGS_ERR_POINTER;
   if (x == y) return MGS_ERR_POINTER;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (prec == 1) return backsolve_launch<PrecD>(n, R, ldr, y, x, info, st);
-  if (prec == 2) return backsolve_launch<PrecDD>(n, R, ldr, y, x, info, st);
-  return backsolve_launch<PrecQD>(n, R, ldr, y, x, info, st);
+  if (prec == 1) return trsv_launch<PrecD>(n, R, ldr, y, x, info, st);
+  if (prec == 2) return trsv_launch<PrecDD>(n, R, ldr, y, x, info, st);
+  return trsv_launch<PrecQD>(n, R, ldr, y, x, info, st);
 }
 
 int ls_solve(int m, int n, int prec, const double *Q, int ldq, const double *R, int ldr,
@@ -1073,9 +1018,9 @@ int ls_solve(int m, int n, int prec, const double *Q, int ldq, const double *R, 
            : prec == 2 ? project_launch<PrecDD>(m, n, Q, ldq, b, y, st)
                        : project_launch<PrecQD>(m, n, Q, ldq, b, y, st);
   if (rc != MGS_OK) return rc;
-  if (prec == 1) return backsolve_launch<PrecD>(n, R, ldr, y, x, info, st);
-  if (prec == 2) return backsolve_launch<PrecDD>(n, R, ldr, y, x, info, st);
-  return backsolve_launch<PrecQD>(n, R, ldr, y, x, info, st);
+  if (prec == 1) return trsv_launch<PrecD>(n, R, ldr, y, x, info, st);
+  if (prec == 2) return trsv_launch<PrecDD>(n, R, ldr, y, x, info, st);
+  return trsv_launch<PrecQD>(n, R, ldr, y, x, info, st);
 }
 
 int ls_adjoint(int m, int n, int prec, const double *A, int lda, const double *b, const double *Q, int ldq,

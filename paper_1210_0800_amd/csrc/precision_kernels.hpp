@@ -405,11 +405,11 @@ __global__ __launch_bounds__(256) void proj_replay_kernel(int m, int n, const do
     target += (unsigned int)G;
     if (tid == 0) {
       atomicAdd(&ctl->bar, 1u);
-      const long long t0 = wall_clock64();
+      PollBound poll;
       int good = 1;
       while (__hip_atomic_load(&ctl->bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-        if (__hip_atomic_load(&ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
-            wall_clock64() - t0 > spin_ticks) {
+        if (poll.due() && (__hip_atomic_load(&ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
+                           poll.late(spin_ticks))) {
           __hip_atomic_store(&ctl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           good = 0;
           break;

@@ -215,15 +215,31 @@ __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
   for (int i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(1);
 }
 
+// The bound of a polling wait: the wall clock (and, in res_give_up, the abort
+// flag, a device-scope load) is looked at on every 16th turn only, so that a
+// turn is one read of what is waited for and the wait ends one read after
+// the data is there, not two.
+struct PollBound {
+  long long t0 = -1;
+  int turns = 0;
+  __device__ __forceinline__ bool due() { return (++turns & 15) == 0; }
+  __device__ __forceinline__ bool late(long long limit) {
+    const long long now = wall_clock64();
+    if (t0 < 0) t0 = now;
+    return now - t0 > limit;
+  }
+};
+
 // Common end of a bounded wait: true (and the abort flag set, info
 // written) once the wall-clock limit has passed, or when another wave has
 // aborted.
 template <class Args>
-__device__ __forceinline__ bool res_give_up(const Args &a, long long t0) {
+__device__ __forceinline__ bool res_give_up(const Args &a, PollBound &poll) {
+  if (!poll.due()) return false;
   if (__builtin_amdgcn_readfirstlane(
           (int)__hip_atomic_load(a.sync + RES_ABORT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0)
     return true;
-  if (wall_clock64() - t0 > a.spin_ticks) {
+  if (poll.late(a.spin_ticks)) {
     __hip_atomic_store(a.sync + RES_ABORT, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a.info, MGS_INFO_SYNC_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
@@ -237,7 +253,7 @@ __device__ __forceinline__ bool res_give_up(const Args &a, long long t0) {
 template <class Args>
 __device__ __forceinline__ bool res_wait(const Args &a, int k, int wave, int &seen) {
   if (seen > k) return true;
-  const long long t0 = wall_clock64();
+  PollBound poll;
   unsigned int *cnt = a.sync + 16 * wave;
   while (true) {
     const int v = __builtin_amdgcn_readfirstlane(
@@ -247,7 +263,7 @@ __device__ __forceinline__ bool res_wait(const Args &a, int k, int wave, int &se
       asm volatile("" ::: "memory");
       return true;
     }
-    if (res_give_up(a, t0)) return false;
+    if (res_give_up(a, poll)) return false;
     __builtin_amdgcn_s_sleep(1);
   }
 }
@@ -603,7 +619,7 @@ struct Resident {
   // Returns false on abort or time-out.
   __device__ __forceinline__ bool load_col(const double *base, size_t ld, size_t plane, int k, C (&q)[RR]) {
     const double *src = base + (size_t)k * ld;
-    long long t0 = -1;
+    PollBound poll;
     while (true) {
       bool miss = false;
 #pragma unroll
@@ -613,8 +629,7 @@ struct Resident {
         if (i < a.m) q[r] = res_coh_load<P>(src + i, plane, miss);
       }
       if (__ballot(miss) == 0) return true;
-      if (t0 < 0) t0 = wall_clock64();
-      if (res_give_up(a, t0)) return false;
+      if (res_give_up(a, poll)) return false;
       __builtin_amdgcn_s_sleep(1);
     }
   }
@@ -648,9 +663,9 @@ struct Resident {
     bool ok = true;
     if (tid == 0) {
       __hip_atomic_fetch_add(a.sync + RES_GRID, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const long long t0 = wall_clock64();
+      PollBound poll;
       while (__hip_atomic_load(a.sync + RES_GRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned int)a.G) {
-        if (res_give_up(a, t0)) {
+        if (res_give_up(a, poll)) {
           ok = false;
           break;
         }
