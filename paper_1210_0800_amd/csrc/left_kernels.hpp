@@ -299,4 +299,85 @@ __global__ __launch_bounds__(256) void left_finish_kernel(int m, int n, double *
   }
 }
 
+// Projections y = Q^H b: y_k = q_k^H b^(k-1), b^(k) = b^(k-1) - y_k q_k for
+// k = 1..n, the operations of the augmented column of Equation (1).  One
+// workgroup of 8 waves, b in registers (RPT rows per thread).  A chain of
+// one inner product, one block sum (one barrier: two buffers alternate) and
+// one update per column; q_k is loaded RING columns ahead, so the memory's
+// latency is off the chain (700 x 500 double: 0.89 us a column with the
+// loads on it and two barriers).
+template <class P, int RPT, int RING>
+__global__ __launch_bounds__(512) void project_kernel(int m, int n, const double *Q, int ldq, size_t planeQ,
+                                                      const double *b, double *y) {
+  using C = typename P::C;
+  using Acc = typename P::Acc;
+  using RAcc = typename P::RAcc;
+  using Rl = typename P::R;
+  using G = GridSum<P>;
+  constexpr int NW = 8, H = G::H, RWG = 64 * NW;
+  __shared__ double xch[2][2][H][NW];  // wave totals, [buffer][part][word][wave]
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  // rows past m load the last row and hold a zero of b
+  C bv[RPT];
+  int row[RPT];
+#pragma unroll
+  for (int r = 0; r < RPT; ++r) {
+    const int i = r * RWG + tid;
+    row[r] = i < m ? i : m - 1;
+    bv[r] = i < m ? P::load(b + i, (size_t)m) : P::czero();
+  }
+  C q[RING][RPT];
+  auto fetch = [&](int k, C (&v)[RPT]) __attribute__((always_inline)) {
+    const double *qk = Q + (size_t)min(k, n - 1) * ldq;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) v[r] = P::load(qk + row[r], planeQ);
+  };
+  static_for<RING>([&](auto tI) __attribute__((always_inline)) {
+    constexpr int t = decltype(tI)::value;
+    fetch(t, q[t]);
+  });
+  int buf = 0;
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += RING) {
+    static_for<RING>([&](auto tI) __attribute__((always_inline)) {
+      constexpr int t = decltype(tI)::value;
+      const int k = k0 + t;
+      Acc acc;
+      P::acc_zero(acc);
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        if (r * RWG + tid >= m) q[t][r] = P::czero();
+        P::acc_cmulc(acc, q[t][r], bv[r]);
+      }
+      RAcc v = G::fold32(G::parts(acc)[0], G::parts(acc)[1]);
+      v = G::fold16(v, v);
+      G::template rot<0x128>(v);
+      G::template rot<0x124>(v);
+      G::template rot<0x122>(v);
+      G::template rot<0x121>(v);
+      if ((lane & 31) == 0) {
+        const double *p = reinterpret_cast<const double *>(&v);
+#pragma unroll
+        for (int i = 0; i < H; ++i) xch[buf][lane >> 5][i][wave] = p[i];
+      }
+      lds_barrier();
+      {
+        double *p = reinterpret_cast<double *>(&v);
+#pragma unroll
+        for (int i = 0; i < H; ++i) p[i] = xch[buf][lane >> 5][i][lane & (NW - 1)];
+      }
+      G::template rot<0xB1>(v);
+      G::template rot<0x4E>(v);
+      G::template rot<0x124>(v);
+      buf ^= 1;
+      const Rl yk = P::racc_value(v);
+      if (wave == 0 && (lane & 31) == 0 && k < n) P::store_real(y + k + (size_t)(lane >> 5) * n, 2 * (size_t)n, yk);
+      const C c = G::spread(yk);
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) P::upd(bv[r], c, q[t][r]);
+      fetch(k + RING, q[t]);
+    });
+  }
+}
+
 }  // namespace mgsq

@@ -467,47 +467,4 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(1, 1))) void
   }
 }
 
-// ------------------------------------------ projections y = Q^H b --------
-// y_k = q_k^H b^(k-1), b^(k) = b^(k-1) - y_k q_k for k = 1..n: the same
-// operations as the augmented column of Equation (1).  One block; b stays
-// in registers (RB rows per thread).
-template <class P, int RB>
-__global__ __launch_bounds__(WG) void project_kernel(int m, int n, const double *Q, int ldq, size_t planeQ,
-                                                      const double *b, double *y) {
-  using C = typename P::C;
-  using Acc = typename P::Acc;
-  __shared__ Acc lds[NWAVE];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  C bv[RB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    int i = r * WG + tid;
-    bv[r] = (i < m) ? P::load(b + i, (size_t)m) : P::czero();
-  }
-#pragma unroll 1
-  for (int k = 0; k < n; ++k) {
-    const double *qk = Q + (size_t)k * ldq;
-    C q[RB];
-    Acc acc;
-    P::acc_zero(acc);
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      int i = r * WG + tid;
-      q[r] = (i < m) ? P::load(qk + i, planeQ) : P::czero();
-      P::acc_cmulc(acc, q[r], bv[r]);
-    }
-    wave_reduce<P>(acc);
-    if (lane == 0) lds[wave] = acc;
-    __syncthreads();
-    acc = lds[0];
-#pragma unroll
-    for (int w = 1; w < NWAVE; ++w) P::acc_merge(acc, lds[w]);
-    __syncthreads();
-    C yk = P::acc_value(acc);
-    if (tid == 0) P::store(y + k, (size_t)n, yk);
-#pragma unroll
-    for (int r = 0; r < RB; ++r) P::upd(bv[r], yk, q[r]);
-  }
-}
-
 }  // namespace mgsq

@@ -200,24 +200,26 @@ int trsv_launch(int n, const double *R, int ldr, const double *y, double *x, int
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
 
+// Columns in flight: as the registers allow (256 a lane).
 template <class P>
 int project_launch(int m, int n, const double *Q, int ldq, const double *b, double *y, hipStream_t st) {
-  const int rb = pow2_at_least(ceil_div(m, WG));
   const size_t planeQ = (size_t)ldq * n;
-#define MGS_RB_CASE(RBV)                                                                                     \
-  case RBV:                                                                                                  \
-    hipLaunchKernelGGL((project_kernel<P, RBV>), dim3(1), dim3(WG), 0, st, m, n, Q, ldq, planeQ, b, y);       \
+#define MGS_PROJ_CASE(RPTV, RINGV)                                                                                \
+  case RPTV:                                                                                                      \
+    hipLaunchKernelGGL((project_kernel<P, RPTV, RINGV>), dim3(1), dim3(512), 0, st, m, n, Q, ldq, planeQ, b, y); \
     break;
-  switch (rb) {
-    MGS_RB_CASE(1)
-    MGS_RB_CASE(2)
-    MGS_RB_CASE(4)
-    MGS_RB_CASE(8)
-    MGS_RB_CASE(16)
+  switch (pow2_at_least(ceil_div(m, 512))) {
+    MGS_PROJ_CASE(1, (P::L == 4 ? 3 : 4))
+    MGS_PROJ_CASE(2, (P::L == 4 ? 2 : 4))
+    MGS_PROJ_CASE(4, (P::L == 4 ? 1 : P::L == 2 ? 2 : 4))
     default:
-      return MGS_ERR_DIMS;
+      if constexpr (P::L == 4) {
+        return MGS_ERR_DIMS;  // past the qd row limit
+      } else {
+        switch (8) { MGS_PROJ_CASE(8, (P::L == 2 ? 1 : 2)) }
+      }
   }
-#undef MGS_RB_CASE
+#undef MGS_PROJ_CASE
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
 
@@ -796,14 +798,50 @@ bool newton_dims_ok(int batch, int neq, int nvar, int nmon, int nvpm, int prec) 
   return batch >= 0 && batch <= 65535 && nvar >= 1 && nvar <= NT_MAX_VARS && neq >= nvar && nmon >= 1 && nmon <= NT_MAX_MON &&
          nvpm >= 1 && nvpm <= NT_MAX_VPM && batched_fits(neq, nvar, nvar + 1, prec);
 }
+// Evaluation of neq equations at batch points.  Few points: two equations per
+// one-wave workgroup, spread over the card; from 8 workgroups per compute
+// unit on, whole points, so that the powers are formed once (qd and dd: up
+// to 4 waves, as many as LDS holds twice per compute unit).
+template <class P, bool HALF>
+int poly_launch_half(int batch, int neq, int nvar, int nmon, int nvpm, const int *vars, const int *exps,
+                     const double *coef, const double *x, double *A, double *b, bool negate, hipStream_t st) {
+  const int eq = HALF ? 2 : 1;
+  const size_t table = nt_table_doubles(P::L, nvar) * sizeof(double);
+  const size_t per_wave = nt_wave_doubles(P::L, nvpm) * sizeof(double);
+  DevInfo d;
+  const int cus = dev_info(d) && d.cus > 0 ? d.cus : 256;
+  int waves = 1, neqb = eq;
+  if ((long long)batch >= 2 * cus) {
+    waves = ceil_div(neq, eq) < 4 ? ceil_div(neq, eq) : 4;
+    while (waves > 1 && table + waves * per_wave > 80 * 1024) --waves;
+    neqb = neq;
+  } else {
+    while (neqb < neq && (long long)batch * ceil_div(neq, neqb) > 8 * cus) neqb += eq;
+  }
+  const size_t shmem = table + waves * per_wave;
+  auto kern = poly_eval_kernel<P, HALF>;
+  if (shmem > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)shmem) != hipSuccess)
+    return MGS_ERR_LAUNCH;
+  hipLaunchKernelGGL(kern, dim3(ceil_div(neq, neqb), batch), dim3(64 * waves), shmem, st, neq, nvar, nmon, nvpm, vars,
+                     exps, coef, x, A, b, neqb, negate);
+  return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
+}
+template <class P>
+int poly_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *vars, const int *exps, const double *coef,
+                const double *x, double *A, double *b, bool negate, hipStream_t st) {
+  return nmon <= 32 ? poly_launch_half<P, true>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, A, b, negate, st)
+                    : poly_launch_half<P, false>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, A, b, negate, st);
+}
+
 template <class P>
 int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *vars, const int *exps,
                   const double *coef, double *x, int iters, double *dnorm, const NewtonWork &w, int *info,
                   long long spin, hipStream_t st) {
   for (int k = 0; k < iters; ++k) {
-    hipLaunchKernelGGL((poly_eval_kernel<P>), dim3(neq, batch), dim3(64), 0, st, neq, nvar, nmon, nvpm, vars, exps,
-                       coef, x, w.A, w.b, true);
-    if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
+    const int pe = poly_launch<P>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, w.A, w.b, true, st);
+    if (pe != MGS_OK) return pe;
     if (w.qrw != nullptr) {
       // One point in qd: mgs_qr's single-system schedule (one column per
       // launch), quicker than a batch of one, then the back substitution
@@ -1089,16 +1127,9 @@ int mgs_poly_eval(int batch, int neq, int nvar, int nmon, int nvpm, int prec, co
       (reinterpret_cast<uintptr_t>(exps) & 3u))
     return MGS_ERR_POINTER;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (prec == 1)
-    hipLaunchKernelGGL((poly_eval_kernel<PrecD>), dim3(neq, batch), dim3(64), 0, st, neq, nvar, nmon, nvpm, vars,
-                       exps, coef, x, J, F, false);
-  else if (prec == 2)
-    hipLaunchKernelGGL((poly_eval_kernel<PrecDD>), dim3(neq, batch), dim3(64), 0, st, neq, nvar, nmon, nvpm, vars,
-                       exps, coef, x, J, F, false);
-  else
-    hipLaunchKernelGGL((poly_eval_kernel<PrecQD>), dim3(neq, batch), dim3(64), 0, st, neq, nvar, nmon, nvpm, vars,
-                       exps, coef, x, J, F, false);
-  return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
+  if (prec == 1) return poly_launch<PrecD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, J, F, false, st);
+  if (prec == 2) return poly_launch<PrecDD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, J, F, false, st);
+  return poly_launch<PrecQD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, J, F, false, st);
 }
 
 int mgs_newton_workspace_size(int batch, int neq, int nvar, int prec, size_t *bytes) {

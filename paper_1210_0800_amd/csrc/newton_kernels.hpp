@@ -22,23 +22,9 @@ constexpr int NT_MAX_VARS = 63;  // variables (columns of [J -f] <= 64)
 constexpr int NT_MAX_VPM = 8;    // variables per monomial
 constexpr int NT_MAX_DEG = 16;   // exponent bound
 
-// Lane 63's accumulator, wave-uniform.
-template <class P>
-__device__ __forceinline__ typename P::Acc acc_lane63(const typename P::Acc &v) {
-  using Acc = typename P::Acc;
-  constexpr int NA = sizeof(Acc) / sizeof(double);
-  Acc r;
-  double *pr = reinterpret_cast<double *>(&r);
-  const double *pv = reinterpret_cast<const double *>(&v);
-#pragma unroll
-  for (int c = 0; c < NA; ++c) {
-    const long long bits = __double_as_longlong(pv[c]);
-    const int lo = __builtin_amdgcn_readlane((int)(bits & 0xffffffffLL), 63);
-    const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), 63);
-    pr[c] = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-  }
-  return r;
-}
+// Powers x_j^d, d = 1..NT_TAB, kept per point; a higher one is continued by
+// repeated products.
+constexpr int NT_TAB = 6;
 
 template <class P>
 __device__ __forceinline__ typename P::C nt_mul(const typename P::C &a, const typename P::C &b) {
@@ -47,131 +33,183 @@ __device__ __forceinline__ typename P::C nt_mul(const typename P::C &a, const ty
   P::acc_cmul(acc, a, b);
   return P::acc_value(acc);
 }
-template <class P>
-__device__ __forceinline__ typename P::C nt_pow(const typename P::C &b, int d) {
-  typename P::C r = P::czero();
-  r.re = P::rone();
-  for (int k = 0; k < d; ++k) r = nt_mul<P>(r, b);
-  return r;
-}
 
-// One wave per (equation e, point s); lane m holds monomial m.  Its value
-// c prod_t x_t^{d_t} and its derivatives c d_t x_t^{d_t - 1} prod_{u != t}
-// x_u^{d_u} (prefix and suffix products) are formed in the working
-// precision; f_e is a wave sum (DPP, fixed tree), and each Jacobian entry
-// J(e, j) the sum, in monomial order, of the derivatives by x_j: the
-// derivative entries are listed by variable (stable, so each list is in
-// monomial order: counts, their prefix sum over the lanes, then a fill),
-// and the lane of variable j merges its list from LDS, all lanes at once,
-// in as many rounds as the longest list.  f_e (-f_e when negate) goes to
-// b, J to A, both in the batched least-squares layout.
-template <class P>
-__global__ __launch_bounds__(64) void poly_eval_kernel(int neq, int nvar, int nmon, int nvpm, const int *vars,
-                                                       const int *exps, const double *coef, const double *x,
-                                                       double *A, double *b, bool negate) {
+// Dynamic LDS of poly_eval_kernel: the power table, then per wave the
+// derivatives of its 64 lanes' monomials.
+constexpr size_t nt_table_doubles(int L, int nvar) { return (size_t)2 * L * NT_TAB * nvar; }
+constexpr size_t nt_wave_doubles(int L, int nvpm) { return (size_t)2 * L * 64 * nvpm; }
+
+// One workgroup evaluates neqb equations at one point; its waves take them
+// HALF ? two at a time (nmon <= 32: a lane per monomial, an equation per half
+// wave) : one at a time.  The powers of the point's variables are formed
+// once per workgroup.  A lane forms its monomial c prod_t x_t^{d_t} and its
+// derivatives c d_t x_t^{d_t - 1} prod_{u != t} x_u^{d_u} from suffix
+// products (kept in the derivatives' places in LDS) and a running prefix
+// product, so nothing but the current products is held in registers.  f_e is
+// a sum over the lanes (fixed tree).  J(e, j) is summed by the lane of
+// variable j in monomial order: ballots give each lane the monomials (and
+// factors) that hold its variable, and all lanes walk their lists at once.
+// f_e (-f_e when negate) goes to b, J to A, both in the batched
+// least-squares layout.
+//
+// Bound by the products: qd, 32 equations of 32 monomials of 5 variables at
+// 1024 points took 3.1 ms with a power per factor, half the lanes idle and
+// 1.7 KB of scratch per lane.
+template <class P, bool HALF>
+__global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int nmon, int nvpm, const int *vars,
+                                                        const int *exps, const double *coef, const double *x,
+                                                        double *A, double *b, int neqb, bool negate) {
   using C = typename P::C;
   using Acc = typename P::Acc;
-  constexpr int NP = 2 * P::L;
-  __shared__ double xs[NP][NT_MAX_VARS];                       // the point
-  __shared__ double ds[NP][NT_MAX_MON * NT_MAX_VPM];           // derivatives [m * nvpm + t]
-  __shared__ int vs[NT_MAX_MON * NT_MAX_VPM];                  // their variables
-  __shared__ int by_var[NT_MAX_MON * NT_MAX_VPM];              // entries listed by variable
-  const int lane = threadIdx.x;
-  const int e = blockIdx.x, s = blockIdx.y;
+  using G = GridSum<P>;
+  constexpr int NP = 2 * P::L, EQ = HALF ? 2 : 1, SEG = 64 / EQ;  // lanes per equation
+  extern __shared__ double lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nwave = blockDim.x >> 6;
+  const int s = blockIdx.y;
+  const size_t tabp = (size_t)NT_TAB * nvar, dsp = (size_t)64 * nvpm;  // plane strides
+  double *tab = lds;                                                      // [plane][d - 1][variable]
+  double *ds = lds + nt_table_doubles(P::L, nvar) + wave * nt_wave_doubles(P::L, nvpm);  // [plane][lane * nvpm + t]
   const double *xp = x + (size_t)s * NP * nvar;
-  if (lane < nvar) {
-#pragma unroll
-    for (int q = 0; q < NP; ++q) xs[q][lane] = xp[lane + (size_t)q * nvar];
+  if (tid < nvar) {
+    const C v = P::load(xp + tid, (size_t)nvar);
+    C p = v;
+    P::store(tab + tid, tabp, p);
+#pragma unroll 1
+    for (int d = 2; d <= NT_TAB; ++d) {
+      p = nt_mul<P>(p, v);
+      P::store(tab + (size_t)(d - 1) * nvar + tid, tabp, p);
+    }
   }
   __syncthreads();
-  C mono = P::czero();
-  const bool live = lane < nmon;
-  if (live) {
-    const size_t base = ((size_t)e * nmon + lane) * nvpm;
-    C c = P::load(coef + (size_t)e * nmon + lane, (size_t)neq * nmon);
-    C pw[NT_MAX_VPM], pd[NT_MAX_VPM];  // x_t^{d_t}, x_t^{d_t - 1}
+  // x_v^d
+  auto power = [&](int v, int d) __attribute__((always_inline)) {
+    const int k = d < 1 ? 1 : (d > NT_TAB ? NT_TAB : d);
+    C p = P::load(tab + (size_t)(k - 1) * nvar + v, tabp);
+    if (d < 1) {
+      p = P::czero();
+      p.re = P::rone();
+    }
+    if (d > NT_TAB) {
+      const C xv = P::load(tab + v, tabp);
+#pragma unroll 1
+      for (int i = NT_TAB; i < d; ++i) p = nt_mul<P>(p, xv);
+    }
+    return p;
+  };
+  const int seg = HALF ? lane >> 5 : 0, ml = lane & (SEG - 1);  // the lane's equation and monomial
+  const int e1 = min(neq, (blockIdx.x + 1) * neqb);
+#pragma unroll 1
+  for (int e0 = blockIdx.x * neqb + wave * EQ; e0 < e1; e0 += nwave * EQ) {
+    const int e = e0 + seg;
+    const bool live = e < e1 && ml < nmon;
+    const size_t base = live ? ((size_t)e * nmon + ml) * nvpm : 0;
+    // the monomial's factors: indices and exponents outside their bounds are
+    // clamped into them
     int vt[NT_MAX_VPM], dt[NT_MAX_VPM];
 #pragma unroll
     for (int t = 0; t < NT_MAX_VPM; ++t) {
+      vt[t] = -1;
+      dt[t] = 0;
       if (t < nvpm) {
-        // indices and exponents outside their bounds are clamped into them
         const int v0 = vars[base + t], d0 = exps[base + t];
         vt[t] = v0 < 0 ? 0 : (v0 >= nvar ? nvar - 1 : v0);
         dt[t] = d0 < 0 ? 0 : (d0 > NT_MAX_DEG ? NT_MAX_DEG : d0);
-        const C xv = P::load(&xs[0][vt[t]], (size_t)NT_MAX_VARS);
-        pd[t] = nt_pow<P>(xv, dt[t] > 0 ? dt[t] - 1 : 0);
-        pw[t] = dt[t] > 0 ? nt_mul<P>(pd[t], xv) : pd[t];
-      } else {
-        vt[t] = 0;
-        dt[t] = 0;
-        pw[t] = pd[t] = P::czero();
       }
     }
-    // prefix products pre[t] = c prod_{u < t} pw[u]; suffix products
-    C pre[NT_MAX_VPM + 1];
-    pre[0] = c;
-#pragma unroll
-    for (int t = 0; t < NT_MAX_VPM; ++t) pre[t + 1] = t < nvpm ? nt_mul<P>(pre[t], pw[t]) : pre[t];
-    mono = pre[NT_MAX_VPM];
+    C pre = P::load(coef + (live ? (size_t)e * nmon + ml : 0), (size_t)neq * nmon);
+    if (!live) pre = P::czero();
     C suf = P::czero();
     suf.re = P::rone();
 #pragma unroll
     for (int t = NT_MAX_VPM - 1; t >= 0; --t) {
       if (t < nvpm) {
-        C dv = P::czero();
-        if (dt[t] > 0) {
-          C k = P::czero();
-          k.re = P::rfrom((double)dt[t]);
-          dv = nt_mul<P>(nt_mul<P>(nt_mul<P>(pre[t], k), pd[t]), suf);
+        P::store(ds + lane * nvpm + t, dsp, suf);
+        if (t > 0) {
+          const C p = power(vt[t], dt[t]);
+          suf = t == nvpm - 1 ? p : nt_mul<P>(p, suf);
         }
-        P::store(&ds[0][lane * nvpm + t], (size_t)NT_MAX_MON * NT_MAX_VPM, dv);
-        vs[lane * nvpm + t] = vt[t];
-        suf = nt_mul<P>(pw[t], suf);
       }
     }
-  }
-  // -f_e: wave sum of the monomials (lanes past nmon hold zero)
-  Acc acc;
-  P::acc_set(acc, mono);
-  wave_sum_any<P>(acc, false);
-  const C fe = P::acc_value(acc_lane63<P>(acc));
-  double *bp = b + (size_t)s * NP * neq;
-  if (lane == 0) P::store(bp + e, (size_t)neq, negate ? P::cneg(fe) : fe);
-  __syncthreads();
-  // J(e, j) for j = lane.  The entries of variable `lane`, in ascending
-  // order, go to by_var[off, off + cnt).
-  const int nent = nmon * nvpm;
-  int cnt = 0;
-  for (int k = 0; k < nent; ++k) cnt += vs[k] == lane ? 1 : 0;
-  int off = cnt;  // inclusive scan over the lanes, then exclusive
 #pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(off, d);
-    if (lane >= d) off += o;
-  }
-  off -= cnt;
-  {
-    int w = off;
-    for (int k = 0; k < nent; ++k) {
-      if (vs[k] == lane) by_var[w++] = k;
+    for (int t = 0; t < NT_MAX_VPM; ++t) {
+      if (t < nvpm) {
+        C dv = P::scale(power(vt[t], dt[t] - 1), P::rfrom((double)dt[t]));  // d_t x_t^(d_t - 1)
+        dv = nt_mul<P>(pre, dv);
+        if (t < nvpm - 1) dv = nt_mul<P>(dv, P::load(ds + lane * nvpm + t, dsp));
+        if (dt[t] == 0) dv = P::czero();
+        P::store(ds + lane * nvpm + t, dsp, dv);
+        pre = nt_mul<P>(pre, power(vt[t], dt[t]));
+      }
     }
-  }
-  int rounds = cnt;
+    // f_e: the monomials of an equation, summed over its lanes
+    Acc acc;
+    P::acc_set(acc, pre);
+    typename P::RAcc re = G::parts(acc)[0], im = G::parts(acc)[1];
+    auto tree = [&](typename P::RAcc &v) __attribute__((always_inline)) {
+      if constexpr (!HALF) v = G::fold32(v, v);
+      v = G::fold16(v, v);
+      G::template rot<0x128>(v);
+      G::template rot<0x124>(v);
+      G::template rot<0x122>(v);
+      G::template rot<0x121>(v);
+    };
+    tree(re);
+    tree(im);
+    if (ml == 0 && e < e1) {
+      C fe;
+      fe.re = P::racc_value(re);
+      fe.im = P::racc_value(im);
+      P::store(b + (size_t)s * NP * neq + e, (size_t)neq, negate ? P::cneg(fe) : fe);
+    }
+    lds_wait();  // the derivatives of the other lanes
+    // J(e, j): the lanes of an equation take SEG variables at a time
+#pragma unroll 1
+    for (int j0 = 0; j0 < nvar; j0 += SEG) {
+      unsigned long long has[NT_MAX_VPM];  // monomials whose factor t is this lane's variable
 #pragma unroll
-  for (int mask = 32; mask >= 1; mask >>= 1) rounds = max(rounds, __shfl_xor(rounds, mask));
-  __syncthreads();
-  Acc aj;
-  P::acc_zero(aj);
-  for (int c = 0; c < rounds; ++c) {
-    if (c < cnt) {
-      Acc d1;
-      P::acc_set(d1, P::load(&ds[0][by_var[off + c]], (size_t)NT_MAX_MON * NT_MAX_VPM));
-      P::acc_merge(aj, d1);
+      for (int t = 0; t < NT_MAX_VPM; ++t) has[t] = 0;
+      const int jn = min(SEG, nvar - j0);
+#pragma unroll 1
+      for (int jj = 0; jj < jn; ++jj) {
+#pragma unroll
+        for (int t = 0; t < NT_MAX_VPM; ++t) {
+          if (t < nvpm) {
+            const unsigned long long m = __ballot(live && vt[t] == j0 + jj);
+            const unsigned long long mine = HALF ? (seg ? m >> 32 : m & 0xffffffffull) : m;
+            has[t] = ml == jj ? mine : has[t];
+          }
+        }
+      }
+      Acc aj;
+      P::acc_zero(aj);
+#pragma unroll 1
+      while (true) {
+        unsigned long long any = 0;
+#pragma unroll
+        for (int t = 0; t < NT_MAX_VPM; ++t) any |= has[t];
+        if (__ballot(any != 0) == 0) break;
+        if (any != 0) {
+          const int m = __ffsll((long long)any) - 1;
+          int ts = 0;
+          bool found = false;
+#pragma unroll
+          for (int t = 0; t < NT_MAX_VPM; ++t) {
+            const bool hit = !found && ((has[t] >> m) & 1);
+            ts = hit ? t : ts;
+            has[t] &= ~(hit ? 1ull << m : 0ull);
+            found = found || hit;
+          }
+          Acc d1;
+          P::acc_set(d1, P::load(ds + (seg * SEG + m) * nvpm + ts, dsp));
+          P::acc_merge(aj, d1);
+        }
+      }
+      const int j = j0 + ml;
+      if (e < e1 && j < nvar)
+        P::store(A + (size_t)s * NP * neq * nvar + (size_t)j * neq + e, (size_t)neq * nvar, P::acc_value(aj));
     }
-  }
-  if (lane < nvar) {
-    double *ap = A + (size_t)s * NP * neq * nvar;
-    P::store(ap + (size_t)lane * neq + e, (size_t)neq * nvar, P::acc_value(aj));
+    lds_wait();  // read before the next equations overwrite them
   }
 }
 

@@ -93,3 +93,16 @@ def test_first_bad_diagonal(n, bad):
     _, info = api.ls_backsolve(T(R), T(y))
     torch.cuda.synchronize()
     assert int(info.item()) == bad + 1
+
+
+@pytest.mark.parametrize("prec,m,n", [(1, 1, 1), (1, 512, 9), (1, 513, 7), (1, 1025, 6), (1, 2049, 5), (2, 512, 6),
+                                      (2, 1025, 5), (2, 2049, 3), (4, 65, 7), (4, 600, 5), (4, 1100, 3)])
+def test_projections_of_a_new_right_hand_side(prec, m, n):
+    p = inputs.random_problem(prec, m, n, seed=m + n, config=93)
+    o = oracle.mgs(p["A"], p["b"])
+    x, info = api.ls_solve(T(o["Q"]), T(o["R"]), T(p["b"]))
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    xo, _ = oracle.ls_solve(o["Q"], o["R"], p["b"])
+    # kappa below 100 at these shapes, relative to ||x|| + ||b|| / sigma_min
+    assert rel(x.cpu().numpy(), xo) <= 100 * TAU[prec]
