@@ -5,8 +5,16 @@
 //
 // Per system the operations are those of Figure 1 (Section 3) on the
 // augmented matrix of Equation (1): column j receives the projections
-// k = 1, ..., j-1 in order, then its norm r_jj and q_j = a_j / r_jj; then
-// the back substitution of Section 6, Figure 3 on y = the projections of b.
+// k = 1, ..., j-1 in order, then its norm r_jj; then the back substitution
+// of Section 6, Figure 3 on y = the projections of b.  The projections are
+// made with u_k, column k after its last one, before its normalisation:
+//   r_kj = (u_k^H a_j) / r_kk,   a_j -= ((u_k^H a_j) / ||u_k||^2) u_k,
+// equal to q_k^H a_j and r_kj q_k in exact arithmetic; the inner products
+// and ||u_k||^2 come out of one sum, so the chain from column to column has
+// one sum and one division and neither square root nor normalisation (one
+// 32 x 32 system: double 41 -> 34 us, dd 80 -> 69 us).  qd, and dd past 32
+// rows, use q_k itself (there the second reciprocal's registers and products
+// cost more than the shorter chain gives: qd 453 against 502 us).
 //
 // A wave is a grid of 16 row groups x 4 columns: lane 4 g + c holds rows
 // g, g + 16, ... (RPL of them) of one column per slot, so that a wave works
@@ -17,17 +25,20 @@
 // never receives a projection, has no slot.  Sums: the two halves of the
 // wave exchange so that one half carries on with the real and one with the
 // imaginary part, the odd and even rows of 16 lanes likewise with two slots
-// (permlane32_swap / permlane16_swap), then two rotations within a row: 5
-// merges of real accumulators for two complex sums (6 + 6 each way in a scan
-// of 64 lanes).  The tree of an inner product is the same whatever the wave
-// count and the slot, so a system's results do not depend on the shape.
+// or with the norm (permlane32_swap / permlane16_swap), then two rotations
+// within a row: 5 merges of real accumulators for two complex sums (6 + 6
+// each way in a scan of 64 lanes).  The tree of a sum and every later
+// operation is the same whatever the wave count and the slot, so a system's
+// results do not depend on the shape.
 //
 // One wave per system (NW = 1, large batches) needs no synchronisation at
-// all.  With several waves (a short chain for few systems) q_k passes
-// through a ring in LDS: the owner of column k+1 applies q_k to that column
-// first, normalises and publishes it, and only then applies q_k to its other
-// slots; the ring's entry is reused when every wave has read it.  Every
-// wait is bounded by a wall-clock limit (MGS_INFO_SYNC_TIMEOUT in info).
+// all.  With several waves (a short chain for few systems) u_k passes
+// through a ring in LDS: the owner of column k+1 applies u_k to that slot
+// first and publishes u_{k+1}, and only then goes on with its other slots;
+// the ring's entry is reused when every wave has read it.  The first wave,
+// whose columns are the last to be due, normalises: Q and R's diagonal.
+// Every wait is bounded by a wall-clock limit (MGS_INFO_SYNC_TIMEOUT in
+// info).
 #pragma once
 #include "../../include/mgsqr.h"
 #include "resident_kernels.hpp"
@@ -127,24 +138,44 @@ struct GridSum {
   }
   __device__ static __forceinline__ const RAcc *parts(const Acc &t) { return reinterpret_cast<const RAcc *>(&t); }
 
+  // Packed sums: the real part in the lower half of the wave, the imaginary
+  // part in the upper; t0 in the even rows of 16 lanes, t1 in the odd.
+  __device__ static __forceinline__ Rl sum2(const Acc &t0, const Acc &t1) {
+    return finish(fold16(fold32(parts(t0)[0], parts(t0)[1]), fold32(parts(t1)[0], parts(t1)[1])));
+  }
+  __device__ static __forceinline__ Rl sum(const Acc &t) {
+    const RAcc u = fold32(parts(t)[0], parts(t)[1]);
+    return finish(fold16(u, u));
+  }
   __device__ static __forceinline__ Rl real_sum(const Acc &t) {
     RAcc u = parts(t)[0];
     u = fold32(u, u);
     return finish(fold16(u, u));
   }
-  __device__ static __forceinline__ C sum(const Acc &t) {
-    const RAcc u = fold32(parts(t)[0], parts(t)[1]);
-    return spread(finish(fold16(u, u)));
+  // t in every row, and the real sum s in every lane.
+  __device__ static __forceinline__ Rl sum_and_real(const Acc &t, const Acc &s, Rl &real) {
+    RAcc u = parts(s)[0];
+    u = fold32(u, u);
+    Rl v = finish(fold16(fold32(parts(t)[0], parts(t)[1]), u));
+    unpack16(v, real);
+    return v;
   }
-  __device__ static __forceinline__ void sum2(const Acc &t0, const Acc &t1, C &c0, C &c1) {
-    Rl v0 = finish(fold16(fold32(parts(t0)[0], parts(t0)[1]), fold32(parts(t1)[0], parts(t1)[1]))), v1 = v0;
-    double *p0 = reinterpret_cast<double *>(&v0), *p1 = reinterpret_cast<double *>(&v1);
+  // a's even rows in all rows of a, its odd rows in all rows of b.
+  __device__ static __forceinline__ void unpack16(Rl &a, Rl &b) {
+    b = a;
+    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
 #pragma unroll
-    for (int i = 0; i < L; ++i) lane_swap16(p0[i], p1[i]);
-    c0 = spread(v0);
-    c1 = spread(v1);
+    for (int i = 0; i < L; ++i) lane_swap16(pa[i], pb[i]);
   }
 };
+
+// Whether the projections are made with the unnormalised u_k.  It takes the
+// square root and the normalisation off the chain, for one multiplication of
+// each sum and registers for both reciprocals.
+template <class P, int RPL>
+constexpr bool bat_unnormalised() {
+  return P::L <= 2 && P::L * RPL <= 4;
+}
 
 // RPL rows per lane (m <= 16 RPL), SL slots (columns 2, 3, ... of [A b]: at
 // most 4 NW SL), NW waves, at least WPE waves per SIMD (the register
@@ -155,16 +186,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   using Acc = typename P::Acc;
   using Rl = typename P::R;
   using G = GridSum<P>;
-  constexpr int NP = 2 * P::L;              // planes of a complex element
+  constexpr int L = P::L, NP = 2 * L;       // limbs, planes of a complex element
   constexpr int MP = BAT_RG * RPL;          // padded rows
   constexpr int STEP = BAT_CG * NW;         // columns per slot
-  constexpr int RING = NW == 1 ? 2 : 8;     // q vectors kept
-  __shared__ double qs[RING][NP][MP];       // q_c in entry c mod RING
-  __shared__ double ys[NP][BAT_MAX_COLS];   // y
-  __shared__ int pub;                       // q vectors published
-  __shared__ int done[NW];                  // q vectors each wave has read
+  constexpr int RING = NW == 1 ? 2 : 8;     // u vectors kept
+  constexpr bool UF = bat_unnormalised<P, RPL>();  // u_k is column k unnormalised
+  constexpr bool LATE = UF && NW > 1;       // R and y are divided by r_kk at the end
+  __shared__ double us[RING][NP][MP];       // u_c in entry c mod RING
+  __shared__ double ys[NP][BAT_MAX_COLS];   // y (NW > 1: over 1 / r_kk until the end)
+  __shared__ double invs[L][LATE ? BAT_MAX_COLS : 1];  // 1 / r_kk
+  __shared__ double ups[UF ? BAT_MAX_COLS : 1];  // what each column was divided by
+  __shared__ int pub;                       // u vectors published
+  __shared__ int done[NW];                  // u vectors each wave has read
   __shared__ int status;                    // this system's info
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cg = lane & (BAT_CG - 1), rg = lane / BAT_CG;
   const int sys = blockIdx.x;
   const int m = a.m, n = a.n, last = a.ncols - 1;
@@ -176,7 +212,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   double *y = a.y != nullptr ? a.y + (size_t)sys * NP * n : nullptr;
   if (tid == 0) {
     status = 0;
-    pub = 0;
+    pub = 1;
   }
   if (tid < NW) done[tid] = 0;
   const int first = last - (BAT_CG * w + cg);  // this lane's column in slot 0; slot s: first - STEP s
@@ -193,14 +229,96 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       }
     }
   };
+  auto put_u = [&](int c, const C (&v)[RPL]) __attribute__((always_inline)) {
+    double *dst = &us[c & (RING - 1)][0][0];
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) P::store(dst + rg + BAT_RG * r, (size_t)MP, v[r]);
+  };
+  // b, and a column of A with an entry of 2^200 or more, over the power of
+  // two of its largest entry: exact, and it keeps 1 / ||u||^2 and u^H a in
+  // range.  An infinity or a NaN stays one; the bound keeps both powers
+  // normal numbers.
+  auto rescale = [&](int j, C (&v)[RPL]) __attribute__((always_inline)) {
+    if constexpr (UF) {
+      double t[NP], big = 0.0;
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) {
+        P::store(t, 1, v[r]);
+        big = fmax(big, fmax(fabs(t[0]), fabs(t[1])));
+      }
+      double f = 1.0;
+      if (__any(j == n || big >= 0x1p200)) {
+#pragma unroll
+        for (int k = BAT_CG; k < 64; k *= 2) big = fmax(big, __shfl_xor(big, k));
+        int e = (j == n || big >= 0x1p200) && big > 0.0 && big < INFINITY ? ilogb(big) : 0;
+        e = e > 1000 ? 1000 : (e < -1000 ? -1000 : e);
+        f = ldexp(1.0, e);
+        const double down = ldexp(1.0, -e);
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+          P::store(t, 1, v[r]);
+#pragma unroll
+          for (int i = 0; i < NP; ++i) t[i] *= down;
+          v[r] = P::load(t, 1);
+        }
+      }
+      if (rg == 0 && j >= 0) ups[j] = f;
+    }
+  };
   C col[SL][RPL];
   static_for<SL>([&](auto sI) __attribute__((always_inline)) {
     constexpr int s = decltype(sI)::value;
     const int j = first - STEP * s;
     load_col(j >= 1 ? j : -1, col[s]);
   });
-  C q[RPL];
-  if (w == 0) load_col(0, q);
+  static_for<SL>([&](auto sI) __attribute__((always_inline)) {
+    constexpr int s = decltype(sI)::value;
+    const int j = first - STEP * s;
+    rescale(j >= 1 ? j : -1, col[s]);
+  });
+  C u[RPL];
+  Rl s2, rkk, inv;  // ||u_k||^2, its root, 1 over that
+  // Q's column c and R's diagonal from u (unnormalised) in lane group g1
+  auto normalise = [&](int c, int g1, C (&v)[RPL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+      const int i = rg + BAT_RG * r;
+      v[r] = P::scale(v[r], inv);
+      if (cg == g1 && i < m) P::store(Q + (size_t)c * a.ldq + i, planeQ, v[r]);
+    }
+    if (rg == 0 && cg == g1) {
+      double t[L];
+      P::store_real(t, 1, s2);
+      bool ok = P::ok_norm(s2);
+      if constexpr (UF) ok = ok && t[0] * ups[c] * ups[c] < INFINITY;
+      if (!ok) atomicCAS(&status, 0, c + 1);
+      if constexpr (LATE) P::store_real(&invs[0][c], BAT_MAX_COLS, inv);
+      P::store_real(t, 1, rkk);
+#pragma unroll
+      for (int i = 0; i < L; ++i) {
+        double *p = R + (size_t)c * a.ldr + c + (size_t)(2 * i) * planeR;
+        p[0] = UF ? t[i] * ups[c] : t[i];
+        p[planeR] = 0.0;
+      }
+    }
+  };
+  auto norm = [&](const C (&v)[RPL]) __attribute__((always_inline)) {
+    Acc t;
+    P::acc_zero(t);
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) P::acc_abs2(t, v[r]);
+    return t;
+  };
+  if (w == 0) {
+    load_col(0, u);
+    rescale(cg == 0 ? 0 : -1, u);
+    if constexpr (!UF) {
+      s2 = G::real_sum(norm(u));
+      root_and_inverse<P>(s2, rkk, inv);
+      normalise(0, 0, u);
+    }
+    if (cg == 0) put_u(0, u);
+  }
   __syncthreads();
 
   bool alive = true;
@@ -216,21 +334,60 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     }
     return true;
   };
-  // r_cc = ||v||, q_c = v / r_cc for column c in lane group gc of this wave
-  // (every group computes, group gc stores): Q, the ring, R(c, c).
-  auto normalise = [&](int c, int gc, C (&v)[RPL]) __attribute__((always_inline)) {
+  auto dot = [&](const C (&v)[RPL]) __attribute__((always_inline)) {
     Acc t;
     P::acc_zero(t);
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) P::acc_abs2(t, v[r]);
-    const Rl s2 = G::real_sum(t);
-    Rl rkk, inv;
-    root_and_inverse<P>(s2, rkk, inv);
+    for (int r = 0; r < RPL; ++r) P::acc_cmulc(t, u[r], v[r]);
+    return t;
+  };
+  // r_kj of column j (this lane's part: the upper half's is the imaginary
+  // one) to R, or to y for b; one lane per column and part stores.  With
+  // several waves it is u_k^H a_j, to be divided by r_kk at the end: the
+  // square root stays off the chain.
+  auto store_r = [&](int k, int j, const Rl &v) __attribute__((always_inline)) {
+    if ((rg & 3) == 0 && j > k) {
+      double t[L];
+      P::store_real(t, 1, v);
+      const int part = lane >> 5;
+      if (j < n) {
+        double *p = R + (size_t)j * a.ldr + k + part * planeR;
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) v[r] = P::scale(v[r], inv);
+        for (int i = 0; i < L; ++i) p[(size_t)(2 * i) * planeR] = t[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < L; ++i) {
+          ys[2 * i + part][k] = t[i];
+          if (!UF && y != nullptr) y[k + (size_t)(2 * i + part) * n] = t[i];
+        }
+      }
+    }
+  };
+  auto update = [&](int k, int j, const Rl &t, C (&v)[RPL]) __attribute__((always_inline)) {
+    const C c = G::spread(t);
+    if (j > k) {
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) P::upd(v[r], c, u[r]);
+    }
+  };
+  // Column c, in slot s1 and lane group g1 of this wave, to the ring.
+  auto publish = [&](int c, int s1, int g1) __attribute__((always_inline)) {
+    C v[RPL];
+    static_for<SL>([&](auto sI) __attribute__((always_inline)) {
+      constexpr int s = decltype(sI)::value;
+      if (s == s1) {
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) v[r] = col[s][r];
+      }
+    });
+    if constexpr (!UF) {
+      s2 = G::real_sum(norm(v));
+      root_and_inverse<P>(s2, rkk, inv);
+      normalise(c, g1, v);
+    }
     if constexpr (NW > 1) {
-      // the ring's entry is free once every wave has read q_{c - RING}
-      if (alive && c >= RING)
+      // the entry is free once every wave has read u_{c - RING}
+      if (c >= RING)
         alive = wait_for([&]() __attribute__((always_inline)) {
           int lo = c;
 #pragma unroll
@@ -239,58 +396,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
           return lo > c - RING;
         });
     }
-    if (cg == gc) {
-      double *dst = &qs[c & (RING - 1)][0][0];
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) {
-        const int i = rg + BAT_RG * r;
-        P::store(dst + i, (size_t)MP, v[r]);
-        if (i < m) P::store(Q + (size_t)c * a.ldq + i, planeQ, v[r]);
-      }
-      if (rg == 0) {
-        if (!P::ok_norm(s2)) atomicCAS(&status, 0, c + 1);
-        C d;
-        d.re = rkk;
-        d.im = P::rzero();
-        P::store(R + (size_t)c * a.ldr + c, planeR, d);
-      }
-    }
+    if (cg == g1) put_u(c, v);
     lds_wait();
     if (NW > 1 && lane == 0) __hip_atomic_store(&pub, c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
-  auto dot = [&](const C (&v)[RPL]) __attribute__((always_inline)) {
-    Acc t;
-    P::acc_zero(t);
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) P::acc_cmulc(t, q[r], v[r]);
-    return t;
-  };
-  // r_kj of column j to R (to y for b), a_j -= r_kj q_k.
-  auto update = [&](int k, int j, const C &rk, C (&v)[RPL]) __attribute__((always_inline)) {
-    if (j > k) {
-      if (rg == 0) {
-        if (j < n)
-          P::store(R + (size_t)j * a.ldr + k, planeR, rk);
-        else {
-          P::store(&ys[0][k], (size_t)BAT_MAX_COLS, rk);
-          if (y != nullptr) P::store(y + k, (size_t)n, rk);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) P::upd(v[r], rk, q[r]);
-    }
-  };
 
-  if (w == 0) normalise(0, 0, q);
+  bool mine = false;  // u_k was published by this wave
   for (int k = 0; k < n; ++k) {
     // slots holding a column past k: the largest column of slot s is
-    // last - 4 w - STEP s
+    // last - 4 w - STEP s; the first wave goes on to normalise
     const int above = last - BAT_CG * w - k;
-    if (above <= 0) break;
-    const int nact = (above + STEP - 1) / STEP;
+    if (above <= 0 && (!UF || w > 0)) break;
+    const int nact = above > 0 ? (above + STEP - 1) / STEP : 0;
     res_jitter(a.jitter, (unsigned)k);
     if constexpr (NW > 1) {
-      if (!wait_for([&]() __attribute__((always_inline)) {
+      if (!mine && !wait_for([&]() __attribute__((always_inline)) {
             return __hip_atomic_load(&pub, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > k;
           })) {
         alive = false;
@@ -299,65 +419,82 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       asm volatile("" ::: "memory");
     }
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) q[r] = P::load(&qs[k & (RING - 1)][0][rg + BAT_RG * r], (size_t)MP);
+    for (int r = 0; r < RPL; ++r) u[r] = P::load(&us[k & (RING - 1)][0][rg + BAT_RG * r], (size_t)MP);
     if constexpr (NW > 1) {
       lds_wait();
       if (lane == 0) __hip_atomic_store(&done[w], k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     // position of column k + 1 among the slots (its slot, wave and group)
     const int pos = last - (k + 1);
-    const int s1 = pos / STEP, w1 = (pos - s1 * STEP) / BAT_CG, g1 = pos & (BAT_CG - 1);
-    const bool own = k + 1 < n && w1 == w;
+    const int s1 = pos / STEP, g1 = pos & (BAT_CG - 1);
+    const bool own = k + 1 < n && (pos - s1 * STEP) / BAT_CG == w;
+    mine = own;
     if constexpr (NW == 1) {
+      Rl iw;
+      if constexpr (UF) {
+        s2 = G::real_sum(norm(u));
+        iw = P::recip(s2);
+        root_and_inverse<P>(s2, rkk, inv);
+      }
+      auto times = [&](const Rl &v, const Rl &f) __attribute__((always_inline)) { return UF ? P::rmul(v, f) : v; };
       static_for<SL / 2>([&](auto pI) __attribute__((always_inline)) {
         constexpr int s = 2 * decltype(pI)::value;
+        const int j0 = first - STEP * s, j1 = first - STEP * (s + 1);
         if (s + 1 < nact) {
-          C r0, r1;
-          G::sum2(dot(col[s]), dot(col[s + 1]), r0, r1);
-          update(k, first - STEP * s, r0, col[s]);
-          update(k, first - STEP * (s + 1), r1, col[s + 1]);
+          const Rl v = G::sum2(dot(col[s]), dot(col[s + 1]));
+          store_r(k, (lane >> 4) & 1 ? j1 : j0, times(v, inv));
+          Rl t0 = times(v, iw), t1;
+          G::unpack16(t0, t1);
+          update(k, j0, t0, col[s]);
+          update(k, j1, t1, col[s + 1]);
         } else if (s < nact) {
-          update(k, first - STEP * s, G::sum(dot(col[s])), col[s]);
+          const Rl v = G::sum(dot(col[s]));
+          if (((lane >> 4) & 1) == 0) store_r(k, j0, times(v, inv));
+          update(k, j0, times(v, iw), col[s]);
         }
       });
-      if (own) {
+      if (own) publish(k + 1, s1, g1);
+    } else {
+      // the slot of the next column first, then its publication
+      Rl iw;
+      if (nact > 0) {
+        const int sf = own ? s1 : 0;
+        Rl vf;
         static_for<SL>([&](auto sI) __attribute__((always_inline)) {
           constexpr int s = decltype(sI)::value;
-          if (s == s1) {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) q[r] = col[s][r];
+          if (s == sf) {
+            if constexpr (UF) {
+              vf = G::sum_and_real(dot(col[s]), norm(u), s2);
+              iw = P::recip(s2);
+              update(k, first - STEP * s, P::rmul(vf, iw), col[s]);
+            } else {
+              vf = G::sum(dot(col[s]));
+              update(k, first - STEP * s, vf, col[s]);
+            }
           }
         });
-        normalise(k + 1, g1, q);
-      }
-    } else {
-      // the next column first: its projection, its norm, its publication
-      C qk[RPL];
-#pragma unroll
-      for (int r = 0; r < RPL; ++r) qk[r] = q[r];
-#pragma unroll 1
-      for (int pass = own ? 0 : 1; pass < 2; ++pass) {
+        if (own) publish(k + 1, s1, g1);
+        if (((lane >> 4) & 1) == 0) store_r(k, first - STEP * sf, vf);
         static_for<SL>([&](auto sI) __attribute__((always_inline)) {
           constexpr int s = decltype(sI)::value;
-          if (s < nact && (pass == 0 ? s == s1 : !(own && s == s1)))
-            update(k, first - STEP * s, G::sum(dot(col[s])), col[s]);
+          if (s < nact && s != sf) {
+            const Rl v = G::sum(dot(col[s]));
+            update(k, first - STEP * s, UF ? P::rmul(v, iw) : v, col[s]);
+            if (((lane >> 4) & 1) == 0) store_r(k, first - STEP * s, v);
+          }
         });
-        if (pass == 0) {
-          static_for<SL>([&](auto sI) __attribute__((always_inline)) {
-            constexpr int s = decltype(sI)::value;
-            if (s == s1) {
-#pragma unroll
-              for (int r = 0; r < RPL; ++r) q[r] = col[s][r];
-            }
-          });
-          normalise(k + 1, g1, q);
-          if (!alive) break;
-#pragma unroll
-          for (int r = 0; r < RPL; ++r) q[r] = qk[r];
-        }
+      } else if constexpr (UF) {
+        s2 = G::real_sum(norm(u));
       }
-      if (!alive) break;
+      if constexpr (UF) {
+        if (w == 0) root_and_inverse<P>(s2, rkk, inv);
+      }
     }
+    // u_k in every lane group: the first wave normalises column k
+    if constexpr (UF) {
+      if (w == 0) normalise(k, 0, u);
+    }
+    if (!alive) break;
   }
   if constexpr (NW > 1) {
     if (lane == 0) __hip_atomic_store(&done[w], BAT_MAX_COLS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -369,12 +506,44 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
     for (int r = 0; r < RPL; ++r) P::acc_abs2(t, col[0][r]);
     const Rl s2 = G::real_sum(t);
-    if (lane == 0) P::store_real(a.rho + (size_t)sys * P::L, 1, P::ok_norm(s2) ? P::sqrt_(s2) : P::rzero());
+    if (lane == 0) {
+      double t2[L];
+      P::store_real(t2, 1, P::ok_norm(s2) ? P::sqrt_(s2) : P::rzero());
+#pragma unroll
+      for (int i = 0; i < L; ++i) a.rho[(size_t)sys * L + i] = (UF ? t2[i] * ups[n] : t2[i]);
+    }
   }
-  // Zeros below the diagonal of R.
+  // R below its diagonal: zeros.  Above it, and in y, what is still missing:
+  // 1 / r_kk, and the power of two of the column.
+  auto late = [&](int k, int j, const C &v) __attribute__((always_inline)) {
+    Rl f;
+    double *pf = reinterpret_cast<double *>(&f), t[NP];
+    if constexpr (LATE) {
+#pragma unroll
+      for (int i = 0; i < L; ++i) pf[i] = invs[i][k];
+      P::store(t, 1, P::scale(v, f));
+    } else {
+      P::store(t, 1, v);
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i) t[i] *= ups[j];
+    return P::load(t, 1);
+  };
+  if constexpr (UF) __syncthreads();
   for (int j = w; j < n; j += NW) {
-    const int i = j + 1 + lane;
-    if (i < n) P::store(R + (size_t)j * a.ldr + i, planeR, P::czero());
+    if (lane >= n) continue;
+    double *p = R + (size_t)j * a.ldr + lane;
+    if (lane > j) P::store(p, planeR, P::czero());
+    if constexpr (UF) {
+      if (lane < j && (LATE || ups[j] != 1.0)) P::store(p, planeR, late(lane, j, P::load(p, planeR)));
+    }
+  }
+  if constexpr (UF) {
+    if (w == 0 && last == n && lane < n) {
+      const C v = late(lane, n, P::load(&ys[0][lane], (size_t)BAT_MAX_COLS));
+      P::store(&ys[0][lane], (size_t)BAT_MAX_COLS, v);
+      if (y != nullptr) P::store(y + lane, (size_t)n, v);
+    }
   }
   __syncthreads();
   const int bad = status;
@@ -385,7 +554,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // y_j -= r_jk x_k for j < k (column k of R read coalesced, two ahead).
   const int jl = lane < n ? lane : n - 1;
   C yv = P::load(&ys[0][jl], (size_t)BAT_MAX_COLS);
-  const Rl inv = P::recip(P::load(R + (size_t)jl * a.ldr + jl, planeR).re);
+  inv = P::recip(P::load(R + (size_t)jl * a.ldr + jl, planeR).re);
   auto rcol = [&](int k) __attribute__((always_inline)) {
     return P::load(R + (size_t)(k > 0 ? k : 0) * a.ldr + jl, planeR);
   };

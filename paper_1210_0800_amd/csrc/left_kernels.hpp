@@ -89,6 +89,7 @@ mgs_left_kernel(LeftArgs a) {
   constexpr int H = G::H, L = P::L, RWG = 64 * NW;
   __shared__ double xch[2][2][H][NW];  // wave totals, [buffer][part][word][wave]
   __shared__ double lrec[2][L];        // 1 / ||u_k||^2 of the step
+  __shared__ int emax;                 // a large column's exponent
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int buf = 0, seen = 0;
   unsigned step = 0;
@@ -166,6 +167,35 @@ mgs_left_kernel(LeftArgs a) {
       for (int r = 0; r < RPT; ++r) {
         const int i = r * RWG + tid;
         col[r] = i < a.m ? P::load(src + i, pl) : P::czero();
+      }
+    }
+    // A column with an entry of 2^200 or more, over the power of two of its
+    // largest entry (`up`): exact, and it keeps 1 / ||u||^2 and u^H a in
+    // range.  An infinity or a NaN stays one; the bound keeps both powers
+    // normal numbers.
+    double up = 1.0;
+    if (!isb) {
+      double t[2 * L], big = 0.0;
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        P::store(t, 1, col[r]);
+        big = fmax(big, fmax(fabs(t[0]), fabs(t[1])));
+      }
+      if (__syncthreads_or(big >= 0x1p200)) {
+        if (tid == 0) emax = 0;
+        __syncthreads();
+        if (big >= 0x1p200) atomicMax(&emax, big < INFINITY ? ilogb(big) : 2000);
+        __syncthreads();
+        const int e = emax == 2000 ? 0 : emax > 1000 ? 1000 : emax;
+        up = ldexp(1.0, e);
+        const double down = ldexp(1.0, -e);
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+          P::store(t, 1, col[r]);
+#pragma unroll
+          for (int i = 0; i < 2 * L; ++i) t[i] *= down;
+          col[r] = P::load(t, 1);
+        }
       }
     }
     const int kend = c < a.n ? c : a.n;
@@ -258,21 +288,27 @@ mgs_left_kernel(LeftArgs a) {
       continue;
     }
     put_record(c, 0, P::recip(s2));
-    if (!P::ok_norm(s2) && tid == 0) info_first_bad(a.info, c + 1);
     Rl rkk, inv;
     root_and_inverse<P>(s2, rkk, inv);
     put_record(c, 1, inv);
     if (tid == 0) {
-      C d;
-      d.re = rkk;
-      d.im = P::rzero();
-      P::store(a.R + (size_t)c * a.ldr + c, a.planeR, d);
+      double t[L];
+      P::store_real(t, 1, s2);
+      if (!P::ok_norm(s2) || !(t[0] * up * up < INFINITY)) info_first_bad(a.info, c + 1);
+      // R(c, c); its imaginary part carries `up` to left_finish_kernel
+      P::store_real(t, 1, rkk);
+      double *d = a.R + (size_t)c * a.ldr + c;
+#pragma unroll
+      for (int i = 0; i < L; ++i) {
+        d[(size_t)(2 * i) * a.planeR] = t[i] * up;
+        d[(size_t)(2 * i + 1) * a.planeR] = i == 0 ? up : 0.0;
+      }
     }
   }
 }
 
-// Column j of Q times 1 / r_jj, R(k, j) times 1 / r_kk for k < j, zeros below
-// R's diagonal.  One workgroup per column.
+// Column j of Q times 1 / r_jj, R(k, j) times 1 / r_kk and column j's power of
+// two for k < j, zeros below R's diagonal.  One workgroup per column.
 template <class P>
 __global__ __launch_bounds__(256) void left_finish_kernel(int m, int n, double *Q, int ldq, size_t planeQ, double *R,
                                                           int ldr, size_t planeR, const double *rec) {
@@ -286,15 +322,22 @@ __global__ __launch_bounds__(256) void left_finish_kernel(int m, int n, double *
     return v;
   };
   const Rl inv = inverse(j);
+  double *diag = R + (size_t)j * ldr + j + planeR;
+  const double up = *diag;
+  __syncthreads();
+  if (threadIdx.x == 0) *diag = 0.0;
   for (int i = threadIdx.x; i < m; i += 256) {
     double *p = Q + (size_t)j * ldq + i;
     P::store(p, planeQ, P::scale(P::load(p, planeQ), inv));
   }
   for (int k = threadIdx.x; k < n; k += 256) {
     double *p = R + (size_t)j * ldr + k;
-    if (k < j)
-      P::store(p, planeR, P::scale(P::load(p, planeR), inverse(k)));
-    else if (k > j)
+    if (k < j) {
+      double t[2 * P::L];
+      P::store(t, 1, P::scale(P::load(p, planeR), inverse(k)));
+#pragma unroll
+      for (int i = 0; i < 2 * P::L; ++i) p[(size_t)i * planeR] = t[i] * up;
+    } else if (k > j)
       P::store(p, planeR, P::czero());
   }
 }

@@ -687,36 +687,42 @@ int batched_launch(const BatArgs &a, hipStream_t st) {
 // The shape by batch size, all with the same results.  While the systems
 // alone do not fill the card, several waves each shorten a system's chain;
 // beyond, one wave per system does the least work (pairs of slots share a
-// sum, nothing is synchronised).  Measured, 32 x 32, us per call for 8
-// waves of 1 slot against 1 wave of 8: double 41 / 50 at 1 system, 53 / 56
-// at 512, 94 / 63 at 1024; dd 80 / 130, 117 / 141, 215 / 148.  qd (one
-// wave per SIMD), 4 waves of 2 slots, 2 of 4, 1 of 8: 447 / 631 / 1006 at 1,
-// 479 / 639 / 1048 at 256, 901 / 668 / 1088 at 512, 1796 / 1277 / 1134 at
-// 1024.  More than 32 slotted columns or rows: fewer slots per wave, as the
-// registers allow (64 x 63, 4000 systems: double 2 x 8 0.90 ms, 4 x 4 1.16,
-// 8 x 2 1.50; dd 3.92, 3.82 with scratch, 4.32).
+// sum, nothing is synchronised).  Measured, us per call:
+//   32 x 32, 8 waves of 1 slot / 1 wave of 8: double 34 / 48 at 1 system,
+//   47 / 56 at 512, 80 / 63 at 1024; dd 69 / 128, 118 / 145, 215 / 149.
+//   qd (one wave per SIMD), 4 waves of 2 slots / 2 of 4 / 1 of 8: 453 / 627 /
+//   954 at 1, 480 / 657 / 1012 at 256, 928 / 681 / 1028 at 512, 1838 / 1288 /
+//   1080 at 1024.
+// More than 32 slotted columns, the slots per wave as the registers allow
+// (waves x slots):
+//   double 64 x 63, 16 x 1 / 4 x 4: 88 / 110 at 1, 105 / 127 at 256, 184 /
+//   156 at 512, 1299 / 1110 at 4000 (42 x 42: 50 / 62 and 706 / 455);
+//   dd 64 x 63, 8 x 2 / 4 x 4 / 2 x 8: 250 / 268 / 431 at 1, 281 / 304 / 471
+//   at 256, 1062 / 1143 / 945 at 1024 (42 x 42: 121 / 128 / 186, 137 / 145 /
+//   206, 516 / 366 / 417);
+//   qd 48 x 40, 4 x 4 / 8 x 2: 841 / 1057 at 1, 3396 / 4567 at 1024.
+// qd past 32 rows with at most 32 slotted columns (48 x 28), 4 waves of 2
+// slots / 2 of 4: 517 / 698 at 1, 549 / 743 at 256, 2074 / 1509 at 1024.
 template <class P, int RPL>
 int batched_shape(const BatArgs &a, int cus, hipStream_t st) {
   const int slotted = a.ncols - 1;  // column 1 has no slot
+  const bool one = a.batch <= cus, two = a.batch <= 2 * cus;  // systems per compute unit
   if constexpr (P::L == 4) {
-    if constexpr (RPL == 4) {
+    if constexpr (RPL >= 3) {
       if (slotted > 32) return batched_launch<P, RPL, 4, 4, 1>(a, st);
-      if (a.batch <= cus) return batched_launch<P, RPL, 2, 4, 1>(a, st);
-      return batched_launch<P, RPL, 4, 2, 1>(a, st);
+      return one ? batched_launch<P, RPL, 2, 4, 1>(a, st) : batched_launch<P, RPL, 4, 2, 1>(a, st);
     } else {
-      if (a.batch <= cus) return batched_launch<P, RPL, 2, 4, 1>(a, st);
-      if (a.batch <= 2 * cus) return batched_launch<P, RPL, 4, 2, 1>(a, st);
-      return batched_launch<P, RPL, 8, 1, 1>(a, st);
+      if (one) return batched_launch<P, RPL, 2, 4, 1>(a, st);
+      return two ? batched_launch<P, RPL, 4, 2, 1>(a, st) : batched_launch<P, RPL, 8, 1, 1>(a, st);
     }
+  } else if constexpr (RPL >= 3) {
+    if (slotted <= 32) return two ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 1>(a, st);
+    if constexpr (P::L == 1)
+      return one ? batched_launch<P, RPL, 1, 16, 4>(a, st) : batched_launch<P, RPL, 4, 4, 2>(a, st);
+    if (one) return batched_launch<P, RPL, 2, 8, 2>(a, st);
+    return RPL == 3 ? batched_launch<P, RPL, 4, 4, 1>(a, st) : batched_launch<P, RPL, 8, 2, 1>(a, st);
   } else {
-    const bool few = a.batch <= 2 * cus;
-    if constexpr (RPL == 4) {
-      if (slotted > 32)
-        return few ? batched_launch<P, RPL, 2, 8, 2>(a, st) : batched_launch<P, RPL, 8, 2, 1>(a, st);
-      return few ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 1>(a, st);
-    } else {
-      return few ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 2>(a, st);
-    }
+    return two ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 2>(a, st);
   }
 }
 template <class P>
@@ -725,6 +731,7 @@ int batched_dispatch(const BatArgs &a, hipStream_t st) {
   const int cus = dev_info(d) && d.cus > 0 ? d.cus : 256;
   if (a.m <= BAT_RG) return batched_shape<P, 1>(a, cus, st);
   if (a.m <= 2 * BAT_RG) return batched_shape<P, 2>(a, cus, st);
+  if (a.m <= 3 * BAT_RG) return batched_shape<P, 3>(a, cus, st);
   return batched_shape<P, 4>(a, cus, st);
 }
 int batched_dispatch(int prec, const BatArgs &a, hipStream_t st) {

@@ -35,3 +35,38 @@ def test_results_do_not_depend_on_the_shape(prec, m, n):
             assert torch.equal(f[k], ref[k][idx]), (batch, k)
         for k in ("Q", "R", "info"):
             assert torch.equal(g[k], qr[k][idx]), (batch, k)
+
+
+@pytest.mark.parametrize("prec,m,n", [(1, 20, 12), (1, 42, 42), (1, 64, 63), (2, 32, 32), (2, 48, 40), (4, 30, 20)])
+def test_powers_of_two(prec, m, n):
+    """Columns and b times powers of two whose squares are still in range:
+    the same Q, x, y and R up to those powers, to the precision's error bar
+    (64 eps: no operation rounds differently but at the ends of the range);
+    a column whose squares are out of range is refused, as is one after it
+    that is fine."""
+    eps = {1: 2.0**-52, 2: 2.0**-104, 4: 2.0**-208}[prec]
+    p = inputs.random_problem(prec, m, n, seed=5, config=97)
+    e = np.zeros(n, int)
+    e[1], e[n // 2], e[n - 1], eb = 480, 300, 150, 400
+    A2, b2 = p["A"] * np.ldexp(1.0, e)[None, None, :, None], p["b"] * 2.0**eb
+    one = torch.from_numpy(np.stack([p["A"]])).cuda(), torch.from_numpy(np.stack([p["b"]])).cuda()
+    f = api.lstsq_batched(*one, with_y=True, with_rho=True)
+    for batch in (1, 300, 600):
+        A = torch.from_numpy(A2).cuda().expand(batch, *A2.shape).contiguous()
+        b = torch.from_numpy(b2).cuda().expand(batch, *b2.shape).contiguous()
+        g = api.lstsq_batched(A, b, with_y=True, with_rho=True)
+        torch.cuda.synchronize()
+        assert int((g["info"] != 0).sum().item()) == 0
+        back = {k: g[k][-1].cpu().numpy() for k in ("Q", "R", "x", "y", "rho")}
+        back["R"] = back["R"] / np.ldexp(1.0, e)[None, None, :, None]
+        back["x"] = back["x"] * np.ldexp(1.0, e - eb)
+        back["y"], back["rho"] = back["y"] * 2.0**-eb, back["rho"] * 2.0**-eb
+        for k, v in back.items():
+            # limb by limb from the leading one: the difference is exact
+            d = np.abs(sum(v[i] - f[k][0].cpu().numpy()[i] for i in range(prec)))
+            assert float(d.max()) <= 64 * eps * max(1.0, float(np.abs(f[k][0].cpu().numpy()[0]).max())), (batch, k)
+    A2 = p["A"].copy()
+    A2[:, :, n // 2] *= 2.0**530
+    for batch in (1, 600):
+        A = torch.from_numpy(A2).cuda().expand(batch, *A2.shape).contiguous()
+        assert int(api.lstsq_batched(A)["info"][-1].item()) == n // 2 + 1

@@ -112,3 +112,29 @@ def test_bad_columns():
     f = api.mgs_qr(T(A), T(p["b"]))
     torch.cuda.synchronize()
     assert int(f["info"].item()) == 1
+
+
+@pytest.mark.parametrize("m,n", [(40, 20), (100, 30), (600, 8)])
+def test_columns_near_the_end_of_the_range(m, n):
+    # columns times powers of two whose squares are still in range: the same
+    # Q, y and R up to those powers (64 eps: no operation rounds differently);
+    # a column whose squares are out of range is refused
+    p = inputs.random_problem(4, m, n, seed=15, config=98)
+    e = np.zeros(n, int)
+    e[0], e[n // 2], e[n - 1] = 490, 480, 300
+    A2 = p["A"] * np.ldexp(1.0, e)[None, None, :, None]
+    f, g = api.mgs_qr(T(p["A"]), T(p["b"])), api.mgs_qr(T(A2), T(p["b"]))
+    torch.cuda.synchronize()
+    assert int(g["info"].item()) == 0
+    back = {k: N(g[k]) for k in ("Q", "R", "y", "rho")}
+    assert np.all(back["R"][:, 1, np.arange(n), np.arange(n)] == 0)
+    back["R"] = back["R"] / np.ldexp(1.0, e)[None, None, :, None]
+    for k, v in back.items():
+        w = N(f[k])
+        d = np.abs(sum(v[i] - w[i] for i in range(4)))
+        assert float(d.max()) <= 64 * 2.0**-208 * max(1.0, float(np.abs(w[0]).max())), k
+    A2 = p["A"].copy()
+    A2[:, :, n // 2] *= 2.0**530
+    g = api.mgs_qr(T(A2), T(p["b"]))
+    torch.cuda.synchronize()
+    assert int(g["info"].item()) == n // 2 + 1
