@@ -68,107 +68,6 @@ struct BatArgs {
   unsigned jitter;  // race checks: seed of the timing jitter (0: none)
 };
 
-// a's upper half of the wave against b's lower half: a = [a.lo, b.lo],
-// b = [a.hi, b.hi].
-__device__ __forceinline__ void lane_swap32(double &a, double &b) {
-  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  a = __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]);
-  b = __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
-}
-// The same for a's odd rows of 16 lanes against b's even rows.
-__device__ __forceinline__ void lane_swap16(double &a, double &b) {
-  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  a = __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]);
-  b = __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
-}
-
-// Sums over the row groups of a wave's lane grid.
-template <class P>
-struct GridSum {
-  using Acc = typename P::Acc;
-  using RAcc = typename P::RAcc;
-  using Rl = typename P::R;
-  using C = typename P::C;
-  static constexpr int H = sizeof(RAcc) / sizeof(double), L = P::L;
-
-  // a and b folded over the halves (16: over the row pairs): a in the lower
-  // half (even rows), b in the upper half (odd rows).
-  __device__ static __forceinline__ RAcc fold32(RAcc a, RAcc b) {
-    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
-#pragma unroll
-    for (int i = 0; i < H; ++i) lane_swap32(pa[i], pb[i]);
-    P::racc_merge(a, b);
-    return a;
-  }
-  __device__ static __forceinline__ RAcc fold16(RAcc a, RAcc b) {
-    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
-#pragma unroll
-    for (int i = 0; i < H; ++i) lane_swap16(pa[i], pb[i]);
-    P::racc_merge(a, b);
-    return a;
-  }
-  // The rest of the sum, within rows of 16 lanes (4 row groups).
-  __device__ static __forceinline__ Rl finish(RAcc v) {
-    rot<0x128>(v);  // row_ror:8
-    rot<0x124>(v);  // row_ror:4
-    return P::racc_value(v);
-  }
-  template <int CTRL>
-  __device__ static __forceinline__ void rot(RAcc &v) {
-    RAcc o;
-    double *po = reinterpret_cast<double *>(&o);
-    const double *pv = reinterpret_cast<const double *>(&v);
-#pragma unroll
-    for (int i = 0; i < H; ++i) po[i] = dpp_shift<CTRL, 0xf>(pv[i]);
-    P::racc_merge(v, o);
-  }
-  // v of the lower half in re, of the upper half in im, in every lane.
-  __device__ static __forceinline__ C spread(const Rl &v) {
-    C c;
-    c.re = v;
-    c.im = v;
-    double *pr = reinterpret_cast<double *>(&c.re), *pi = reinterpret_cast<double *>(&c.im);
-#pragma unroll
-    for (int i = 0; i < L; ++i) lane_swap32(pr[i], pi[i]);
-    return c;
-  }
-  __device__ static __forceinline__ const RAcc *parts(const Acc &t) { return reinterpret_cast<const RAcc *>(&t); }
-
-  // Packed sums: the real part in the lower half of the wave, the imaginary
-  // part in the upper; t0 in the even rows of 16 lanes, t1 in the odd.
-  __device__ static __forceinline__ Rl sum2(const Acc &t0, const Acc &t1) {
-    return finish(fold16(fold32(parts(t0)[0], parts(t0)[1]), fold32(parts(t1)[0], parts(t1)[1])));
-  }
-  __device__ static __forceinline__ Rl sum(const Acc &t) {
-    const RAcc u = fold32(parts(t)[0], parts(t)[1]);
-    return finish(fold16(u, u));
-  }
-  __device__ static __forceinline__ Rl real_sum(const Acc &t) {
-    RAcc u = parts(t)[0];
-    u = fold32(u, u);
-    return finish(fold16(u, u));
-  }
-  // t in every row, and the real sum s in every lane.
-  __device__ static __forceinline__ Rl sum_and_real(const Acc &t, const Acc &s, Rl &real) {
-    RAcc u = parts(s)[0];
-    u = fold32(u, u);
-    Rl v = finish(fold16(fold32(parts(t)[0], parts(t)[1]), u));
-    unpack16(v, real);
-    return v;
-  }
-  // a's even rows in all rows of a, its odd rows in all rows of b.
-  __device__ static __forceinline__ void unpack16(Rl &a, Rl &b) {
-    b = a;
-    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
-#pragma unroll
-    for (int i = 0; i < L; ++i) lane_swap16(pa[i], pb[i]);
-  }
-};
-
 // Whether the projections are made with the unnormalised u_k.  It takes the
 // square root and the normalisation off the chain, for one multiplication of
 // each sum and registers for both reciprocals.
@@ -234,10 +133,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
     for (int r = 0; r < RPL; ++r) P::store(dst + rg + BAT_RG * r, (size_t)MP, v[r]);
   };
-  // b, and a column of A with an entry of 2^200 or more, over the power of
-  // two of its largest entry: exact, and it keeps 1 / ||u||^2 and u^H a in
-  // range.  An infinity or a NaN stays one; the bound keeps both powers
-  // normal numbers.
+  // b, and a column of A whose largest entry is not within 2^-200 .. 2^200,
+  // over the power of two of that entry: exact, and it keeps 1 / ||u||^2 and
+  // u^H a in range.  An infinity or a NaN stays one; the bound keeps both
+  // powers normal numbers.
   auto rescale = [&](int j, C (&v)[RPL]) __attribute__((always_inline)) {
     if constexpr (UF) {
       double t[NP], big = 0.0;
@@ -247,10 +146,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
         big = fmax(big, fmax(fabs(t[0]), fabs(t[1])));
       }
       double f = 1.0;
-      if (__any(j == n || big >= 0x1p200)) {
+      auto far = [](double v) __attribute__((always_inline)) { return v >= 0x1p200 || (v > 0.0 && v <= 0x1p-200); };
+      if (__any(j == n || far(big))) {
 #pragma unroll
         for (int k = BAT_CG; k < 64; k *= 2) big = fmax(big, __shfl_xor(big, k));
-        int e = (j == n || big >= 0x1p200) && big > 0.0 && big < INFINITY ? ilogb(big) : 0;
+        int e = (j == n || far(big)) && big > 0.0 && big < INFINITY ? ilogb(big) : 0;
         e = e > 1000 ? 1000 : (e < -1000 ? -1000 : e);
         f = ldexp(1.0, e);
         const double down = ldexp(1.0, -e);
@@ -290,7 +190,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       double t[L];
       P::store_real(t, 1, s2);
       bool ok = P::ok_norm(s2);
-      if constexpr (UF) ok = ok && t[0] * ups[c] * ups[c] < INFINITY;
+      if constexpr (UF) ok = ok && t[0] * ups[c] * ups[c] < INFINITY && t[0] * ups[c] * ups[c] > 0.0;
       if (!ok) atomicCAS(&status, 0, c + 1);
       if constexpr (LATE) P::store_real(&invs[0][c], BAT_MAX_COLS, inv);
       P::store_real(t, 1, rkk);

@@ -169,10 +169,10 @@ mgs_left_kernel(LeftArgs a) {
         col[r] = i < a.m ? P::load(src + i, pl) : P::czero();
       }
     }
-    // A column with an entry of 2^200 or more, over the power of two of its
-    // largest entry (`up`): exact, and it keeps 1 / ||u||^2 and u^H a in
-    // range.  An infinity or a NaN stays one; the bound keeps both powers
-    // normal numbers.
+    // A column whose largest entry is not within 2^-200 .. 2^200, over the
+    // power of two of that entry (`up`): exact, and it keeps 1 / ||u||^2 and
+    // u^H a in range.  An infinity or a NaN stays one; the bound keeps both
+    // powers normal numbers.
     double up = 1.0;
     if (!isb) {
       double t[2 * L], big = 0.0;
@@ -181,12 +181,12 @@ mgs_left_kernel(LeftArgs a) {
         P::store(t, 1, col[r]);
         big = fmax(big, fmax(fabs(t[0]), fabs(t[1])));
       }
-      if (__syncthreads_or(big >= 0x1p200)) {
-        if (tid == 0) emax = 0;
+      if (__syncthreads_or(big >= 0x1p200 || (big > 0.0 && big <= 0x1p-200))) {
+        if (tid == 0) emax = -2000;
         __syncthreads();
-        if (big >= 0x1p200) atomicMax(&emax, big < INFINITY ? ilogb(big) : 2000);
+        if (big > 0.0) atomicMax(&emax, big < INFINITY ? ilogb(big) : 2000);
         __syncthreads();
-        const int e = emax == 2000 ? 0 : emax > 1000 ? 1000 : emax;
+        const int e = emax >= 2000 || (emax < 200 && emax >= -200) ? 0 : emax > 1000 ? 1000 : emax < -1000 ? -1000 : emax;
         up = ldexp(1.0, e);
         const double down = ldexp(1.0, -e);
 #pragma unroll
@@ -294,7 +294,7 @@ mgs_left_kernel(LeftArgs a) {
     if (tid == 0) {
       double t[L];
       P::store_real(t, 1, s2);
-      if (!P::ok_norm(s2) || !(t[0] * up * up < INFINITY)) info_first_bad(a.info, c + 1);
+      if (!P::ok_norm(s2) || !(t[0] * up * up < INFINITY && t[0] * up * up > 0.0)) info_first_bad(a.info, c + 1);
       // R(c, c); its imaginary part carries `up` to left_finish_kernel
       P::store_real(t, 1, rkk);
       double *d = a.R + (size_t)c * a.ldr + c;

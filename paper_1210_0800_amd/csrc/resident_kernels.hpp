@@ -27,12 +27,18 @@
 //    owner copies it, not yet normalised, to U and only then normalises
 //    it.  The owners of the next `defer` columns poll U[k] directly (Q and
 //    U hold a signalling-NaN pattern until written) and, in one block sum
-//    with one barrier (DPP scans per wave, the NW wave totals merged by
-//    every thread), get both ||a_k||^2 and a_k^H a_j; from these they form
-//    r_kk and q_k exactly as the owner does (same partials, same merge
-//    tree, same operations) and r_kj = (a_k^H a_j) / r_kk, equal to
-//    q_k^H a_j in exact arithmetic.  Their other columns receive these
-//    projections later, from Q, in order.
+//    with one barrier (each wave's halves and rows of lanes carry the real
+//    part, the imaginary part and the norm together, the NW wave totals are
+//    merged by every wave), get both ||a_k||^2 and a_k^H a_j; from these,
+//    with one reciprocal and neither square root nor normalisation,
+//    a_j -= ((a_k^H a_j) / ||a_k||^2) a_k, and off the chain r_kj =
+//    (a_k^H a_j) / r_kk, equal to r_kj q_k and q_k^H a_j in exact
+//    arithmetic.  Their other columns receive these projections later,
+//    from Q, in order.
+//
+//    The chain's link bounds every size that fits (18 merges of real
+//    accumulators and a square root on it before, 7 and a reciprocal now):
+//    dd 1024 x 1024 5.1 -> 4.7 us a link, 512 x 384 3.7 -> 3.3 us.
 //  * Consecutive columns sit on the same XCD (workgroup numbering is
 //    rotated so that logical workgroups 0..G/8-1 land on one XCD).
 //
@@ -268,11 +274,7 @@ __device__ __forceinline__ bool res_wait(const Args &a, int k, int wave, int &se
   }
 }
 
-// Wave reduction by DPP: an inclusive scan inside each row of 16 lanes
-// (shifts 1, 2, 4, 8), then the row totals carried across rows; lane 63
-// ends with the sum of all 64 lanes (a fixed merge tree, so results are
-// reproducible).  Lanes shifted in from outside a row read zero, which
-// the accumulator merge adds exactly.
+// v of another lane of the row of 16, by the DPP control CTRL.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_shift(double v) {
   const long long b = __double_as_longlong(v);
@@ -280,33 +282,118 @@ __device__ __forceinline__ double dpp_shift(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-// One DPP step of a wave sum for any accumulator: every double of the
-// accumulator (the real half only when re_only) moves by CTRL, then the
-// merge.  Lanes shifted in from outside a row read zero.
-template <class P, int CTRL, int ROWS>
-__device__ __forceinline__ void dpp_step_any(typename P::Acc &a, bool re_only) {
-  using Acc = typename P::Acc;
-  constexpr int NA = sizeof(Acc) / sizeof(double);
-  Acc o;
-  double *po = reinterpret_cast<double *>(&o);
-  const double *pa = reinterpret_cast<const double *>(&a);
-#pragma unroll
-  for (int c = 0; c < NA; ++c) po[c] = (re_only && c >= NA / 2) ? 0.0 : dpp_shift<CTRL, ROWS>(pa[c]);
-  if (re_only)
-    P::acc_merge_re(a, o);
-  else
-    P::acc_merge(a, o);
+// a's upper half of the wave against b's lower half: a = [a.lo, b.lo],
+// b = [a.hi, b.hi].
+__device__ __forceinline__ void lane_swap32(double &a, double &b) {
+  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  a = __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
 }
-// Wave sum into lane 63 (fixed tree: row scans, then the row totals).
+// The same for a's odd rows of 16 lanes against b's even rows.
+__device__ __forceinline__ void lane_swap16(double &a, double &b) {
+  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  a = __longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
+// Sums over a wave: its halves, then its odd and even rows of 16 lanes, each
+// exchange so that one carries on with one sum and the other with another,
+// then rotations within the rows.  A complex sum over all 64 lanes takes 7
+// merges of real accumulators with a second real sum beside it (18 in scans).
 template <class P>
-__device__ __forceinline__ void wave_sum_any(typename P::Acc &a, bool re_only) {
-  dpp_step_any<P, 0x111, 0xf>(a, re_only);  // row_shr:1
-  dpp_step_any<P, 0x112, 0xf>(a, re_only);  // row_shr:2
-  dpp_step_any<P, 0x114, 0xf>(a, re_only);  // row_shr:4
-  dpp_step_any<P, 0x118, 0xf>(a, re_only);  // row_shr:8
-  dpp_step_any<P, 0x142, 0xa>(a, re_only);  // row_bcast:15 into rows 1, 3
-  dpp_step_any<P, 0x143, 0xc>(a, re_only);  // row_bcast:31 into rows 2, 3
-}
+struct GridSum {
+  using Acc = typename P::Acc;
+  using RAcc = typename P::RAcc;
+  using Rl = typename P::R;
+  using C = typename P::C;
+  static constexpr int H = sizeof(RAcc) / sizeof(double), L = P::L;
+
+  // a and b folded over the halves (16: over the row pairs): a in the lower
+  // half (even rows), b in the upper half (odd rows).
+  __device__ static __forceinline__ RAcc fold32(RAcc a, RAcc b) {
+    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
+#pragma unroll
+    for (int i = 0; i < H; ++i) lane_swap32(pa[i], pb[i]);
+    P::racc_merge(a, b);
+    return a;
+  }
+  __device__ static __forceinline__ RAcc fold16(RAcc a, RAcc b) {
+    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
+#pragma unroll
+    for (int i = 0; i < H; ++i) lane_swap16(pa[i], pb[i]);
+    P::racc_merge(a, b);
+    return a;
+  }
+  // v summed over the rows of 16 lanes.
+  __device__ static __forceinline__ RAcc row_sum(RAcc v) {
+    rot<0x128>(v);  // row_ror:8
+    rot<0x124>(v);  // row_ror:4
+    rot<0x122>(v);  // row_ror:2
+    rot<0x121>(v);  // row_ror:1
+    return v;
+  }
+  // The rest of a sum over the row groups of a 16 x 4 lane grid, within rows
+  // of 16 lanes (4 row groups).
+  __device__ static __forceinline__ Rl finish(RAcc v) {
+    rot<0x128>(v);  // row_ror:8
+    rot<0x124>(v);  // row_ror:4
+    return P::racc_value(v);
+  }
+  template <int CTRL>
+  __device__ static __forceinline__ void rot(RAcc &v) {
+    RAcc o;
+    double *po = reinterpret_cast<double *>(&o);
+    const double *pv = reinterpret_cast<const double *>(&v);
+#pragma unroll
+    for (int i = 0; i < H; ++i) po[i] = dpp_shift<CTRL, 0xf>(pv[i]);
+    P::racc_merge(v, o);
+  }
+  // v of the lower half in re, of the upper half in im, in every lane.
+  __device__ static __forceinline__ C spread(const Rl &v) {
+    C c;
+    c.re = v;
+    c.im = v;
+    double *pr = reinterpret_cast<double *>(&c.re), *pi = reinterpret_cast<double *>(&c.im);
+#pragma unroll
+    for (int i = 0; i < L; ++i) lane_swap32(pr[i], pi[i]);
+    return c;
+  }
+  __device__ static __forceinline__ const RAcc *parts(const Acc &t) { return reinterpret_cast<const RAcc *>(&t); }
+
+  // Packed sums: the real part in the lower half of the wave, the imaginary
+  // part in the upper; t0 in the even rows of 16 lanes, t1 in the odd.
+  __device__ static __forceinline__ Rl sum2(const Acc &t0, const Acc &t1) {
+    return finish(fold16(fold32(parts(t0)[0], parts(t0)[1]), fold32(parts(t1)[0], parts(t1)[1])));
+  }
+  __device__ static __forceinline__ Rl sum(const Acc &t) {
+    const RAcc u = fold32(parts(t)[0], parts(t)[1]);
+    return finish(fold16(u, u));
+  }
+  __device__ static __forceinline__ Rl real_sum(const Acc &t) {
+    RAcc u = parts(t)[0];
+    u = fold32(u, u);
+    return finish(fold16(u, u));
+  }
+  // t in every row, and the real sum s in every lane.
+  __device__ static __forceinline__ Rl sum_and_real(const Acc &t, const Acc &s, Rl &real) {
+    RAcc u = parts(s)[0];
+    u = fold32(u, u);
+    Rl v = finish(fold16(fold32(parts(t)[0], parts(t)[1]), u));
+    unpack16(v, real);
+    return v;
+  }
+  // a's even rows in all rows of a, its odd rows in all rows of b.
+  __device__ static __forceinline__ void unpack16(Rl &a, Rl &b) {
+    b = a;
+    double *pa = reinterpret_cast<double *>(&a), *pb = reinterpret_cast<double *>(&b);
+#pragma unroll
+    for (int i = 0; i < L; ++i) lane_swap16(pa[i], pb[i]);
+  }
+};
 
 // One complex element of a planar array (2L planes, stride `plane`) with
 // device-scope loads / stores, plane by plane; `miss` is set when a plane
@@ -345,11 +432,14 @@ struct Resident {
   static constexpr int NA = sizeof(Acc) / sizeof(double);  // doubles per accumulator
   double (*red)[NA][RWG];  // LDS: per-thread partial sums, [CB][NA][RWG]
   Acc *rsum;               // LDS: reduced sums, [CB]
-  double (*xch)[RES_BWMAX][NA][NW];  // LDS: wave totals of the panel steps, [2][RES_BWMAX][NA][NW]
+  using RAcc = typename P::RAcc;
+  using G = GridSum<P>;
+  static constexpr int H = G::H;  // doubles per real accumulator
+  double (*xch)[4][H][NW];  // LDS: wave totals of the chain's steps, [2][row of 16 lanes][H][NW]
   int xb = 0;              // xch buffer of the next panel-step reduction
 
   __device__ __forceinline__ Resident(const ResArgs &args, double (*r)[NA][RWG], Acc *rs,
-                                      double (*x)[RES_BWMAX][NA][NW])
+                                      double (*x)[4][H][NW])
       : a(args), red(r), rsum(rs), xch(x) {
     tid = threadIdx.x;
     wave = tid >> 6;
@@ -388,9 +478,10 @@ struct Resident {
     }
   }
   __device__ __forceinline__ void reduce_slot(int s, bool re_only) {
-    Acc t = red_tree<0, NW>(s, re_only);
-    wave_sum_any<P>(t, re_only);
-    if (lane == 63) rsum[s] = t;
+    const Acc t = red_tree<0, NW>(s, re_only);
+    const RAcc u = G::fold32(G::parts(t)[0], G::parts(t)[re_only ? 0 : 1]);
+    const RAcc v = G::row_sum(G::fold16(u, u));
+    if ((lane & 31) == 0) reinterpret_cast<RAcc *>(&rsum[s])[lane >> 5] = v;
   }
 
   // r_kj for the slots s whose column lies in (k, hi) and >= lo: the inner
@@ -432,38 +523,37 @@ struct Resident {
     });
   }
 
-  // Block sums on the critical path (the steps that factor a panel), with a
-  // single barrier: each wave scans its own partial (DPP), lane 63 stores
-  // the wave total, and after the barrier every wave merges the NW wave
-  // totals in the same fixed pairwise tree (xch_sum), so all threads hold
-  // the same sum.  Two buffers alternate: a wave can only overwrite one
-  // after every wave has passed the next barrier, i.e. finished reading it.
-  __device__ __forceinline__ void xch_put(int pos, Acc t, bool re_only) {
-    wave_sum_any<P>(t, re_only);
-    if (lane == 63) {
-      const double *d = reinterpret_cast<const double *>(&t);
+  // Block sums on the critical path, with a single barrier: the real and the
+  // imaginary part of t over the wave in its rows 0 and 2 of 16 lanes and
+  // the real sum s in its odd rows, each row's total by its first lane to
+  // LDS.  Two buffers alternate: a wave can only overwrite one after every
+  // wave has passed the next barrier, i.e. finished reading it.
+  __device__ __forceinline__ void xch_put(const RAcc &re, const RAcc &im, const RAcc &s) {
+    const RAcc v = G::row_sum(G::fold16(G::fold32(re, im), G::fold32(s, s)));
+    if ((lane & 15) == 0) {
+      const double *d = reinterpret_cast<const double *>(&v);
 #pragma unroll
-      for (int c = 0; c < NA; ++c) xch[xb][pos][c][wave] = d[c];
+      for (int c = 0; c < H; ++c) xch[xb][lane >> 4][c][wave] = d[c];
     }
   }
-  // The merge of the NW wave totals, spread over the lanes: lane l starts
-  // from the total of wave l mod NW and log2(NW) butterfly steps merge it
-  // with the lane l^1, l^2, l^4 (DPP inside rows of 16 lanes, where the
-  // totals repeat with period NW, so that a rotation by 4 reaches the l^4
-  // partner's value).  The accumulator merge gives the same bits in either
-  // operand order (TwoSum's error term is exact), so every lane ends with
-  // the pairwise tree ((w0 w1)(w2 w3))((w4 w5)(w6 w7)), in 3 merges per
-  // lane instead of 7 one after another.
-  __device__ __forceinline__ Acc xch_sum(int pos, bool re_only) const {
+  // The merge of the NW wave totals of every row's sum, spread over the
+  // lanes: lane l starts from the total of wave l mod NW and log2(NW)
+  // butterfly steps merge it with the lane l^1, l^2, l^4 (DPP inside rows of
+  // 16 lanes, where the totals repeat with period NW, so that a rotation by 4
+  // reaches the l^4 partner's value).  The accumulator merge gives the same
+  // bits in either operand order (TwoSum's error term is exact), so every
+  // lane of a row ends with the same sum.
+  __device__ __forceinline__ Rl xch_sum() {
     static_assert(NW == 1 || NW == 2 || NW == 4 || NW == 8, "butterfly over at most 8 waves");
-    Acc x;
+    RAcc x;
     double *dx = reinterpret_cast<double *>(&x);
 #pragma unroll
-    for (int c = 0; c < NA; ++c) dx[c] = xch[xb][pos][c][lane & (NW - 1)];
-    if constexpr (NW >= 2) dpp_step_any<P, 0xB1, 0xf>(x, re_only);   // quad_perm [1,0,3,2]: lane l^1
-    if constexpr (NW >= 4) dpp_step_any<P, 0x4E, 0xf>(x, re_only);   // quad_perm [2,3,0,1]: lane l^2
-    if constexpr (NW >= 8) dpp_step_any<P, 0x124, 0xf>(x, re_only);  // row_ror:4: lane l+-4 within the row
-    return x;
+    for (int c = 0; c < H; ++c) dx[c] = xch[xb][lane >> 4][c][lane & (NW - 1)];
+    if constexpr (NW >= 2) G::template rot<0xB1>(x);   // quad_perm [1,0,3,2]: lane l^1
+    if constexpr (NW >= 4) G::template rot<0x4E>(x);   // quad_perm [2,3,0,1]: lane l^2
+    if constexpr (NW >= 8) G::template rot<0x124>(x);  // row_ror:4: lane l+-4 within the row
+    xb ^= 1;
+    return P::racc_value(x);
   }
 
   // Publication of q_k: this wave's device-scope stores of its rows are
@@ -513,10 +603,10 @@ struct Resident {
         for (int r = 0; r < RR; ++r) P::acc_abs2(nacc, col[s][r]);
       }
     });
-    xch_put(0, nacc, true);
+    const RAcc n2 = G::parts(nacc)[0];
+    xch_put(n2, n2, n2);
     lds_barrier();
-    const Rl s2 = P::acc_value_re(xch_sum(0, true));
-    xb ^= 1;
+    const Rl s2 = xch_sum();
     if (!P::ok_norm(s2) && tid == 0) info_first_bad(a.info, a.kbase + x + 1);
     Rl rkk, inv;
     root_and_inverse<P>(s2, rkk, inv);
@@ -546,49 +636,52 @@ struct Resident {
   }
 
   // Critical-path projection of column k onto the owned column ps (k >=
-  // ps - defer), from u = a_k after its last projection, read from U (in
-  // u's registers, which hold q_k on return).  One block sum gives both
-  // ||u||^2 and u^H a_ps; then r_kk and 1/r_kk exactly as the owner of
-  // column k computes them (same partials, same merge tree, same
-  // operations), q_k = u / r_kk, r_{k,ps} = (u^H a_ps) / r_kk (equal to
-  // q_k^H a_ps up to rounding) and a_ps -= r_{k,ps} q_k.  After the last
-  // projection (k = ps - 1) column ps is final and is handed on through U
-  // before anything else.
+  // ps - defer), from u = a_k after its last projection, read from U.  One
+  // block sum gives both u^H a_ps and ||u||^2, and
+  //   a_ps -= ((u^H a_ps) / ||u||^2) u,  r_{k,ps} = (u^H a_ps) / r_kk,
+  // equal to r_{k,ps} q_k and q_k^H a_ps in exact arithmetic: of the norm only
+  // a reciprocal is on the chain (a norm whose square or its reciprocal is
+  // near the end of the range goes by way of q_k = u / r_kk; only the owner
+  // decides whether column k is bad).  After the last projection (k =
+  // ps - 1) column ps is final and is handed on through U before anything
+  // else.
   __device__ __forceinline__ void lookahead_step(C (&u)[RR], int k, int ps, bool last) {
-    {
-      Acc an;
-      P::acc_zero(an);
+    Acc an, ad;
+    P::acc_zero(an);
 #pragma unroll
-      for (int r = 0; r < RR; ++r) P::acc_abs2(an, u[r]);
-      xch_put(1, an, true);
-    }
+    for (int r = 0; r < RR; ++r) P::acc_abs2(an, u[r]);
+    P::acc_zero(ad);
     static_for<CB>([&](auto sI) __attribute__((always_inline)) {
       constexpr int s = decltype(sI)::value;
       if (cidx[s] == ps) {
-        Acc ad;
-        P::acc_zero(ad);
 #pragma unroll
         for (int r = 0; r < RR; ++r) P::acc_cmulc(ad, u[r], col[s][r]);
-        xch_put(0, ad, false);
       }
     });
+    xch_put(G::parts(ad)[0], G::parts(ad)[1], G::parts(an)[0]);
     if (last) RES_TRACE_LAST(ps, 8);
     lds_barrier();
     if (last) RES_TRACE(ps, 5);
-    const Rl s2 = P::acc_value_re(xch_sum(1, true));
-    const C d = P::acc_value(xch_sum(0, false));
-    xb ^= 1;
-    Rl rkk, inv;
-    root_and_inverse<P>(s2, rkk, inv);
-    if (last) RES_TRACE(ps, 6);
+    Rl d = xch_sum(), s2;  // d: the real part in the lower half of the wave, the imaginary in the upper
+    G::unpack16(d, s2);
+    Rl f, rkk, inv;
+    double lead[P::L];
+    P::store_real(lead, 1, s2);
+    if (__any(lead[0] > 0x1p800 || lead[0] < 0x1p-800)) {
+      root_and_inverse<P>(s2, rkk, inv);
 #pragma unroll
-    for (int r = 0; r < RR; ++r) u[r] = P::scale(u[r], inv);
-    const C rk = P::scale(d, inv);
+      for (int r = 0; r < RR; ++r) u[r] = P::scale(u[r], inv);
+      f = inv;
+    } else {
+      f = P::recip(s2);
+    }
+    if (last) RES_TRACE(ps, 6);
+    const C t = G::spread(P::rmul(d, f));
     static_for<CB>([&](auto sI) __attribute__((always_inline)) {
       constexpr int s = decltype(sI)::value;
       if (cidx[s] == ps) {
 #pragma unroll
-        for (int r = 0; r < RR; ++r) P::upd(col[s][r], rk, u[r]);
+        for (int r = 0; r < RR; ++r) P::upd(col[s][r], t, u[r]);
       }
     });
     if (last) {
@@ -601,7 +694,12 @@ struct Resident {
     // R(k, ps) last: stores count towards the same wait counter as loads,
     // so a store issued before the hand-off would hold wave 0's rows of U
     // back until it completes.
-    if (tid == 0) P::store(a.R + (size_t)ps * a.ldr + k, a.planeR, rk);
+    if (wave == 0) {
+      root_and_inverse<P>(s2, rkk, inv);
+      const Rl rk = P::rmul(d, inv);
+      if ((lane & 31) == 0)
+        P::store_real(a.R + (size_t)ps * a.ldr + k + (lane >> 5) * a.planeR, 2 * a.planeR, rk);
+    }
   }
 
   __device__ __forceinline__ void copy_own(int k, C (&q)[RR]) {
@@ -876,7 +974,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW < 4 
   constexpr int NA = sizeof(Acc) / sizeof(double);
   __shared__ double red[CB][NA][64 * NW];
   __shared__ Acc rsum[CB];
-  __shared__ double xch[2][RES_BWMAX][NA][NW];
+  __shared__ double xch[2][4][NA / 2][NW];
   Resident<P, RR, CB, NW> st(a, red, rsum, xch);
   st.run();
 }

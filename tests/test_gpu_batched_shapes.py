@@ -47,7 +47,7 @@ def test_powers_of_two(prec, m, n):
     eps = {1: 2.0**-52, 2: 2.0**-104, 4: 2.0**-208}[prec]
     p = inputs.random_problem(prec, m, n, seed=5, config=97)
     e = np.zeros(n, int)
-    e[1], e[n // 2], e[n - 1], eb = 480, 300, 150, 400
+    e[1], e[n // 2], e[n - 2], e[n - 1], eb = 480, 300, -350, 150, 400
     A2, b2 = p["A"] * np.ldexp(1.0, e)[None, None, :, None], p["b"] * 2.0**eb
     one = torch.from_numpy(np.stack([p["A"]])).cuda(), torch.from_numpy(np.stack([p["b"]])).cuda()
     f = api.lstsq_batched(*one, with_y=True, with_rho=True)

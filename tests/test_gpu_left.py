@@ -121,7 +121,7 @@ def test_columns_near_the_end_of_the_range(m, n):
     # a column whose squares are out of range is refused
     p = inputs.random_problem(4, m, n, seed=15, config=98)
     e = np.zeros(n, int)
-    e[0], e[n // 2], e[n - 1] = 490, 480, 300
+    e[0], e[n // 2], e[n - 2], e[n - 1] = 490, 480, -250, 300
     A2 = p["A"] * np.ldexp(1.0, e)[None, None, :, None]
     f, g = api.mgs_qr(T(p["A"]), T(p["b"])), api.mgs_qr(T(A2), T(p["b"]))
     torch.cuda.synchronize()
