@@ -392,9 +392,13 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   // launches of a converged solve return at once, so the fixed max_iter
   // steps cost little past convergence.
   DevInfo d;
-  // (the barrier count of all steps must fit the 32-bit counter)
-  bool fused = m <= PR_MAX_ROWS && (long long)max_iter * 2 * nchunk * NBP < (1LL << 31) && dev_info(d) &&
-               d.cus >= NBP;
+  // (the barrier count of all steps must fit the 32-bit counter; the partial
+  // sums that pass between its workgroups lie where the residual's were, 80
+  // bytes per row and panel against 16 to 31)
+  const int pr_wgs = ceil_div(m, PR_ROWS);
+  bool fused = m <= PR_MAX_ROWS && (long long)max_iter * pr_wgs < (1LL << 31) && dev_info(d) && d.cus >= pr_wgs &&
+               (pr_wgs == 1 || sizeof(double) * 2 * NBP * (size_t)(nchunk < 3 ? nchunk : 3) * pr_wgs <=
+                                   sizeof(PrecQD::Acc) * (size_t)nchunk * m);
   const long long spin = fused ? (long long)d.wclk_khz * 2000 : 0;  // 2 s
   const unsigned jitter = g_jitter.load(std::memory_order_relaxed);
   for (int it = 1; it <= max_iter; ++it) {
@@ -403,18 +407,18 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
     hipLaunchKernelGGL((residual_finish_kernel<PrecQD>), dim3(ceil_div(m, 256)), dim3(256), 0, st, m, nchunk,
                        static_cast<const PrecQD::Acc *>(w.partial), w.r64, w.ctl);
     if (fused) {
-      // arrivals at the grid barriers of the earlier steps (2 per panel, G each)
-      unsigned int base = (unsigned int)(it - 1) * 2u * (unsigned int)nchunk * (unsigned int)NBP;
-      const double *Qa = w.Q64;
+      // arrivals at the grid barriers of the earlier steps (one each)
+      unsigned int base = pr_wgs > 1 ? (unsigned int)(it - 1) * (unsigned int)pr_wgs : 0u;
+      const double *Qa = w.Q64, *ra = w.r64;
       size_t pq = planeQ, pw = (size_t)n;
-      double *ra = w.r64, *wa = w.y64;
+      double *wa = w.y64, *pa = static_cast<double *>(w.partial);
       RefineCtl *ctl = w.ctl;
       int mm = m, nn = n;
       long long sp = spin;
       unsigned jt = jitter;
-      void *args[] = {&mm, &nn, &Qa, &pq, &ra, &wa, &pw, &ctl, &info, &base, &sp, &jt};
-      if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(proj_replay_kernel), dim3(NBP), dim3(256), args, 0,
-                                     st) != hipSuccess) {
+      void *args[] = {&mm, &nn, &Qa, &pq, &ra, &wa, &pw, &pa, &ctl, &info, &base, &sp, &jt};
+      if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(proj_replay_kernel), dim3(pr_wgs), dim3(256), args,
+                                     0, st) != hipSuccess) {
         (void)hipGetLastError();
         fused = false;  // the barrier count is off from here: per-panel launches for the rest
       }

@@ -185,7 +185,7 @@ struct RefineCtl {
   int iters;
   double dprev;
   double err_est;
-  unsigned int bar;    // arrivals at the grid barriers of proj_replay_kernel (zero at the start of a solve)
+  unsigned int bar;    // arrivals at the grid barrier of proj_replay_kernel (zero at the start of a solve)
   unsigned int abort;  // set when one of its waits timed out
 };
 
@@ -372,55 +372,62 @@ __global__ __launch_bounds__(256) void proj_r_kernel(int m, int nbp, const doubl
 
 // The correction's projections of all panels in one cooperative launch (one
 // per refinement step instead of two per panel): for each panel of NBP
-// columns, w_p = Q_p^H r (workgroup g forms columns g, g + G, ... with the
-// operations of proj_w_kernel), a grid barrier, r -= Q_p w_p (rows spread
-// over the grid, the operations of proj_r_kernel), a grid barrier.  Every
-// value is formed by one workgroup in a fixed order, so the results are
-// those of the per-panel kernels, bit for bit.  r and w pass between
-// workgroups with device-scope loads and stores (Q, written before the
-// launch, with plain loads), so a barrier needs no cache maintenance: every
-// wave waits for its stores to complete, then one thread per workgroup
-// counts its arrival in ctl->bar (which grows by G per barrier from `base`,
-// the arrivals of the earlier steps of this solve) and waits, bounded, for
-// the others; on a time-out the step ends with status 3 and
-// MGS_INFO_SYNC_TIMEOUT in info.  m <= PR_MAX_ROWS.
+// columns w_p = Q_p^H r, then r -= Q_p w_p.  Workgroup g holds rows 64 g ..
+// 64 g + 63 of r in registers for the whole launch, a row per lane, and wave
+// v its rows' entries of columns 16 v .. 16 v + 15 of the panel: both
+// products use them from one (coalesced) read, issued a panel ahead.  The
+// 16 columns' sums over the wave's rows halve the lanes and the values
+// together, step by step (31 additions for 32 sums).  Between workgroups
+// only the 128 partial sums per workgroup and panel pass, through `part`:
+// every workgroup reads all of them and adds them in one fixed order, so
+// that one exchange per panel is enough (bounded by it: 2048 x 2048, 781 ->
+// about 130 us per step; one exchange of w and one of r, by two grid barriers,
+// before).
+//
+// `part` ([min(3, panels)][G][2 NBP]) holds the empty marker until a value is written
+// (device-scope), so readers poll the data; a workgroup clears what it wrote
+// for panel p-1 when it has read all of panel p (which nobody sends before
+// having read panel p-1), and its stores are complete before it sends panel
+// p+1, which precedes any look at panel p+2 in the same place.  Before the
+// first panel every workgroup clears its places and the grid meets once
+// (ctl->bar, which grows by G per step from `base`).  On a time-out the step
+// ends with status 3 and MGS_INFO_SYNC_TIMEOUT in info.  m <= PR_MAX_ROWS.
 constexpr int PR_MAX_ROWS = 4096;
-__global__ __launch_bounds__(256) void proj_replay_kernel(int m, int n, const double *Q, size_t planeQ, double *r,
-                                                           double *w, size_t planew, RefineCtl *ctl, int *info,
-                                                           unsigned int base, long long spin_ticks,
-                                                           unsigned jitter) {
+constexpr int PR_ROWS = 64;  // rows per workgroup
+// One step of a wave's sums: the lanes with (lane & BIT) == 0 go on with a,
+// the others with b; CTRL brings the other lane's value.
+template <int BIT, int CTRL>
+__device__ __forceinline__ double pr_fold(double a, double b, int lane) {
+  const bool up = (lane & BIT) != 0;
+  return (up ? b : a) + dpp_shift<CTRL, 0xf>(up ? a : b);
+}
+__global__ __launch_bounds__(256) void proj_replay_kernel(int m, int n, const double *Q, size_t planeQ,
+                                                           const double *r, double *w, size_t planew, double *part,
+                                                           RefineCtl *ctl, int *info, unsigned int base,
+                                                           long long spin_ticks, unsigned jitter) {
   if (ctl->status != 0) return;
-  constexpr int NS = PR_MAX_ROWS / 256;
-  __shared__ double sr[4], si[4];
-  __shared__ double wl[2][NBP];
-  __shared__ int ok;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int WC = NBP / 4;  // panel columns per wave
+  __shared__ double ws[2][2 * NBP];   // w in two halves of the workgroups
+  __shared__ double xs[4][2][PR_ROWS];  // the waves' parts of Q_p w_p
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = gridDim.x, g = blockIdx.x;
-  unsigned int target = base;
-  unsigned step = 0;
-  auto grid_barrier = [&]() __attribute__((always_inline)) -> bool {
-    res_jitter(jitter, step++);
-    wait_vmem();  // this wave's device-scope stores of r and w have completed
-    __syncthreads();
-    target += (unsigned int)G;
-    if (tid == 0) {
-      atomicAdd(&ctl->bar, 1u);
-      PollBound poll;
-      int good = 1;
-      while (__hip_atomic_load(&ctl->bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-        if (poll.due() && (__hip_atomic_load(&ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ||
-                           poll.late(spin_ticks))) {
-          __hip_atomic_store(&ctl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          good = 0;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      ok = good;
-    }
-    __syncthreads();
-    asm volatile("" ::: "memory");
-    return ok != 0;
+  const int row = g * PR_ROWS + lane;
+  const int np = (n + NBP - 1) / NBP;
+  const size_t slot = (size_t)2 * NBP * G;  // doubles per panel of `part`
+  // this lane's place among a workgroup's sums: real parts, then imaginary
+  const int at = (lane >> 5) * NBP + wave * WC + ((lane >> 1) & (WC - 1));
+  double *own = part + (size_t)g * 2 * NBP + at;
+  const double e = __longlong_as_double(RES_EMPTY);
+  if (tid == 0) bad = 0;
+  if (tid < 2 * NBP) ws[1][tid] = 0.0;
+  PollBound poll;
+  auto give_up = [&]() __attribute__((always_inline)) {
+    if (!poll.due()) return false;
+    if (__hip_atomic_load(&ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && !poll.late(spin_ticks))
+      return false;
+    __hip_atomic_store(&ctl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
   };
   auto fail = [&]() __attribute__((always_inline)) {
     if (tid == 0) {
@@ -428,71 +435,128 @@ __global__ __launch_bounds__(256) void proj_replay_kernel(int m, int n, const do
       __hip_atomic_store(info, MGS_INFO_SYNC_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
-  for (int k0 = 0; k0 < n; k0 += NBP) {
-    const int nb = n - k0 < NBP ? n - k0 : NBP;
-    const double *Qp = Q + (size_t)k0 * m;
-    double *wp = w + k0;
-    if (g < nb) {
-      // this thread's rows tid + 256 s of r, all loads in flight together
-      double xr[NS], xi[NS];
+  double qr[WC], qi[WC];
+  auto load_panel = [&](int p, double (&vr)[WC], double (&vi)[WC]) __attribute__((always_inline)) {
+    const int c0 = p * NBP + wave * WC;
+    const double *src = Q + (size_t)c0 * m + row;
 #pragma unroll
-      for (int s2 = 0; s2 < NS; ++s2) {
-        const int i = tid + 256 * s2;
-        xr[s2] = i < m ? coh_load(r + i) : 0.0;
-        xi[s2] = i < m ? coh_load(r + i + m) : 0.0;
+    for (int c = 0; c < WC; ++c) {
+      const bool in = c0 + c < n && row < m;
+      vr[c] = in ? src[(size_t)c * m] : 0.0;
+      vi[c] = in ? src[(size_t)c * m + planeQ] : 0.0;
+    }
+  };
+  load_panel(0, qr, qi);
+  double xr = row < m ? r[row] : 0.0, xi = row < m ? r[row + m] : 0.0;
+  if (G > 1) {
+    if ((lane & 1) == 0) {
+      for (int k = 0; k < 3 && k < np; ++k) coh_store(own + k * slot, e);
+    }
+    wait_vmem();
+    __syncthreads();
+    if (tid == 0) {
+      atomicAdd(&ctl->bar, 1u);
+      while (__hip_atomic_load(&ctl->bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < base + (unsigned int)G) {
+        if (give_up()) {
+          bad = 1;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
       }
-      for (int c = g; c < nb; c += G) {
-        const double *qr = Qp + (size_t)c * m, *qi = qr + planeQ;
-        double ar = 0.0, ai = 0.0;
+    }
+  }
+  __syncthreads();
+  if (bad != 0) return fail();
+  int buf = 0, prev = 2;  // panel p mod 3, p - 1 mod 3
+  for (int p = 0; p < np; ++p) {
+    res_jitter(jitter, (unsigned)p);
+    // v[c], v[WC + c]: q_c^H r over this lane's row, then over the wave's
+    double v[2 * WC];
 #pragma unroll
-        for (int s2 = 0; s2 < NS; ++s2) {
-          const int i = tid + 256 * s2;
-          if (i < m) {
-            ar = __fma_rn(qr[i], xr[s2], ar);
-            ar = __fma_rn(qi[i], xi[s2], ar);
-            ai = __fma_rn(qr[i], xi[s2], ai);
-            ai = __fma_rn(-qi[i], xr[s2], ai);
+    for (int c = 0; c < WC; ++c) {
+      v[c] = __fma_rn(qi[c], xi, qr[c] * xr);
+      v[WC + c] = __fma_rn(-qi[c], xr, qr[c] * xi);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      lane_swap32(v[i], v[i + 16]);
+      v[i] += v[i + 16];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      lane_swap16(v[i], v[i + 8]);
+      v[i] += v[i + 8];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = pr_fold<8, 0x128>(v[i], v[i + 4], lane);  // row_ror:8: lane ^ 8
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = pr_fold<4, 0x141>(v[i], v[i + 2], lane);  // row_half_mirror: lane ^ 7
+    v[0] = pr_fold<2, 0x4E>(v[0], v[1], lane);                                   // quad_perm: lane ^ 2
+    v[0] += dpp_shift<0xB1, 0xf>(v[0]);                                          // quad_perm: lane ^ 1
+    double nr[WC], ni[WC];
+    if (G == 1) {
+      if ((lane & 1) == 0) ws[0][at] = v[0];
+      load_panel(p + 1, nr, ni);
+    } else {
+      wait_vmem();  // the cleared places of panel p - 2
+      if ((lane & 1) == 0) coh_store(own + buf * slot, v[0]);
+      load_panel(p + 1, nr, ni);
+      // sum tid mod 2 NBP of the workgroups of one parity
+      const double *src = part + buf * slot + (tid & (2 * NBP - 1));
+      const int h = tid / (2 * NBP);
+      double sum = 0.0;
+      constexpr int NF = 16;  // reads in flight
+      for (int g0 = h; g0 < G; g0 += 2 * NF) {
+        double t[NF];
+        while (true) {
+          bool miss = false;
+#pragma unroll
+          for (int i = 0; i < NF; ++i) {
+            const int gi = g0 + 2 * i;
+            t[i] = gi < G ? coh_load(src + (size_t)gi * 2 * NBP) : 0.0;
+            miss = miss || __double_as_longlong(t[i]) == RES_EMPTY;
           }
+          if (__ballot(miss) == 0) break;
+          if (give_up()) {
+            bad = 1;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
         }
 #pragma unroll
-        for (int mask = 32; mask >= 1; mask >>= 1) {
-          ar += __shfl_xor(ar, mask);
-          ai += __shfl_xor(ai, mask);
-        }
-        if (lane == 0) {
-          sr[wave] = ar;
-          si[wave] = ai;
-        }
-        __syncthreads();
-        if (tid == 0) {
-          coh_store(wp + c, ((sr[0] + sr[1]) + sr[2]) + sr[3]);
-          coh_store(wp + c + planew, ((si[0] + si[1]) + si[2]) + si[3]);
-        }
-        __syncthreads();
+        for (int i = 0; i < NF; ++i) sum += t[i];
       }
+      ws[h][tid & (2 * NBP - 1)] = sum;
     }
-    if (!grid_barrier()) return fail();
-    if (g * 256 < m) {
-      if (tid < nb) {
-        wl[0][tid] = coh_load(wp + tid);
-        wl[1][tid] = coh_load(wp + tid + planew);
-      }
-      __syncthreads();
-      for (int i = g * 256 + tid; i < m; i += G * 256) {
-        double xr = coh_load(r + i), xi = coh_load(r + i + m);
-        for (int c = 0; c < nb; ++c) {
-          const double qr = Qp[(size_t)c * m + i], qi = Qp[(size_t)c * m + i + planeQ];
-          const double wr = wl[0][c], wi = wl[1][c];
-          xr = __fma_rn(-qr, wr, xr);
-          xr = __fma_rn(qi, wi, xr);
-          xi = __fma_rn(-qr, wi, xi);
-          xi = __fma_rn(-qi, wr, xi);
-        }
-        coh_store(r + i, xr);
-        coh_store(r + i + m, xi);
-      }
+    __syncthreads();
+    if (bad != 0) return fail();
+    if (G > 1 && p > 0 && (lane & 1) == 0) coh_store(own + prev * slot, e);
+    if (g == 0 && tid < NBP && p * NBP + tid < n) {
+      w[p * NBP + tid] = ws[0][tid] + ws[1][tid];
+      w[p * NBP + tid + planew] = ws[0][NBP + tid] + ws[1][NBP + tid];
     }
-    if (!grid_barrier()) return fail();
+    double ar = 0.0, ai = 0.0;
+#pragma unroll
+    for (int c = 0; c < WC; ++c) {
+      const int k = wave * WC + c;
+      const double wr = ws[0][k] + ws[1][k], wi = ws[0][NBP + k] + ws[1][NBP + k];
+      ar = __fma_rn(qr[c], wr, ar);
+      ar = __fma_rn(-qi[c], wi, ar);
+      ai = __fma_rn(qr[c], wi, ai);
+      ai = __fma_rn(qi[c], wr, ai);
+    }
+    xs[wave][0][lane] = ar;
+    xs[wave][1][lane] = ai;
+    __syncthreads();
+    xr -= (xs[0][0][lane] + xs[1][0][lane]) + (xs[2][0][lane] + xs[3][0][lane]);
+    xi -= (xs[0][1][lane] + xs[1][1][lane]) + (xs[2][1][lane] + xs[3][1][lane]);
+#pragma unroll
+    for (int c = 0; c < WC; ++c) {
+      qr[c] = nr[c];
+      qi[c] = ni[c];
+    }
+    prev = buf;
+    buf = buf == 2 ? 0 : buf + 1;
   }
 }
 
