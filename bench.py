@@ -45,13 +45,13 @@ F_DD = dict(cmulc=60, upd=66, abs2=28, scale=20, merge=16)
 # policies (not the qd functions, which it does not use), of mgs_kernels.hpp
 # the helpers it uses, of mgsqr.hip the part that plans and launches the
 # single-launch factorisation); reported as null otherwise.
-TRAFFIC = dict(fetch_bytes=2.0 * 1.595e5 * 1024, write_bytes=1.687e5 * 1024, sources="6b02a83aa1e85c44")
+TRAFFIC = dict(fetch_bytes=2.0 * 1.590e5 * 1024, write_bytes=1.690e5 * 1024, sources="1c2b350fcfbc41fc")
 KERNEL_SOURCES = ["paper_1210_0800_amd/csrc/resident_kernels.hpp",
                   ("paper_1210_0800_amd/csrc/ddqd.hpp", "// Device arithmetic", "// " + "-" * 67 + " qd --"),
                   ("paper_1210_0800_amd/csrc/ddqd.hpp", "// " + "-" * 57 + " precisions ----", None),
                   ("paper_1210_0800_amd/csrc/mgs_kernels.hpp", "// MGS QR, least-squares", "struct StepArgs {"),
                   ("paper_1210_0800_amd/csrc/mgsqr.hip", "// Columns held by the workgroup holding the most",
-                   "// dd systems of at most SMALL_MAX_ROWS")]
+                   "// " + "-" * 48 + " left-looking qd ------")]
 
 
 def _source_part(entry):
@@ -421,11 +421,10 @@ def newton_context(torch, api, steps=None, paths=1024, path_steps=5):
     return out
 
 
-# FP64 flops of one qd 1024 x 1024 factorisation of [A b] (per-panel
-# schedule), counted by rocprofv3 (SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64 x 64
-# lanes, FMA = 2) over all step launches of one mgs_qr call
-# (profiles/mgs_step_qd_1024x1024.md).
-QD1024_FLOPS = 9.632e11
+# FP64 flops of one qd 1024 x 1024 factorisation of [A b] (left-looking
+# launch), counted by rocprofv3 (SQ_INSTS_VALU_{ADD,MUL,FMA,TRANS}_F64 x 64
+# lanes, FMA = 2) over one mgs_qr call (profiles/mgs_left_qd_1024x1024.md).
+QD1024_FLOPS = 7.417e11
 
 
 def qd_large(torch, api, n=1024, reps=2):

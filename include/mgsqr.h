@@ -112,13 +112,16 @@ int mgs_workspace_size(int m, int n, int prec, int op, size_t *bytes);
  * at most 5 columns per compute unit, 8 when m <= 512, e.g. 1024 x 1024
  * with b on 256 compute units; double: m <= 2048, 5 columns per compute
  * unit beyond 1024 rows, 8 below) one cooperative launch with the columns
- * held in registers; otherwise (and in qd) one launch per panel of
+ * held in registers; in qd with m <= 1024 one cooperative launch that takes
+ * a column per workgroup at a time; otherwise one launch per panel of
  * columns.
  * mgs_qr_schedule (below) forces one of them.
  * All schedules apply the projections of Figure 1 in the same order per
- * column; reduction trees differ, and in the single launch the last twelve
- * projections onto each column use r_kj = (a_k^H a_j) / r_kk with a_k
- * before its normalisation (equal to q_k^H a_j in exact arithmetic), so
+ * column; reduction trees differ, and the projections of the one-workgroup
+ * schedule (double, and dd with m <= 32), of the qd launch (b excepted), and
+ * the last twelve onto each column in the resident launch use a_k before its
+ * normalisation, r_kj = (a_k^H a_j) / r_kk and a_j -= ((a_k^H a_j) /
+ * ||a_k||^2) a_k (equal to q_k^H a_j and r_kj q_k in exact arithmetic), so
  * results agree to rounding.
  */
 int mgs_qr(int m, int n, int prec, const double *A, int lda, double *Q, int ldq, double *R, int ldr,
