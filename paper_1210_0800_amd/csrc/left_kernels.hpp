@@ -16,10 +16,13 @@
 // rows by 1 / r_kk.  The right-hand side, whose size has nothing to do with
 // the columns', uses q_k = u_k / r_kk itself.
 //
-// What bounds it: up to one column per workgroup, the chain; beyond, the qd
-// operations of the projections (a column of 1024 rows costs about 8 waves x
-// 2 rows x 1120 operations per projection, and its u_k streams from the
-// shared cache once per projection).
+// What bounds it: up to one column per workgroup, the chain (5.5 us a link at
+// 80 rows, 8.6 at 320, where one launch per column took 16 and 24); beyond,
+// the issue of the qd operations (1024 x 1024: 1.08e10 wave instructions,
+// 17.5 ms of 30.8; one launch per column 71.5) and waiting at the chain.
+// Equal work per compute unit by dealing the second workgroup of each its
+// columns in reverse was slower (42.7 ms against 32.6 a solve), as was a
+// raised wave priority near the chain at 300 columns (5.2 against 4.7 ms).
 //
 // u_k passes through Q with device-scope stores.  Q and the records hold the
 // empty marker until written, so readers poll the data itself; when Q is A

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(256) void proj_r_kernel(int m, int nbp, const doubl
 // only the 128 partial sums per workgroup and panel pass, through `part`:
 // every workgroup reads all of them and adds them in one fixed order, so
 // that one exchange per panel is enough (bounded by it: 2048 x 2048, 781 ->
-// about 130 us per step; one exchange of w and one of r, by two grid barriers,
+// 111 us per step; one exchange of w and one of r, by two grid barriers,
 // before).
 //
 // `part` ([min(3, panels)][G][2 NBP]) holds the empty marker until a value is written
