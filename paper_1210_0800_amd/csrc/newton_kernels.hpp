@@ -118,7 +118,6 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
       }
     }
     C pre = P::load(coef + (live ? (size_t)e * nmon + ml : 0), (size_t)neq * nmon);
-    if (!live) pre = P::czero();
     C suf = P::czero();
     suf.re = P::rone();
 #pragma unroll
@@ -142,7 +141,9 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
         pre = nt_mul<P>(pre, power(vt[t], dt[t]));
       }
     }
-    // f_e: the monomials of an equation, summed over its lanes
+    // f_e: the monomials of an equation, summed over its lanes; a lane without
+    // one adds nothing, whatever the factors that it evaluated came to
+    if (!live) pre = P::czero();
     Acc acc;
     P::acc_set(acc, pre);
     typename P::RAcc re = G::parts(acc)[0], im = G::parts(acc)[1];
