@@ -133,8 +133,9 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
 #pragma unroll
     for (int t = 0; t < NT_MAX_VPM; ++t) {
       if (t < nvpm) {
-        C dv = P::scale(power(vt[t], dt[t] - 1), P::rfrom((double)dt[t]));  // d_t x_t^(d_t - 1)
-        dv = nt_mul<P>(pre, dv);
+        // (the exponent to the coefficient's side: d_t x_t^(d_t - 1) can overflow
+        // where c d_t x_t^(d_t - 1) does not)
+        C dv = nt_mul<P>(P::scale(pre, P::rfrom((double)dt[t])), power(vt[t], dt[t] - 1));
         if (t < nvpm - 1) dv = nt_mul<P>(dv, P::load(ds + lane * nvpm + t, dsp));
         if (dt[t] == 0) dv = P::czero();
         P::store(ds + lane * nvpm + t, dsp, dv);

@@ -1,6 +1,7 @@
 """Polynomial evaluation where one monomial overflows: what does not contain
 it stays finite and agrees with the oracle (the lanes without a monomial add
-nothing).
+nothing), and a derivative whose coefficient brings it back in range is
+finite although its power times its exponent is not.
 
 Bar: that of the other evaluation tests (4096 units of the precision times
 the 64 terms an entry may sum).
@@ -39,3 +40,18 @@ def test_an_overflowing_monomial_stays_alone(L, nmon, value):
         assert np.max(np.abs(diff(F[:, :, 1:], Fo[:, :, 1:]))) <= tol
         assert np.max(np.abs(diff(J[:, :, :, 1:], Jo[:, :, :, 1:]))) <= tol * 3
         assert not np.isfinite(F[0, 0, 0])
+
+
+@pytest.mark.parametrize("L", [1, 2, 4])
+def test_a_derivative_brought_back_by_its_coefficient(L):
+    # c x^16 with x = 2^68, c = 2^-100: 16 x^15 is 2^1024, c 16 x^15 is 2^924
+    coef = np.zeros((L, 2, 1, 1))
+    coef[0, 0] = 2.0 ** -100
+    ds = api.PolySystem(np.zeros((1, 1, 1), int), np.full((1, 1, 1), 16), coef, 1, torch.device("cuda:0"))
+    X = torch.zeros((1, L, 2, 1), dtype=torch.float64, device="cuda")
+    X[0, 0, 0, 0] = 2.0 ** 68
+    J, _ = api.poly_eval(ds, X)
+    torch.cuda.synchronize()
+    want = np.zeros((L, 2, 1, 1))
+    want[0, 0] = 2.0 ** 924
+    assert np.array_equal(J[0].cpu().numpy(), want)
