@@ -308,6 +308,13 @@ def set_jitter(seed):
     _lib.lib().mgs_set_jitter(int(seed) & 0xFFFFFFFF)
 
 
+def set_wait_limit(launch, ticks=-1):
+    """Tests of the time-out paths (mgs_set_wait_limit): the launch-th launch
+    with bounded waits of this thread from here times out after `ticks`
+    wall-clock ticks; launch = 0 takes it back."""
+    _lib.lib().mgs_set_wait_limit(int(launch), int(ticks))
+
+
 class PolySystem:
     """A polynomial system on the card (Section 7: transferred once):
     vars, exps int32 [neq, nmon, nvpm], coef float64 [prec, 2, neq, nmon]

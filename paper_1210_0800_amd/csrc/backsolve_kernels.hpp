@@ -32,12 +32,13 @@ constexpr int TS_ROWS = 32;   // rows of a wave
 constexpr int TS_WAVES = 4;   // waves of a workgroup, at most: one per SIMD
 constexpr int TS_BLOCK = TS_ROWS * TS_WAVES;
 
-// x := empty marker (all planes), info := 0; nothing when *skip != 0.
+// x := empty marker (all planes), info := 0 unless keep; nothing when
+// *skip != 0.
 template <int L>
-__global__ __launch_bounds__(256) void bs_mark_kernel(int n, double *x, int *info, const int *skip) {
+__global__ __launch_bounds__(256) void bs_mark_kernel(int n, double *x, int *info, int keep, const int *skip) {
   if (skip != nullptr && *skip != 0) return;
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i == 0 && info != nullptr) *info = 0;
+  if (i == 0 && info != nullptr && !keep) *info = 0;
   if (i < n) {
 #pragma unroll
     for (int p = 0; p < 2 * L; ++p) x[i + (size_t)p * n] = __longlong_as_double(RES_EMPTY);
@@ -49,12 +50,13 @@ __global__ __launch_bounds__(256) void bs_mark_kernel(int n, double *x, int *inf
 // conj(r_ci), rows below the pivot updated).  Workgroup g takes the blocks
 // g, g + G, ... of blockDim / 2 rows in solve order; marked: x holds the
 // empty marker (needed for more than one block), else the one block clears
-// info itself.
+// info itself.  keep: info stays as it is unless this solve has something to
+// report (a time-out, or a bad diagonal entry where it was 0 or a later one).
 template <class P, bool FWD>
 __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double *R, int ldr, size_t planeR,
                                                              const double *y, size_t planeY, double *x, int *info,
-                                                             const int *skip, int marked, long long spin_ticks,
-                                                             unsigned jitter) {
+                                                             int keep, const int *skip, int marked,
+                                                             long long spin_ticks, unsigned jitter) {
   if (skip != nullptr && *skip != 0) return;
   using C = typename P::C;
   using Rl = typename P::R;
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, part = lane & 1;
   const int nwave = blockDim.x >> 6, rows = nwave * TS_ROWS;
   const int nblk = (n + rows - 1) / rows;
-  if (!marked && tid == 0 && info != nullptr) *info = 0;
+  if (!marked && tid == 0 && info != nullptr && !keep) *info = 0;
   for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
     const int r0 = (FWD ? b : nblk - 1 - b) * rows, r1 = min(r0 + rows, n);  // the block
     __syncthreads();
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double
         const double *src = at(c1 + DIR * s);
         Rl v = P::rzero();
         int avail = 0;  // columns of the chunk that are there
-        PollBound poll;
+        PollBound poll(spin_ticks);
         auto wait_col = [&](int j) __attribute__((always_inline)) {
           while (avail <= j) {
             double *pv = reinterpret_cast<double *>(&v);

@@ -168,35 +168,46 @@ bool dev_info(DevInfo &d);
 // synchronise across waves or workgroups (mgs_set_jitter; 0: none).
 std::atomic<unsigned> g_jitter{0};
 
+// The wall-clock limit of a launch's waits: 2 s.  Tests of the time-out
+// paths (mgs_set_wait_limit) give the calling thread's `t_limit_in`-th launch
+// from here another one.
+thread_local int t_limit_in = 0;
+thread_local long long t_limit_ticks = 0;
+long long wait_limit(long long wclk_khz) {
+  return t_limit_in > 0 && --t_limit_in == 0 ? t_limit_ticks : wclk_khz * 2000;
+}
+
 // R x = y, or R^H x = y with FWD.  Up to 128 rows one workgroup; beyond, one
 // per 128 rows in a cooperative launch, or, where that is refused, one
-// workgroup that takes the blocks in turn.
+// workgroup that takes the blocks in turn.  keep_info: info holds the status
+// of what came before and is not cleared.
 template <class P, bool FWD = false>
 int trsv_launch(int n, const double *R, int ldr, const double *y, double *x, int *info, hipStream_t st,
-                size_t planeR = 0, const int *skip = nullptr, size_t planeY = 0) {
+                bool keep_info = false, size_t planeR = 0, const int *skip = nullptr, size_t planeY = 0) {
   if (planeR == 0) planeR = (size_t)ldr * n;
   if (planeY == 0) planeY = (size_t)n;
   const int waves = ceil_div(n, TS_ROWS) < TS_WAVES ? ceil_div(n, TS_ROWS) : TS_WAVES;
   const int G = ceil_div(n, TS_ROWS * waves);
   DevInfo d;
   const bool have = dev_info(d);
-  long long spin = (have ? d.wclk_khz : 100000) * 2000;  // 2 s
+  long long spin = wait_limit(have ? d.wclk_khz : 100000);
   unsigned jitter = g_jitter.load(std::memory_order_relaxed);
-  int marked = G > 1 ? 1 : 0;
+  int marked = G > 1 ? 1 : 0, keep = keep_info ? 1 : 0;
   auto kern = trsv_kernel<P, FWD>;
   if (marked) {
-    hipLaunchKernelGGL((bs_mark_kernel<P::L>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, x, info, skip);
+    hipLaunchKernelGGL((bs_mark_kernel<P::L>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, x, info, keep,
+                       skip);
     if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
     if (have && d.cus >= G) {
-      void *args[] = {&n, &R, &ldr, &planeR, &y, &planeY, &x, &info, &skip, &marked, &spin, &jitter};
+      void *args[] = {&n, &R, &ldr, &planeR, &y, &planeY, &x, &info, &keep, &skip, &marked, &spin, &jitter};
       if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kern), dim3(G), dim3(64 * waves), args, 0, st) ==
           hipSuccess)
         return MGS_OK;
       (void)hipGetLastError();
     }
   }
-  hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, st, n, R, ldr, planeR, y, planeY, x, info, skip, marked, spin,
-                     jitter);
+  hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, st, n, R, ldr, planeR, y, planeY, x, info, keep, skip, marked,
+                     spin, jitter);
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
 
@@ -256,7 +267,8 @@ int adjoint_launch(int m, int n, const double *A, int lda, const double *b, cons
   auto *part = reinterpret_cast<typename P::Acc *>(r + round256(sizeof(double) * 2 * P::L * (size_t)m) / sizeof(double));
   int rc = trsv_launch<P, true>(n, R, ldr, gx, w, info, st);
   if (rc != MGS_OK) return rc;
-  rc = trsv_launch<P>(n, R, ldr, w, z, info, st);
+  // (info keeps what the first solve had to report)
+  rc = trsv_launch<P>(n, R, ldr, w, z, info, st, true);
   if (rc != MGS_OK) return rc;
   hipLaunchKernelGGL((adj_partial_kernel<P>), dim3(ceil_div(m, ADJ_T), ceil_div(n, ADJ_CH), 2), dim3(ADJ_T), 0, st,
                      m, n, Q, ldq, (size_t)ldq * n, A, lda, (size_t)lda * n, b, x, w, part);
@@ -383,7 +395,7 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   hipLaunchKernelGGL(refine_check_kernel, dim3(1), dim3(64), 0, st, info, w.ctl);
   const int *skip = &w.ctl->status;
   // x0: R x0 = y (the last column of R64)
-  rc = trsv_launch<PrecD>(n, w.R64, n, w.R64 + (size_t)n * n, w.d64, nullptr, st, planeR, skip, planeR);
+  rc = trsv_launch<PrecD>(n, w.R64, n, w.R64 + (size_t)n * n, w.d64, nullptr, st, false, planeR, skip, planeR);
   if (rc != MGS_OK) return rc;
   hipLaunchKernelGGL((set_x_kernel<P>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, w.d64, x);
   const int nchunk = ceil_div(n, NBP);
@@ -399,7 +411,6 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   bool fused = m <= PR_MAX_ROWS && (long long)max_iter * pr_wgs < (1LL << 31) && dev_info(d) && d.cus >= pr_wgs &&
                (pr_wgs == 1 || sizeof(double) * 2 * NBP * (size_t)(nchunk < 3 ? nchunk : 3) * pr_wgs <=
                                    sizeof(PrecQD::Acc) * (size_t)nchunk * m);
-  const long long spin = fused ? (long long)d.wclk_khz * 2000 : 0;  // 2 s
   const unsigned jitter = g_jitter.load(std::memory_order_relaxed);
   for (int it = 1; it <= max_iter; ++it) {
     hipLaunchKernelGGL((residual_partial_kernel<P::L>), dim3(ceil_div(m, 256), nchunk), dim3(256), 0, st, m, n, NBP,
@@ -414,7 +425,7 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
       double *wa = w.y64, *pa = static_cast<double *>(w.partial);
       RefineCtl *ctl = w.ctl;
       int mm = m, nn = n;
-      long long sp = spin;
+      long long sp = wait_limit(d.wclk_khz);
       unsigned jt = jitter;
       void *args[] = {&mm, &nn, &Qa, &pq, &ra, &wa, &pw, &pa, &ctl, &info, &base, &sp, &jt};
       if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(proj_replay_kernel), dim3(pr_wgs), dim3(256), args,
@@ -433,7 +444,7 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
                            (size_t)n, w.r64, w.ctl);
       }
     }
-    rc = trsv_launch<PrecD>(n, w.R64, n, w.y64, w.d64, nullptr, st, planeR, skip);
+    rc = trsv_launch<PrecD>(n, w.R64, n, w.y64, w.d64, nullptr, st, false, planeR, skip);
     if (rc != MGS_OK) return rc;
     hipLaunchKernelGGL((refine_update_kernel<P>), dim3(1), dim3(256), 0, st, n, w.d64, x, tol, it, w.ctl);
     if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
@@ -584,7 +595,7 @@ int res_launch(const StepArgs &s, void *sync, double *u, hipStream_t st) {
   a.G = pl.G;
   a.xcd_group = pl.G % 8 == 0 ? pl.G / 8 : 0;
   a.defer = 12;
-  a.spin_ticks = d.wclk_khz * 2000;  // 2 s
+  a.spin_ticks = wait_limit(d.wclk_khz);
   a.kbase = s.kbase;
   a.init_info = s.init_info;
   a.jitter = g_jitter.load(std::memory_order_relaxed);
@@ -660,7 +671,7 @@ int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
   a.rec = static_cast<double *>(work);
   a.sync = reinterpret_cast<unsigned int *>(static_cast<char *>(work) + qr_w_bytes(s.m, P::L));
   a.marked = s.Q != s.A;
-  a.spin_ticks = d.wclk_khz * 2000;  // 2 s
+  a.spin_ticks = wait_limit(d.wclk_khz);
   a.jitter = g_jitter.load(std::memory_order_relaxed);
   // One column per workgroup (up to an eighth more: a workgroup's first
   // column is soon done): one row per thread, the shortest link (n = 80
@@ -849,7 +860,7 @@ int poly_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *var
 template <class P>
 int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *vars, const int *exps,
                   const double *coef, double *x, int iters, double *dnorm, const NewtonWork &w, int *info,
-                  long long spin, hipStream_t st) {
+                  long long wclk_khz, hipStream_t st) {
   for (int k = 0; k < iters; ++k) {
     const int pe = poly_launch<P>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, w.A, w.b, true, st);
     if (pe != MGS_OK) return pe;
@@ -884,7 +895,7 @@ int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *v
     a.x = w.d;
     a.rho = nullptr;
     a.info = info;
-    a.spin_ticks = spin;
+    a.spin_ticks = wait_limit(wclk_khz);
     a.jitter = g_jitter.load(std::memory_order_relaxed);
     const int rc = batched_dispatch(P::L, a, st);
     if (rc != MGS_OK) return rc;
@@ -901,6 +912,10 @@ extern "C" {
 
 void mgs_set_jitter(unsigned seed) { g_jitter.store(seed, std::memory_order_relaxed); }
 
+void mgs_set_wait_limit(int launch, long long ticks) {
+  t_limit_in = launch;
+  t_limit_ticks = ticks;
+}
 
 #ifdef MGS_TRACE
 // Diagnostic builds only (not declared in the public header).
@@ -997,7 +1012,7 @@ int mgs_qr_schedule(int m, int n, int prec, const double *A, int lda, double *Q,
         ba.x = nullptr;
         ba.rho = a.rho;
         ba.info = info;
-        ba.spin_ticks = d.wclk_khz * 2000;  // 2 s
+        ba.spin_ticks = wait_limit(d.wclk_khz);
         ba.jitter = g_jitter.load(std::memory_order_relaxed);
         rc = batched_dispatch(prec, ba, st);
       }
@@ -1166,13 +1181,15 @@ int mgs_newton_batched(int batch, int neq, int nvar, int nmon, int nvpm, int pre
   if (work_bytes < w.bytes) return MGS_ERR_WORKSPACE;
   DevInfo d;
   if (!dev_info(d)) return MGS_ERR_LAUNCH;
-  const long long spin = d.wclk_khz * 2000;  // 2 s
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (prec == 1)
-    return newton_launch<PrecD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, iters, dnorm, w, info, spin, st);
+    return newton_launch<PrecD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, iters, dnorm, w, info, d.wclk_khz,
+                              st);
   if (prec == 2)
-    return newton_launch<PrecDD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, iters, dnorm, w, info, spin, st);
-  return newton_launch<PrecQD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, iters, dnorm, w, info, spin, st);
+    return newton_launch<PrecDD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, iters, dnorm, w, info, d.wclk_khz,
+                               st);
+  return newton_launch<PrecQD>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, iters, dnorm, w, info, d.wclk_khz,
+                             st);
 }
 
 int mgs_lstsq_batched(int batch, int m, int n, int prec, const double *A, int lda, const double *b, double *Q,
@@ -1209,7 +1226,7 @@ int mgs_lstsq_batched(int batch, int m, int n, int prec, const double *A, int ld
   a.x = b ? x : nullptr;
   a.rho = b ? rho : nullptr;
   a.info = info;
-  a.spin_ticks = d.wclk_khz * 2000;  // 2 s
+  a.spin_ticks = wait_limit(d.wclk_khz);
   a.jitter = g_jitter.load(std::memory_order_relaxed);
   return batched_dispatch(prec, a, reinterpret_cast<hipStream_t>(stream));
 }

@@ -224,10 +224,12 @@ __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
 // The bound of a polling wait: the wall clock (and, in res_give_up, the abort
 // flag, a device-scope load) is looked at on every 16th turn only, so that a
 // turn is one read of what is waited for and the wait ends one read after
-// the data is there, not two.
+// the data is there, not two.  A negative limit (tests of the time-out paths)
+// ends the wait on its first turn.
 struct PollBound {
   long long t0 = -1;
-  int turns = 0;
+  int turns;
+  __device__ __forceinline__ explicit PollBound(long long limit) : turns(limit < 0 ? 15 : 0) {}
   __device__ __forceinline__ bool due() { return (++turns & 15) == 0; }
   __device__ __forceinline__ bool late(long long limit) {
     const long long now = wall_clock64();
@@ -259,7 +261,7 @@ __device__ __forceinline__ bool res_give_up(const Args &a, PollBound &poll) {
 template <class Args>
 __device__ __forceinline__ bool res_wait(const Args &a, int k, int wave, int &seen) {
   if (seen > k) return true;
-  PollBound poll;
+  PollBound poll(a.spin_ticks);
   unsigned int *cnt = a.sync + 16 * wave;
   while (true) {
     const int v = __builtin_amdgcn_readfirstlane(
@@ -717,7 +719,7 @@ struct Resident {
   // Returns false on abort or time-out.
   __device__ __forceinline__ bool load_col(const double *base, size_t ld, size_t plane, int k, C (&q)[RR]) {
     const double *src = base + (size_t)k * ld;
-    PollBound poll;
+    PollBound poll(a.spin_ticks);
     while (true) {
       bool miss = false;
 #pragma unroll
@@ -761,7 +763,7 @@ struct Resident {
     bool ok = true;
     if (tid == 0) {
       __hip_atomic_fetch_add(a.sync + RES_GRID, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      PollBound poll;
+      PollBound poll(a.spin_ticks);
       while (__hip_atomic_load(a.sync + RES_GRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned int)a.G) {
         if (res_give_up(a, poll)) {
           ok = false;

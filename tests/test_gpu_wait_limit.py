@@ -1,0 +1,44 @@
+"""A triangular solve that times out inside a longer call must show in that
+call's info, whatever comes after it: in the adjoint, whose second solve
+shares the status word.
+
+The time-out is forced by a tiny limit on one launch's own bounded waits, so
+every kernel ends normally; a call without it must then succeed again.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1210_0800_amd import api, inputs  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TIMEOUT = -9
+
+
+def T(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def limited(launch, run):
+    """run() with the launch-th waiting launch timed out, then without."""
+    torch.cuda.synchronize()
+    api.set_wait_limit(launch)
+    try:
+        out = run()
+        torch.cuda.synchronize()
+    finally:
+        api.set_wait_limit(0)
+    return out, run()
+
+
+@pytest.mark.parametrize("launch", [1, 2])
+def test_adjoint(launch):
+    p = inputs.random_problem(2, 320, 300, seed=1, config=94)
+    A, b = T(p["A"]), T(p["b"])
+    f = api.lstsq(A, b)
+    gx = f["x"].clone()
+    cut, whole = limited(launch, lambda: api.ls_adjoint(A, b, f["Q"], f["R"], f["x"], gx))
+    torch.cuda.synchronize()
+    assert int(cut[2].item()) == TIMEOUT
+    assert int(whole[2].item()) == 0 and bool(torch.isfinite(whole[0]).all())
