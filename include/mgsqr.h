@@ -332,8 +332,7 @@ int mgs_poly_eval(int batch, int neq, int nvar, int nmon, int nvpm, int prec, co
 /*
  * mgs_newton_workspace_size -- bytes of device workspace mgs_newton_batched
  * needs (J, -f, R and the correction of every point; for a single point in
- * qd also Q^H b, a status word and the workspace of mgs_qr's single-system
- * schedule).
+ * qd also Q^H b and the workspace of mgs_qr).
  */
 int mgs_newton_workspace_size(int batch, int neq, int nvar, int prec, size_t *bytes);
 
@@ -353,9 +352,9 @@ int mgs_newton_workspace_size(int batch, int neq, int nvar, int prec, size_t *by
  *         NaN when that step's factorisation failed.
  *   work  mgs_newton_workspace_size(batch, neq, nvar, prec) bytes.
  *   info  [out] batch device ints: status of each point's last
- *         factorisation (0, k > 0 for a zero or non-finite norm of column
- *         k of J, MGS_INFO_SYNC_TIMEOUT); a failed point keeps its x for
- *         that step.
+ *         factorisation and solve (0, k > 0 for a zero or non-finite norm of
+ *         column k of J, MGS_INFO_SYNC_TIMEOUT); a failed point keeps its
+ *         x for that step.
  * batch == 0 or iters == 0: nothing to do, pointers not examined.
  */
 int mgs_newton_batched(int batch, int neq, int nvar, int nmon, int nvpm, int prec, const int *vars, const int *exps,

@@ -782,10 +782,9 @@ void *scratch_address() {
 
 // Newton: J (batch systems of neq x nvar), b (batch x neq), R (batch x
 // nvar x nvar), d (batch x nvar), each in the working precision; for one
-// point in qd also y (nvar), an int and the workspace of mgs_qr.
+// point in qd also y (nvar) and the workspace of mgs_qr.
 struct NewtonWork {
   double *A, *b, *R, *d, *y;
-  int *info2;
   void *qrw;
   size_t qrw_bytes;
   size_t bytes;
@@ -804,12 +803,10 @@ NewtonWork newton_layout(int batch, int neq, int nvar, int prec, void *base) {
   w.R = take(B * NP * nvar * nvar);
   w.d = take(B * NP * nvar);
   w.y = nullptr;
-  w.info2 = nullptr;
   w.qrw = nullptr;
   w.qrw_bytes = 0;
   if (batch == 1 && prec == 4) {
     w.y = take(NP * nvar);
-    w.info2 = reinterpret_cast<int *>(take(1));
     w.qrw_bytes = qr_work_bytes(neq, nvar, prec);
     w.qrw = take((w.qrw_bytes + sizeof(double) - 1) / sizeof(double));
   }
@@ -865,14 +862,13 @@ int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *v
     const int pe = poly_launch<P>(batch, neq, nvar, nmon, nvpm, vars, exps, coef, x, w.A, w.b, true, st);
     if (pe != MGS_OK) return pe;
     if (w.qrw != nullptr) {
-      // One point in qd: mgs_qr's single-system schedule (one column per
-      // launch), quicker than a batch of one, then the back substitution
-      // (its own status word: a zero pivot is already reported by the
-      // factorisation).
+      // One point in qd: mgs_qr's left-looking launch, quicker than a batch of
+      // one, then the back substitution, which adds a time-out to the
+      // factorisation's status (a zero pivot is already there).
       int rc = mgs_qr_schedule(neq, nvar, P::L, w.A, neq, w.A, neq, w.R, nvar, w.b, w.y, nullptr, w.qrw, w.qrw_bytes,
                                info, MGS_SCHED_AUTO, reinterpret_cast<mgs_stream_t>(st));
       if (rc != MGS_OK) return rc;
-      rc = trsv_launch<P>(nvar, w.R, nvar, w.y, w.d, w.info2, st);
+      rc = trsv_launch<P>(nvar, w.R, nvar, w.y, w.d, info, st, true);
       if (rc != MGS_OK) return rc;
       hipLaunchKernelGGL((newton_update_kernel<P>), dim3(batch), dim3(64), 0, st, nvar, x, w.d, info,
                          dnorm != nullptr ? dnorm + (size_t)k * batch : nullptr);

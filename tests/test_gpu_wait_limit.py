@@ -1,6 +1,7 @@
 """A triangular solve that times out inside a longer call must show in that
-call's info, whatever comes after it: in the adjoint, whose second solve
-shares the status word.
+call's info, whatever comes after it: in the adjoint (whose second solve
+shares the status word), and in the Newton step of one qd point (whose x must
+then stay as it is).
 
 The time-out is forced by a tiny limit on one launch's own bounded waits, so
 every kernel ends normally; a call without it must then succeed again.
@@ -42,3 +43,22 @@ def test_adjoint(launch):
     torch.cuda.synchronize()
     assert int(cut[2].item()) == TIMEOUT
     assert int(whole[2].item()) == 0 and bool(torch.isfinite(whole[0]).all())
+
+
+def test_newton_step_of_one_qd_point():
+    s = inputs.polysys(neq=40, nvar=40, nmon=16, nvpm=3, maxdeg=3, L=4, system=1)
+    ds = api.PolySystem(s["vars"], s["exps"], s["coef"], 40, torch.device("cuda:0"))
+    X = T(np.stack([inputs.near_root(s, 1e-3, L=4, system=1)]))
+
+    def step():
+        return api.newton_batched(ds, X.clone(), 1)
+
+    cut, whole = limited(2, step)  # 1: the factorisation, 2: the back substitution
+    torch.cuda.synchronize()
+    assert int(cut["info"].item()) == TIMEOUT
+    assert torch.equal(cut["x"], X) and bool(torch.isnan(cut["dnorm"]).all())
+    assert int(whole["info"].item()) == 0 and bool(torch.isfinite(whole["x"]).all())
+    # with two steps, the time-out of the first one is not the last status
+    again, _ = limited(2, lambda: api.newton_batched(ds, X.clone(), 2))
+    torch.cuda.synchronize()
+    assert int(again["info"].item()) == 0 and torch.equal(again["x"], whole["x"])
