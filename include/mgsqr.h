@@ -232,7 +232,8 @@ int ls_adjoint(int m, int n, int prec, const double *A, int lda, const double *b
  *   info [device int]: 0 converged; k > 0 zero or non-finite norm at column
  *   k of the FP64 factorisation; -1 stagnated above sqrt(tol); -2 max_iter
  *   reached first; MGS_INFO_SYNC_TIMEOUT when a bounded wait between
- *   workgroups (the FP64 panels' single launch, the projections) ran out.
+ *   workgroups or waves (the FP64 panels' single launch, the projections,
+ *   the triangular solves) ran out.
  * Convergence needs kappa(A) * 2^-53 well below 1 and a consistent or
  * nearly consistent system.
  */

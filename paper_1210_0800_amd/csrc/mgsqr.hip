@@ -395,7 +395,7 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   hipLaunchKernelGGL(refine_check_kernel, dim3(1), dim3(64), 0, st, info, w.ctl);
   const int *skip = &w.ctl->status;
   // x0: R x0 = y (the last column of R64)
-  rc = trsv_launch<PrecD>(n, w.R64, n, w.R64 + (size_t)n * n, w.d64, nullptr, st, false, planeR, skip, planeR);
+  rc = trsv_launch<PrecD>(n, w.R64, n, w.R64 + (size_t)n * n, w.d64, info, st, true, planeR, skip, planeR);
   if (rc != MGS_OK) return rc;
   hipLaunchKernelGGL((set_x_kernel<P>), dim3(ceil_div(n, 256)), dim3(256), 0, st, n, w.d64, x);
   const int nchunk = ceil_div(n, NBP);
@@ -444,9 +444,10 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
                            (size_t)n, w.r64, w.ctl);
       }
     }
-    rc = trsv_launch<PrecD>(n, w.R64, n, w.y64, w.d64, nullptr, st, false, planeR, skip);
+    rc = trsv_launch<PrecD>(n, w.R64, n, w.y64, w.d64, info, st, true, planeR, skip);
     if (rc != MGS_OK) return rc;
-    hipLaunchKernelGGL((refine_update_kernel<P>), dim3(1), dim3(256), 0, st, n, w.d64, x, tol, it, w.ctl);
+    hipLaunchKernelGGL((refine_update_kernel<P>), dim3(1), dim3(256), 0, st, n, w.d64, x, tol, it, w.ctl,
+                       info);
     if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
   }
   hipLaunchKernelGGL(refine_finish_kernel, dim3(1), dim3(64), 0, st, w.ctl, iters, err_est, info);

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void zgemm_update_kernel(int m, int N, int nbp
 
 // ------------------------------------------------------- refinement ------
 struct RefineCtl {
-  int status;  // 0 running, 1 converged, 2 stagnated, 3 factorisation failed or a grid wait timed out
+  int status;  // 0 running, 1 converged, 2 stagnated, 3 factorisation failed or a wait timed out
   int iters;
   double dprev;
   double err_est;
@@ -569,11 +569,16 @@ __global__ __launch_bounds__(256) void set_x_kernel(int n, const double *x64, do
 }
 
 // x += d (d in FP64), with the stopping test on ||d|| and ||x||: stop when
-// ||d|| <= tol ||x|| (converged) or ||d|| > ||d_prev|| / 2 (stalled).  One block.
+// ||d|| <= tol ||x|| (converged) or ||d|| > ||d_prev|| / 2 (stalled), and
+// nothing more once info is set (a triangular solve timed out).  One block.
 template <class P>
 __global__ __launch_bounds__(256) void refine_update_kernel(int n, const double *d64, double *x, double tol,
-                                                             int iter, RefineCtl *ctl) {
+                                                             int iter, RefineCtl *ctl, const int *info) {
   if (ctl->status != 0) return;
+  if (*info != 0) {
+    if (threadIdx.x == 0) ctl->status = 3;
+    return;
+  }
   __shared__ double red[2][4];
   __shared__ int stag;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

@@ -1,7 +1,7 @@
 """A triangular solve that times out inside a longer call must show in that
 call's info, whatever comes after it: in the adjoint (whose second solve
-shares the status word), and in the Newton step of one qd point (whose x must
-then stay as it is).
+shares the status word), in the Newton step of one qd point (whose x must
+then stay as it is) and in the refinement (first solution and correction).
 
 The time-out is forced by a tiny limit on one launch's own bounded waits, so
 every kernel ends normally; a call without it must then succeed again.
@@ -62,3 +62,16 @@ def test_newton_step_of_one_qd_point():
     again, _ = limited(2, lambda: api.newton_batched(ds, X.clone(), 2))
     torch.cuda.synchronize()
     assert int(again["info"].item()) == 0 and torch.equal(again["x"], whole["x"])
+
+
+@pytest.mark.parametrize("prec", [2, 4])
+@pytest.mark.parametrize("launch,max_iter", [(6, 0), (6, 3), (8, 3)])
+def test_refinement(prec, launch, max_iter):
+    # 1..5: the panels, 6: the first solution, 7: the projections of the
+    # residual, 8: the first correction's solve
+    p = inputs.random_problem(prec, 300, 300, seed=2, config=94)
+    A, b = T(p["A"]), T(p["b"])
+    cut, whole = limited(launch, lambda: api.refine_lstsq(A, b, max_iter=max_iter))
+    torch.cuda.synchronize()
+    assert int(cut["info"].item()) == TIMEOUT
+    assert int(whole["info"].item()) != TIMEOUT and bool(torch.isfinite(whole["x"]).all())
