@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double
         const double *src = at(c1 + DIR * s);
         Rl v = P::rzero();
         int avail = 0;  // columns of the chunk that are there
-        PollBound poll(spin_ticks);
+        PollBound poll;
         auto wait_col = [&](int j) __attribute__((always_inline)) {
           while (avail <= j) {
             double *pv = reinterpret_cast<double *>(&v);

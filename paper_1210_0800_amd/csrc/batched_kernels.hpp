@@ -224,7 +224,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   bool alive = true;
   // Bounded wait for `ready()`; false (and the status) on a time-out.
   auto wait_for = [&](auto ready) __attribute__((always_inline)) {
-    PollBound poll(a.spin_ticks);
+    PollBound poll;
     while (!ready()) {
       if (poll.due() && poll.late(a.spin_ticks)) {
         if (lane == 0) atomicExch(&status, MGS_INFO_SYNC_TIMEOUT);

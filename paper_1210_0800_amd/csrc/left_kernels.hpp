@@ -137,7 +137,7 @@ mgs_left_kernel(LeftArgs a) {
   };
   auto wait_record = [&](int k, int which, Rl &v) __attribute__((always_inline)) {
     const double *pv = reinterpret_cast<const double *>(&v);
-    PollBound poll(a.spin_ticks);
+    PollBound poll;
     while (true) {
       bool miss = false;
 #pragma unroll
@@ -207,7 +207,7 @@ mgs_left_kernel(LeftArgs a) {
       res_jitter(a.jitter, step++);
       if (!a.marked && !res_wait(a, k, wave, seen)) return;
       const double *src = a.Q + (size_t)k * a.ldq;
-      PollBound poll(a.spin_ticks);
+      PollBound poll;
       while (true) {
         bool miss = false;
 #pragma unroll

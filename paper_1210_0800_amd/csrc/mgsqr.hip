@@ -168,13 +168,19 @@ bool dev_info(DevInfo &d);
 // synchronise across waves or workgroups (mgs_set_jitter; 0: none).
 std::atomic<unsigned> g_jitter{0};
 
-// The wall-clock limit of a launch's waits: 2 s.  Tests of the time-out
-// paths (mgs_set_wait_limit) give the calling thread's `t_limit_in`-th launch
-// from here another one.
+// What a launch with bounded waits is given: their wall-clock limit (2 s) and
+// the jitter's seed.  Tests of the time-out paths (mgs_set_wait_limit) give
+// the calling thread's `t_limit_in`-th launch from here another limit and
+// long pauses.
 thread_local int t_limit_in = 0;
 thread_local long long t_limit_ticks = 0;
-long long wait_limit(long long wclk_khz) {
-  return t_limit_in > 0 && --t_limit_in == 0 ? t_limit_ticks : wclk_khz * 2000;
+struct WaitArgs {
+  long long ticks;
+  unsigned jitter;
+};
+WaitArgs wait_args(long long wclk_khz) {
+  if (t_limit_in > 0 && --t_limit_in == 0) return {t_limit_ticks, RES_STALL};
+  return {wclk_khz * 2000, g_jitter.load(std::memory_order_relaxed)};
 }
 
 // R x = y, or R^H x = y with FWD.  Up to 128 rows one workgroup; beyond, one
@@ -190,8 +196,7 @@ int trsv_launch(int n, const double *R, int ldr, const double *y, double *x, int
   const int G = ceil_div(n, TS_ROWS * waves);
   DevInfo d;
   const bool have = dev_info(d);
-  long long spin = wait_limit(have ? d.wclk_khz : 100000);
-  unsigned jitter = g_jitter.load(std::memory_order_relaxed);
+  WaitArgs wait = wait_args(have ? d.wclk_khz : 100000);
   int marked = G > 1 ? 1 : 0, keep = keep_info ? 1 : 0;
   auto kern = trsv_kernel<P, FWD>;
   if (marked) {
@@ -199,7 +204,7 @@ int trsv_launch(int n, const double *R, int ldr, const double *y, double *x, int
                        skip);
     if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
     if (have && d.cus >= G) {
-      void *args[] = {&n, &R, &ldr, &planeR, &y, &planeY, &x, &info, &keep, &skip, &marked, &spin, &jitter};
+      void *args[] = {&n, &R, &ldr, &planeR, &y, &planeY, &x, &info, &keep, &skip, &marked, &wait.ticks, &wait.jitter};
       if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kern), dim3(G), dim3(64 * waves), args, 0, st) ==
           hipSuccess)
         return MGS_OK;
@@ -207,7 +212,7 @@ int trsv_launch(int n, const double *R, int ldr, const double *y, double *x, int
     }
   }
   hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, st, n, R, ldr, planeR, y, planeY, x, info, keep, skip, marked,
-                     spin, jitter);
+                     wait.ticks, wait.jitter);
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
 
@@ -411,7 +416,6 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   bool fused = m <= PR_MAX_ROWS && (long long)max_iter * pr_wgs < (1LL << 31) && dev_info(d) && d.cus >= pr_wgs &&
                (pr_wgs == 1 || sizeof(double) * 2 * NBP * (size_t)(nchunk < 3 ? nchunk : 3) * pr_wgs <=
                                    sizeof(PrecQD::Acc) * (size_t)nchunk * m);
-  const unsigned jitter = g_jitter.load(std::memory_order_relaxed);
   for (int it = 1; it <= max_iter; ++it) {
     hipLaunchKernelGGL((residual_partial_kernel<P::L>), dim3(ceil_div(m, 256), nchunk), dim3(256), 0, st, m, n, NBP,
                        A, lda, b, x, static_cast<PrecQD::Acc *>(w.partial), w.ctl);
@@ -425,9 +429,8 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
       double *wa = w.y64, *pa = static_cast<double *>(w.partial);
       RefineCtl *ctl = w.ctl;
       int mm = m, nn = n;
-      long long sp = wait_limit(d.wclk_khz);
-      unsigned jt = jitter;
-      void *args[] = {&mm, &nn, &Qa, &pq, &ra, &wa, &pw, &pa, &ctl, &info, &base, &sp, &jt};
+      WaitArgs wait = wait_args(d.wclk_khz);
+      void *args[] = {&mm, &nn, &Qa, &pq, &ra, &wa, &pw, &pa, &ctl, &info, &base, &wait.ticks, &wait.jitter};
       if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(proj_replay_kernel), dim3(pr_wgs), dim3(256), args,
                                      0, st) != hipSuccess) {
         (void)hipGetLastError();
@@ -596,10 +599,11 @@ int res_launch(const StepArgs &s, void *sync, double *u, hipStream_t st) {
   a.G = pl.G;
   a.xcd_group = pl.G % 8 == 0 ? pl.G / 8 : 0;
   a.defer = 12;
-  a.spin_ticks = wait_limit(d.wclk_khz);
+  const WaitArgs wait = wait_args(d.wclk_khz);
+  a.spin_ticks = wait.ticks;
+  a.jitter = wait.jitter;
   a.kbase = s.kbase;
   a.init_info = s.init_info;
-  a.jitter = g_jitter.load(std::memory_order_relaxed);
 #ifdef MGS_TRACE
   a.trace = g_trace;
 #endif
@@ -672,8 +676,9 @@ int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
   a.rec = static_cast<double *>(work);
   a.sync = reinterpret_cast<unsigned int *>(static_cast<char *>(work) + qr_w_bytes(s.m, P::L));
   a.marked = s.Q != s.A;
-  a.spin_ticks = wait_limit(d.wclk_khz);
-  a.jitter = g_jitter.load(std::memory_order_relaxed);
+  const WaitArgs wait = wait_args(d.wclk_khz);
+  a.spin_ticks = wait.ticks;
+  a.jitter = wait.jitter;
   // One column per workgroup (up to an eighth more: a workgroup's first
   // column is soon done): one row per thread, the shortest link (n = 80
   // 5.9 us a column, 320 x 256 8.3 us against 9.4 with 2 rows per thread on
@@ -892,8 +897,9 @@ int newton_launch(int batch, int neq, int nvar, int nmon, int nvpm, const int *v
     a.x = w.d;
     a.rho = nullptr;
     a.info = info;
-    a.spin_ticks = wait_limit(wclk_khz);
-    a.jitter = g_jitter.load(std::memory_order_relaxed);
+    const WaitArgs wait = wait_args(wclk_khz);
+    a.spin_ticks = wait.ticks;
+    a.jitter = wait.jitter;
     const int rc = batched_dispatch(P::L, a, st);
     if (rc != MGS_OK) return rc;
     hipLaunchKernelGGL((newton_update_kernel<P>), dim3(batch), dim3(64), 0, st, nvar, x, w.d, info,
@@ -1009,8 +1015,9 @@ int mgs_qr_schedule(int m, int n, int prec, const double *A, int lda, double *Q,
         ba.x = nullptr;
         ba.rho = a.rho;
         ba.info = info;
-        ba.spin_ticks = wait_limit(d.wclk_khz);
-        ba.jitter = g_jitter.load(std::memory_order_relaxed);
+        const WaitArgs wait = wait_args(d.wclk_khz);
+        ba.spin_ticks = wait.ticks;
+        ba.jitter = wait.jitter;
         rc = batched_dispatch(prec, ba, st);
       }
     }
@@ -1223,8 +1230,9 @@ int mgs_lstsq_batched(int batch, int m, int n, int prec, const double *A, int ld
   a.x = b ? x : nullptr;
   a.rho = b ? rho : nullptr;
   a.info = info;
-  a.spin_ticks = wait_limit(d.wclk_khz);
-  a.jitter = g_jitter.load(std::memory_order_relaxed);
+  const WaitArgs wait = wait_args(d.wclk_khz);
+  a.spin_ticks = wait.ticks;
+  a.jitter = wait.jitter;
   return batched_dispatch(prec, a, reinterpret_cast<hipStream_t>(stream));
 }
 

@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void proj_replay_kernel(int m, int n, const do
   const double e = __longlong_as_double(RES_EMPTY);
   if (tid == 0) bad = 0;
   if (tid < 2 * NBP) ws[1][tid] = 0.0;
-  PollBound poll(spin_ticks);
+  PollBound poll;
   auto give_up = [&]() __attribute__((always_inline)) {
     if (!poll.due()) return false;
     if (__hip_atomic_load(&ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && !poll.late(spin_ticks))

@@ -210,7 +210,9 @@ __device__ __forceinline__ void info_first_bad(int *info, int v) {
 // the whole wave, drawn from (seed, workgroup, wave, step) by an integer
 // hash.  Results must not change: every reduction order is fixed, so a
 // difference under jitter is a race.  seed 0 (the default) costs one
-// scalar compare.
+// scalar compare.  RES_STALL (tests of the time-out paths): up to 100 us, so
+// that waits on this wave last long.
+constexpr unsigned RES_STALL = 0x57A11ED0u;
 __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
   if (seed == 0) return;
   unsigned h = seed * 0x9E3779B1u ^ blockIdx.x * 0x85EBCA77u ^ (threadIdx.x >> 6) * 0xC2B2AE3Du ^ step * 0x27D4EB2Fu;
@@ -218,18 +220,17 @@ __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
   h *= 0x2C1B3C6Du;
   h ^= h >> 12;
   const int n = __builtin_amdgcn_readfirstlane((int)(h & 15u));
-  for (int i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(1);
+  const int pauses = seed == RES_STALL ? n << 8 : n;
+  for (int i = 0; i < pauses; ++i) __builtin_amdgcn_s_sleep(1);
 }
 
 // The bound of a polling wait: the wall clock (and, in res_give_up, the abort
 // flag, a device-scope load) is looked at on every 16th turn only, so that a
 // turn is one read of what is waited for and the wait ends one read after
-// the data is there, not two.  A negative limit (tests of the time-out paths)
-// ends the wait on its first turn.
+// the data is there, not two.
 struct PollBound {
   long long t0 = -1;
-  int turns;
-  __device__ __forceinline__ explicit PollBound(long long limit) : turns(limit < 0 ? 15 : 0) {}
+  int turns = 0;
   __device__ __forceinline__ bool due() { return (++turns & 15) == 0; }
   __device__ __forceinline__ bool late(long long limit) {
     const long long now = wall_clock64();
@@ -261,7 +262,7 @@ __device__ __forceinline__ bool res_give_up(const Args &a, PollBound &poll) {
 template <class Args>
 __device__ __forceinline__ bool res_wait(const Args &a, int k, int wave, int &seen) {
   if (seen > k) return true;
-  PollBound poll(a.spin_ticks);
+  PollBound poll;
   unsigned int *cnt = a.sync + 16 * wave;
   while (true) {
     const int v = __builtin_amdgcn_readfirstlane(
@@ -719,7 +720,7 @@ struct Resident {
   // Returns false on abort or time-out.
   __device__ __forceinline__ bool load_col(const double *base, size_t ld, size_t plane, int k, C (&q)[RR]) {
     const double *src = base + (size_t)k * ld;
-    PollBound poll(a.spin_ticks);
+    PollBound poll;
     while (true) {
       bool miss = false;
 #pragma unroll
@@ -763,7 +764,7 @@ struct Resident {
     bool ok = true;
     if (tid == 0) {
       __hip_atomic_fetch_add(a.sync + RES_GRID, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      PollBound poll(a.spin_ticks);
+      PollBound poll;
       while (__hip_atomic_load(a.sync + RES_GRID, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned int)a.G) {
         if (res_give_up(a, poll)) {
           ok = false;
