@@ -378,9 +378,9 @@ void mgs_set_jitter(unsigned seed);
  * mgs_set_wait_limit -- tests of the time-out paths (diagnostics, not for
  * production use): of the launches with bounded waits that the calling
  * thread makes from here, the launch-th (1: the next) gets a limit of
- * `ticks` wall-clock ticks in place of 2 s and pauses of up to 100 us per
- * step, so that its waits end with MGS_INFO_SYNC_TIMEOUT (ticks < 0: on the
- * first look at the clock).  launch = 0 takes it back.  Other threads are not
+ * `ticks` wall-clock ticks in place of 2 s and, if it is a triangular solve,
+ * pauses of about 100 us per step, so that its waits end with
+ * MGS_INFO_SYNC_TIMEOUT (ticks < 0: on the first look at the clock).  launch = 0 takes it back.  Other threads are not
  * affected.
  */
 void mgs_set_wait_limit(int launch, long long ticks);

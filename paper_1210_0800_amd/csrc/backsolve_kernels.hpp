@@ -32,6 +32,16 @@ constexpr int TS_ROWS = 32;   // rows of a wave
 constexpr int TS_WAVES = 4;   // waves of a workgroup, at most: one per SIMD
 constexpr int TS_BLOCK = TS_ROWS * TS_WAVES;
 
+// Race checks; with TS_STALL (tests of the time-out paths) about 100 us a step,
+// so that the waits on a wave last longer than 16 turns.
+constexpr unsigned TS_STALL = 0x57A11ED0u;
+__device__ __forceinline__ void trsv_pause(unsigned seed, unsigned step) {
+  if (seed == 0) return;
+  res_jitter(seed, step);
+  if (seed == TS_STALL)
+    for (int i = 0; i < 32; ++i) __builtin_amdgcn_s_sleep(127);
+}
+
 // x := empty marker (all planes), info := 0 unless keep; nothing when
 // *skip != 0.
 template <int L>
@@ -58,7 +68,6 @@ __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double
                                                              int keep, const int *skip, int marked,
                                                              long long spin_ticks, unsigned jitter) {
   if (skip != nullptr && *skip != 0) return;
-  using C = typename P::C;
   using Rl = typename P::R;
   constexpr int L = P::L, DIR = FWD ? 1 : -1;
   constexpr int RING = L == 4 ? 4 : 8;  // columns of R loaded ahead
@@ -144,7 +153,7 @@ __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double
       for (int t = 0; t < RING; ++t) ra[t] = rload(c1 + DIR * t);
 #pragma unroll 1
       for (int s0 = 0; s0 < count; s0 += TS_ROWS) {
-        res_jitter(jitter, (unsigned)s0);
+        trsv_pause(jitter, (unsigned)s0);
         const int s = min(s0 + (lane >> 1), count - 1);
         const double *src = at(c1 + DIR * s);
         Rl v = P::rzero();
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(64 * TS_WAVES) void trsv_kernel(int n, const double
     const double *px = reinterpret_cast<const double *>(&xown);
 #pragma unroll 1
     for (int s0 = 0; s0 < ncol; s0 += RING) {
-      res_jitter(jitter, 0x10000u + (unsigned)s0);
+      trsv_pause(jitter, 0x10000u + (unsigned)s0);
 #pragma unroll
       for (int t = 0; t < RING; ++t) {
         const int c = own + DIR * (s0 + t), k = c - w0;  // k outside [0, ncol) past the block

@@ -170,8 +170,8 @@ std::atomic<unsigned> g_jitter{0};
 
 // What a launch with bounded waits is given: their wall-clock limit (2 s) and
 // the jitter's seed.  Tests of the time-out paths (mgs_set_wait_limit) give
-// the calling thread's `t_limit_in`-th launch from here another limit and
-// long pauses.
+// the calling thread's `t_limit_in`-th launch from here another limit and,
+// where it is a triangular solve, long pauses.
 thread_local int t_limit_in = 0;
 thread_local long long t_limit_ticks = 0;
 struct WaitArgs {
@@ -179,7 +179,7 @@ struct WaitArgs {
   unsigned jitter;
 };
 WaitArgs wait_args(long long wclk_khz) {
-  if (t_limit_in > 0 && --t_limit_in == 0) return {t_limit_ticks, RES_STALL};
+  if (t_limit_in > 0 && --t_limit_in == 0) return {t_limit_ticks, TS_STALL};
   return {wclk_khz * 2000, g_jitter.load(std::memory_order_relaxed)};
 }
 

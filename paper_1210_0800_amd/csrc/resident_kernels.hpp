@@ -210,9 +210,7 @@ __device__ __forceinline__ void info_first_bad(int *info, int v) {
 // the whole wave, drawn from (seed, workgroup, wave, step) by an integer
 // hash.  Results must not change: every reduction order is fixed, so a
 // difference under jitter is a race.  seed 0 (the default) costs one
-// scalar compare.  RES_STALL (tests of the time-out paths): up to 100 us, so
-// that waits on this wave last long.
-constexpr unsigned RES_STALL = 0x57A11ED0u;
+// scalar compare.
 __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
   if (seed == 0) return;
   unsigned h = seed * 0x9E3779B1u ^ blockIdx.x * 0x85EBCA77u ^ (threadIdx.x >> 6) * 0xC2B2AE3Du ^ step * 0x27D4EB2Fu;
@@ -220,8 +218,7 @@ __device__ __forceinline__ void res_jitter(unsigned seed, unsigned step) {
   h *= 0x2C1B3C6Du;
   h ^= h >> 12;
   const int n = __builtin_amdgcn_readfirstlane((int)(h & 15u));
-  const int pauses = seed == RES_STALL ? n << 8 : n;
-  for (int i = 0; i < pauses; ++i) __builtin_amdgcn_s_sleep(1);
+  for (int i = 0; i < n; ++i) __builtin_amdgcn_s_sleep(1);
 }
 
 // The bound of a polling wait: the wall clock (and, in res_give_up, the abort
