@@ -14,7 +14,9 @@
 // one sum and one division and neither square root nor normalisation (one
 // 32 x 32 system: double 41 -> 34 us, dd 80 -> 69 us).  qd, and dd past 32
 // rows, use q_k itself (there the second reciprocal's registers and products
-// cost more than the shorter chain gives: qd 453 against 502 us).
+// cost more than the shorter chain gives: qd 453 against 502 us).  A u_k far
+// from 1 is divided by a power of two, so that products with it have the
+// range of products with q_k.
 //
 // A wave is a grid of 16 row groups x 4 columns: lane 4 g + c holds rows
 // g, g + 16, ... (RPL of them) of one column per slot, so that a wave works
@@ -94,7 +96,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   __shared__ double us[RING][NP][MP];       // u_c in entry c mod RING
   __shared__ double ys[NP][BAT_MAX_COLS];   // y (NW > 1: over 1 / r_kk until the end)
   __shared__ double invs[L][LATE ? BAT_MAX_COLS : 1];  // 1 / r_kk
-  __shared__ double ups[UF ? BAT_MAX_COLS : 1];  // what each column was divided by
+  __shared__ double ups[UF ? BAT_MAX_COLS : 1];  // what u_k (last: b) was divided by
+  __shared__ int far;                       // one of them is not 1
   __shared__ int pub;                       // u vectors published
   __shared__ int done[NW];                  // u vectors each wave has read
   __shared__ int status;                    // this system's info
@@ -112,6 +115,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   if (tid == 0) {
     status = 0;
     pub = 1;
+    if constexpr (UF) far = 0;
   }
   if (tid < NW) done[tid] = 0;
   const int first = last - (BAT_CG * w + cg);  // this lane's column in slot 0; slot s: first - STEP s
@@ -128,16 +132,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       }
     }
   };
+  bool wide = true;  // some ups is not 1
   auto put_u = [&](int c, const C (&v)[RPL]) __attribute__((always_inline)) {
     double *dst = &us[c & (RING - 1)][0][0];
 #pragma unroll
     for (int r = 0; r < RPL; ++r) P::store(dst + rg + BAT_RG * r, (size_t)MP, v[r]);
+    if constexpr (UF) {
+      // (rare; in LDS, so that it costs the others no registers)
+      if (wide && ups[c] != 1.0) {
+        const double f = pow2_inverse(ups[c]);
+#pragma unroll 1
+        for (int i = 0; i < NP * RPL; ++i) dst[rg + BAT_RG * i] *= f;
+      }
+    }
   };
-  // b, and a column of A whose largest entry is not within 2^-200 .. 2^200,
-  // over the power of two of that entry: exact, and it keeps 1 / ||u||^2 and
-  // u^H a in range.  An infinity or a NaN stays one; the bound keeps both
-  // powers normal numbers.
-  auto rescale = [&](int j, C (&v)[RPL]) __attribute__((always_inline)) {
+  // The power of two of column j (ups): that of its largest entry when that
+  // is not within 2^-64 .. 2^64, else 1.  u_j is divided by it when it is
+  // published, so that 1 / ||u||^2 and u^H a are in range wherever those of
+  // q_j are; the columns themselves stay as they are.  b, which is never
+  // published, is itself brought within 2^768, and out of the subnormal
+  // range: exact but for entries 2^1700 below its largest.  An infinity or a
+  // NaN stays one; the bound keeps both powers normal numbers.
+  auto range = [&](int j, C (&v)[RPL]) __attribute__((always_inline)) {
     if constexpr (UF) {
       double t[NP], big = 0.0;
 #pragma unroll
@@ -145,22 +161,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
         P::store(t, 1, v[r]);
         big = fmax(big, fmax(fabs(t[0]), fabs(t[1])));
       }
+      const double hi = j == n ? 0x1p800 : 0x1p64, lo = j == n ? 0x1p-800 : 0x1p-64;
+      auto out = [&](double v) __attribute__((always_inline)) { return v >= hi || (v > 0.0 && v <= lo); };
       double f = 1.0;
-      auto far = [](double v) __attribute__((always_inline)) { return v >= 0x1p200 || (v > 0.0 && v <= 0x1p-200); };
-      if (__any(j == n || far(big))) {
+      if (__any(out(big))) {
 #pragma unroll
         for (int k = BAT_CG; k < 64; k *= 2) big = fmax(big, __shfl_xor(big, k));
-        int e = (j == n || far(big)) && big > 0.0 && big < INFINITY ? ilogb(big) : 0;
+        int e = out(big) && big < INFINITY ? ilogb(big) : 0;
+        if (j == n && e > 0) e -= 767;
         e = e > 1000 ? 1000 : (e < -1000 ? -1000 : e);
         f = ldexp(1.0, e);
-        const double down = ldexp(1.0, -e);
+        if (j == n && e != 0) {
 #pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-          P::store(t, 1, v[r]);
+          for (int r = 0; r < RPL; ++r) {
+            P::store(t, 1, v[r]);
 #pragma unroll
-          for (int i = 0; i < NP; ++i) t[i] *= down;
-          v[r] = P::load(t, 1);
+            for (int i = 0; i < NP; ++i) t[i] *= pow2_inverse(f);
+            v[r] = P::load(t, 1);
+          }
         }
+        if (j >= 0 && j < n && e != 0) far = 1;
       }
       if (rg == 0 && j >= 0) ups[j] = f;
     }
@@ -174,7 +194,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   static_for<SL>([&](auto sI) __attribute__((always_inline)) {
     constexpr int s = decltype(sI)::value;
     const int j = first - STEP * s;
-    rescale(j >= 1 ? j : -1, col[s]);
+    range(j >= 1 ? j : -1, col[s]);
   });
   C u[RPL];
   Rl s2, rkk, inv;  // ||u_k||^2, its root, 1 over that
@@ -211,7 +231,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   };
   if (w == 0) {
     load_col(0, u);
-    rescale(cg == 0 ? 0 : -1, u);
+    range(cg == 0 ? 0 : -1, u);
+    if constexpr (UF) lds_wait();  // ups[0], of one lane, for all
     if constexpr (!UF) {
       s2 = G::real_sum(norm(u));
       root_and_inverse<P>(s2, rkk, inv);
@@ -220,6 +241,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     if (cg == 0) put_u(0, u);
   }
   __syncthreads();
+  if constexpr (UF) wide = __builtin_amdgcn_readfirstlane(far) != 0;
 
   bool alive = true;
   // Bounded wait for `ready()`; false (and the status) on a time-out.
@@ -414,35 +436,36 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     }
   }
   // R below its diagonal: zeros.  Above it, and in y, what is still missing:
-  // 1 / r_kk, and the power of two of the column.
-  auto late = [&](int k, int j, const C &v) __attribute__((always_inline)) {
+  // 1 / r_kk, and the power of two of b.
+  auto late = [&](int k, const C &v) __attribute__((always_inline)) {
     Rl f;
-    double *pf = reinterpret_cast<double *>(&f), t[NP];
+    double *pf = reinterpret_cast<double *>(&f);
     if constexpr (LATE) {
 #pragma unroll
       for (int i = 0; i < L; ++i) pf[i] = invs[i][k];
-      P::store(t, 1, P::scale(v, f));
-    } else {
-      P::store(t, 1, v);
+      return P::scale(v, f);
     }
-#pragma unroll
-    for (int i = 0; i < NP; ++i) t[i] *= ups[j];
-    return P::load(t, 1);
+    return v;
   };
   if constexpr (UF) __syncthreads();
   for (int j = w; j < n; j += NW) {
     if (lane >= n) continue;
     double *p = R + (size_t)j * a.ldr + lane;
     if (lane > j) P::store(p, planeR, P::czero());
-    if constexpr (UF) {
-      if (lane < j && (LATE || ups[j] != 1.0)) P::store(p, planeR, late(lane, j, P::load(p, planeR)));
+    if constexpr (LATE) {
+      if (lane < j) P::store(p, planeR, late(lane, P::load(p, planeR)));
     }
   }
   if constexpr (UF) {
     if (w == 0 && last == n && lane < n) {
-      const C v = late(lane, n, P::load(&ys[0][lane], (size_t)BAT_MAX_COLS));
-      P::store(&ys[0][lane], (size_t)BAT_MAX_COLS, v);
-      if (y != nullptr) P::store(y + lane, (size_t)n, v);
+      double t[NP];
+      P::store(t, 1, late(lane, P::load(&ys[0][lane], (size_t)BAT_MAX_COLS)));
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        t[i] *= ups[n];
+        ys[i][lane] = t[i];
+        if (y != nullptr) y[lane + (size_t)i * n] = t[i];
+      }
     }
   }
   __syncthreads();

@@ -172,10 +172,11 @@ mgs_left_kernel(LeftArgs a) {
         col[r] = i < a.m ? P::load(src + i, pl) : P::czero();
       }
     }
-    // A column whose largest entry is not within 2^-200 .. 2^200, over the
-    // power of two of that entry (`up`): exact, and it keeps 1 / ||u||^2 and
-    // u^H a in range.  An infinity or a NaN stays one; the bound keeps both
-    // powers normal numbers.
+    // The power of two (`up`) of a column's largest entry when that is not
+    // within 2^-64 .. 2^64.  u_c is divided by it when it is handed on, so that
+    // 1 / ||u||^2 and u^H a are in range wherever those of q_c are; the column
+    // itself stays as it is.  An infinity or a NaN stays one; the bound keeps
+    // both powers normal numbers.
     double up = 1.0;
     if (!isb) {
       double t[2 * L], big = 0.0;
@@ -184,21 +185,13 @@ mgs_left_kernel(LeftArgs a) {
         P::store(t, 1, col[r]);
         big = fmax(big, fmax(fabs(t[0]), fabs(t[1])));
       }
-      if (__syncthreads_or(big >= 0x1p200 || (big > 0.0 && big <= 0x1p-200))) {
+      if (__syncthreads_or(big >= 0x1p64 || (big > 0.0 && big <= 0x1p-64))) {
         if (tid == 0) emax = -2000;
         __syncthreads();
         if (big > 0.0) atomicMax(&emax, big < INFINITY ? ilogb(big) : 2000);
         __syncthreads();
-        const int e = emax >= 2000 || (emax < 200 && emax >= -200) ? 0 : emax > 1000 ? 1000 : emax < -1000 ? -1000 : emax;
-        up = ldexp(1.0, e);
-        const double down = ldexp(1.0, -e);
-#pragma unroll
-        for (int r = 0; r < RPT; ++r) {
-          P::store(t, 1, col[r]);
-#pragma unroll
-          for (int i = 0; i < 2 * L; ++i) t[i] *= down;
-          col[r] = P::load(t, 1);
-        }
+        const int e = emax >= 2000 || (emax < 64 && emax >= -64) ? 0 : emax;
+        up = ldexp(1.0, e > 1000 ? 1000 : e < -1000 ? -1000 : e);
       }
     }
     const int kend = c < a.n ? c : a.n;
@@ -262,6 +255,16 @@ mgs_left_kernel(LeftArgs a) {
 #pragma unroll
       for (int r = 0; r < RPT; ++r) P::upd(col[r], rk, u[r]);
     }
+    if (up != 1.0) {
+      double t[2 * L];
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        P::store(t, 1, col[r]);
+#pragma unroll
+        for (int i = 0; i < 2 * L; ++i) t[i] *= pow2_inverse(up);
+        col[r] = P::load(t, 1);
+      }
+    }
     if (!isb) {
       // u_c out (column 0 is raw input: an entry with the marker's bits
       // leaves as a quiet NaN).
@@ -298,20 +301,19 @@ mgs_left_kernel(LeftArgs a) {
       double t[L];
       P::store_real(t, 1, s2);
       if (!P::ok_norm(s2) || !(t[0] * up * up < INFINITY && t[0] * up * up > 0.0)) info_first_bad(a.info, c + 1);
-      // R(c, c); its imaginary part carries `up` to left_finish_kernel
       P::store_real(t, 1, rkk);
       double *d = a.R + (size_t)c * a.ldr + c;
 #pragma unroll
       for (int i = 0; i < L; ++i) {
         d[(size_t)(2 * i) * a.planeR] = t[i] * up;
-        d[(size_t)(2 * i + 1) * a.planeR] = i == 0 ? up : 0.0;
+        d[(size_t)(2 * i + 1) * a.planeR] = 0.0;
       }
     }
   }
 }
 
-// Column j of Q times 1 / r_jj, R(k, j) times 1 / r_kk and column j's power of
-// two for k < j, zeros below R's diagonal.  One workgroup per column.
+// Column j of Q times 1 / r_jj, R(k, j) times 1 / r_kk for k < j, zeros below
+// R's diagonal.  One workgroup per column.
 template <class P>
 __global__ __launch_bounds__(256) void left_finish_kernel(int m, int n, double *Q, int ldq, size_t planeQ, double *R,
                                                           int ldr, size_t planeR, const double *rec) {
@@ -325,22 +327,15 @@ __global__ __launch_bounds__(256) void left_finish_kernel(int m, int n, double *
     return v;
   };
   const Rl inv = inverse(j);
-  double *diag = R + (size_t)j * ldr + j + planeR;
-  const double up = *diag;
-  __syncthreads();
-  if (threadIdx.x == 0) *diag = 0.0;
   for (int i = threadIdx.x; i < m; i += 256) {
     double *p = Q + (size_t)j * ldq + i;
     P::store(p, planeQ, P::scale(P::load(p, planeQ), inv));
   }
   for (int k = threadIdx.x; k < n; k += 256) {
     double *p = R + (size_t)j * ldr + k;
-    if (k < j) {
-      double t[2 * P::L];
-      P::store(t, 1, P::scale(P::load(p, planeR), inverse(k)));
-#pragma unroll
-      for (int i = 0; i < 2 * P::L; ++i) p[(size_t)i * planeR] = t[i] * up;
-    } else if (k > j)
+    if (k < j)
+      P::store(p, planeR, P::scale(P::load(p, planeR), inverse(k)));
+    else if (k > j)
       P::store(p, planeR, P::czero());
   }
 }

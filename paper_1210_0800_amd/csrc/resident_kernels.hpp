@@ -160,6 +160,11 @@ __device__ __forceinline__ double res_unmark(double v) {
   return __double_as_longlong(v) == RES_EMPTY ? __longlong_as_double(0x7ff8000000000000LL) : v;
 }
 
+// 1 / f for f = 2^e, |e| < 1022.
+__device__ __forceinline__ double pow2_inverse(double f) {
+  return __longlong_as_double(0x7FE0000000000000LL - __double_as_longlong(f));
+}
+
 // Widest panel the resident schedule factors.
 constexpr int RES_BWMAX = 4;
 
