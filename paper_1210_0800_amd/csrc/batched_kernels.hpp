@@ -210,14 +210,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       double t[L];
       P::store_real(t, 1, s2);
       bool ok = P::ok_norm(s2);
-      if constexpr (UF) ok = ok && t[0] * ups[c] * ups[c] < INFINITY && t[0] * ups[c] * ups[c] > 0.0;
+      double n2 = 0.0;  // ||a_c||^2
+      if constexpr (UF) {
+        n2 = t[0] * ups[c] * ups[c];
+        ok = ok && n2 < INFINITY && n2 > 0.0;
+      }
       if (!ok) atomicCAS(&status, 0, c + 1);
       if constexpr (LATE) P::store_real(&invs[0][c], BAT_MAX_COLS, inv);
+      // (a refused column's r_cc is not a pivot: later calls with R refuse it too)
       P::store_real(t, 1, rkk);
+      if (UF && !ok) t[0] = n2;
 #pragma unroll
       for (int i = 0; i < L; ++i) {
         double *p = R + (size_t)c * a.ldr + c + (size_t)(2 * i) * planeR;
-        p[0] = UF ? t[i] * ups[c] : t[i];
+        p[0] = UF && ok ? t[i] * ups[c] : t[i];
         p[planeR] = 0.0;
       }
     }

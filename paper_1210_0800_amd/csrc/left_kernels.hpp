@@ -300,12 +300,16 @@ mgs_left_kernel(LeftArgs a) {
     if (tid == 0) {
       double t[L];
       P::store_real(t, 1, s2);
-      if (!P::ok_norm(s2) || !(t[0] * up * up < INFINITY && t[0] * up * up > 0.0)) info_first_bad(a.info, c + 1);
+      const double n2 = t[0] * up * up;  // ||a_c||^2
+      const bool ok = P::ok_norm(s2) && n2 < INFINITY && n2 > 0.0;
+      if (!ok) info_first_bad(a.info, c + 1);
+      // (a refused column's r_cc is not a pivot: later calls with R refuse it too)
       P::store_real(t, 1, rkk);
+      if (!ok) t[0] = n2;
       double *d = a.R + (size_t)c * a.ldr + c;
 #pragma unroll
       for (int i = 0; i < L; ++i) {
-        d[(size_t)(2 * i) * a.planeR] = t[i] * up;
+        d[(size_t)(2 * i) * a.planeR] = ok ? t[i] * up : t[i];
         d[(size_t)(2 * i + 1) * a.planeR] = 0.0;
       }
     }
