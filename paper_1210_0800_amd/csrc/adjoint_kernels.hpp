@@ -22,7 +22,7 @@ template <class P>
 __global__ __launch_bounds__(ADJ_T) void adj_partial_kernel(int m, int n, const double *Q, int ldq, size_t planeQ,
                                                              const double *A, int lda, size_t planeA,
                                                              const double *b, const double *x, const double *w,
-                                                             typename P::Acc *partial) {
+                                                             typename Partial<P>::T *partial) {
   using Acc = typename P::Acc;
   const int i = blockIdx.x * ADJ_T + threadIdx.x;
   const int cb = blockIdx.y, which = blockIdx.z;  // 0: Q w, 1: b - A x
@@ -44,20 +44,20 @@ __global__ __launch_bounds__(ADJ_T) void adj_partial_kernel(int m, int n, const 
     for (int j = j0; j < j1; ++j)
       P::acc_cmul(acc, P::load(A + (size_t)j * lda + i, planeA), P::cneg(P::load(x + j, (size_t)n)));
   }
-  partial[((size_t)which * nchunk + cb) * m + i] = acc;
+  partial[((size_t)which * nchunk + cb) * m + i] = Partial<P>::pack(acc);
 }
 
 template <class P>
-__global__ __launch_bounds__(WG) void adj_finish_kernel(int m, int n, const typename P::Acc *partial, double *gb,
-                                                         double *r) {
+__global__ __launch_bounds__(WG) void adj_finish_kernel(int m, int n, const typename Partial<P>::T *partial,
+                                                         double *gb, double *r) {
   using Acc = typename P::Acc;
   const int i = blockIdx.x * WG + threadIdx.x;
   const int which = blockIdx.y;
   if (i >= m) return;
   const int nchunk = (n + ADJ_CH - 1) / ADJ_CH;
-  const Acc *p = partial + (size_t)which * nchunk * m + i;
-  Acc acc = p[0];
-  for (int c = 1; c < nchunk; ++c) P::acc_merge(acc, p[(size_t)c * m]);
+  const typename Partial<P>::T *p = partial + (size_t)which * nchunk * m + i;
+  Acc acc = Partial<P>::unpack(p[0]);
+  for (int c = 1; c < nchunk; ++c) P::acc_merge(acc, Partial<P>::unpack(p[(size_t)c * m]));
   P::store((which == 0 ? gb : r) + i, (size_t)m, P::acc_value(acc));
 }
 

@@ -808,6 +808,21 @@ struct PrecD {
   __device__ static __forceinline__ void store_real(double *p, size_t stride, const R &v) { p[0] = v; }
 };
 
+// A sum as the kernels leave it in memory for the next launch: the
+// accumulator, in qd its value (four limbs a part, 64 bytes in place of 80).
+template <class P>
+struct Partial {
+  using T = typename P::Acc;
+  __device__ static __forceinline__ T pack(const typename P::Acc &a) { return a; }
+  __device__ static __forceinline__ typename P::Acc unpack(const T &t) { return t; }
+};
+template <>
+struct Partial<PrecQD> {
+  using T = cqd;
+  __device__ static __forceinline__ T pack(const PrecQD::Acc &a) { return PrecQD::acc_value(a); }
+  __device__ static __forceinline__ PrecQD::Acc unpack(const T &t) { return {qd_sum_from(t.re), qd_sum_from(t.im)}; }
+};
+
 // r = sqrt(s) and 1 / r (dd and qd: the fused forms that share their
 // slow steps; FP64: the square root, then the division).
 template <class P>

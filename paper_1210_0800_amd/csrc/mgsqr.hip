@@ -255,7 +255,7 @@ size_t qr_work_bytes(int m, int n, int prec) {
 size_t solve_work_bytes(int n, int prec) { return round256(sizeof(double) * 2 * (size_t)prec * n); }
 // adjoint: w (n), z (n), r (m), then the chunk partials of Q w and b - A x
 // (2 x chunks x m accumulators).
-size_t adj_acc_bytes(int prec) { return prec == 1 ? sizeof(PrecD::Acc) : prec == 2 ? sizeof(PrecDD::Acc) : sizeof(PrecQD::Acc); }
+size_t adj_acc_bytes(int prec) { return prec == 2 ? sizeof(Partial<PrecDD>::T) : sizeof(Partial<PrecQD>::T); }
 size_t adjoint_work_bytes(int m, int n, int prec) {
   const size_t nchunk = (size_t)((n + ADJ_CH - 1) / ADJ_CH);
   return 2 * round256(sizeof(double) * 2 * (size_t)prec * n) + round256(sizeof(double) * 2 * (size_t)prec * m) +
@@ -269,7 +269,8 @@ int adjoint_launch(int m, int n, const double *A, int lda, const double *b, cons
   double *w = static_cast<double *>(work);
   double *z = w + round256(sizeof(double) * 2 * P::L * (size_t)n) / sizeof(double);
   double *r = z + round256(sizeof(double) * 2 * P::L * (size_t)n) / sizeof(double);
-  auto *part = reinterpret_cast<typename P::Acc *>(r + round256(sizeof(double) * 2 * P::L * (size_t)m) / sizeof(double));
+  auto *part =
+      reinterpret_cast<typename Partial<P>::T *>(r + round256(sizeof(double) * 2 * P::L * (size_t)m) / sizeof(double));
   int rc = trsv_launch<P, true>(n, R, ldr, gx, w, info, st);
   if (rc != MGS_OK) return rc;
   // (info keeps what the first solve had to report)
@@ -302,7 +303,7 @@ size_t panel_res_bytes(int m, int n) {
 }
 RefineWork refine_layout(int m, int n, int prec, void *base) {
   const int nchunk = ceil_div(n, NBP);
-  const size_t acc_bytes = sizeof(PrecQD::Acc);  // the residual accumulates in qd
+  const size_t acc_bytes = sizeof(Partial<PrecQD>::T);  // the residual accumulates in qd
   (void)prec;
   size_t off = 0;
   auto take = [&](size_t b) {
@@ -410,17 +411,17 @@ int refine_solve(int m, int n, const double *A, int lda, const double *b, double
   // steps cost little past convergence.
   DevInfo d;
   // (the barrier count of all steps must fit the 32-bit counter; the partial
-  // sums that pass between its workgroups lie where the residual's were, 80
-  // bytes per row and panel against 16 to 31)
+  // sums that pass between its workgroups lie where the residual's were, 64
+  // bytes per row and panel against 16 to 32)
   const int pr_wgs = ceil_div(m, PR_ROWS);
   bool fused = m <= PR_MAX_ROWS && (long long)max_iter * pr_wgs < (1LL << 31) && dev_info(d) && d.cus >= pr_wgs &&
                (pr_wgs == 1 || sizeof(double) * 2 * NBP * (size_t)(nchunk < 3 ? nchunk : 3) * pr_wgs <=
-                                   sizeof(PrecQD::Acc) * (size_t)nchunk * m);
+                                   sizeof(Partial<PrecQD>::T) * (size_t)nchunk * m);
   for (int it = 1; it <= max_iter; ++it) {
     hipLaunchKernelGGL((residual_partial_kernel<P::L>), dim3(ceil_div(m, 256), nchunk), dim3(256), 0, st, m, n, NBP,
-                       A, lda, b, x, static_cast<PrecQD::Acc *>(w.partial), w.ctl);
+                       A, lda, b, x, static_cast<Partial<PrecQD>::T *>(w.partial), w.ctl);
     hipLaunchKernelGGL((residual_finish_kernel<PrecQD>), dim3(ceil_div(m, 256)), dim3(256), 0, st, m, nchunk,
-                       static_cast<const PrecQD::Acc *>(w.partial), w.r64, w.ctl);
+                       static_cast<const Partial<PrecQD>::T *>(w.partial), w.r64, w.ctl);
     if (fused) {
       // arrivals at the grid barriers of the earlier steps (one each)
       unsigned int base = pr_wgs > 1 ? (unsigned int)(it - 1) * (unsigned int)pr_wgs : 0u;

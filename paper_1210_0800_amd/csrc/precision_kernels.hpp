@@ -284,7 +284,7 @@ __device__ __forceinline__ cqd load_qd_from(const double *p, size_t plane) {
 template <int LP>
 __global__ __launch_bounds__(256) void residual_partial_kernel(int m, int n, int chunk, const double *A, int lda,
                                                                 const double *b, const double *x,
-                                                                PrecQD::Acc *partial, const RefineCtl *ctl) {
+                                                                Partial<PrecQD>::T *partial, const RefineCtl *ctl) {
   if (ctl->status != 0) return;
   using P = PrecQD;
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -299,18 +299,19 @@ __global__ __launch_bounds__(256) void residual_partial_kernel(int m, int n, int
   const int j1 = min(n, (cb + 1) * chunk);
   for (int j = cb * chunk; j < j1; ++j)
     P::acc_cmul(acc, load_qd_from<LP>(A + (size_t)j * lda + i, planeA), P::cneg(load_qd_from<LP>(x + j, (size_t)n)));
-  partial[(size_t)cb * m + i] = acc;
+  partial[(size_t)cb * m + i] = Partial<P>::pack(acc);
 }
 
 // Sum the chunk partials in chunk order; r64 = FP64 rounding of r.
 template <class P>
-__global__ __launch_bounds__(256) void residual_finish_kernel(int m, int nchunk, const typename P::Acc *partial,
-                                                               double *r64, const RefineCtl *ctl) {
+__global__ __launch_bounds__(256) void residual_finish_kernel(int m, int nchunk,
+                                                               const typename Partial<P>::T *partial, double *r64,
+                                                               const RefineCtl *ctl) {
   if (ctl->status != 0) return;
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= m) return;
-  typename P::Acc acc = partial[i];
-  for (int c = 1; c < nchunk; ++c) P::acc_merge(acc, partial[(size_t)c * m + i]);
+  typename P::Acc acc = Partial<P>::unpack(partial[i]);
+  for (int c = 1; c < nchunk; ++c) P::acc_merge(acc, Partial<P>::unpack(partial[(size_t)c * m + i]));
   typename P::C v = P::acc_value(acc);
   double tmp[2 * P::L];
   P::store(tmp, 1, v);  // tmp[0] = re hi, tmp[1] = im hi (planes 0 and 1)
