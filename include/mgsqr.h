@@ -112,10 +112,15 @@ int mgs_workspace_size(int m, int n, int prec, int op, size_t *bytes);
  * at most 5 columns per compute unit, 8 when m <= 512, e.g. 1024 x 1024
  * with b on 256 compute units; double: m <= 2048, 5 columns per compute
  * unit beyond 1024 rows, 8 below) one cooperative launch with the columns
- * held in registers; in qd with m <= 1024 one cooperative launch that takes
- * a column per workgroup at a time; otherwise one launch per panel of
- * columns.
- * mgs_qr_schedule (below) forces one of them.
+ * held in registers; in qd with m <= 1024 one (ordinary) launch whose
+ * workgroups take a column at a time, so that calls on several streams run
+ * beside each other; otherwise one launch per panel of columns.
+ * mgs_qr_schedule (below) forces one of them but the qd launch, which only
+ * this call takes.  The waits of the single launches, and of the triangular
+ * solves of more than 32 rows, are bounded: one that lasts 2 s ends the call
+ * with MGS_INFO_SYNC_TIMEOUT.  The cooperative ones and the triangular solves
+ * of more than 128 rows also wait for workgroups that have not started, e.g.
+ * behind another stream's kernel that holds the card that long.
  * All schedules apply the projections of Figure 1 in the same order per
  * column; reduction trees differ, and the projections of the one-workgroup
  * schedule (double, and dd with m <= 32), of the qd launch (b excepted), and

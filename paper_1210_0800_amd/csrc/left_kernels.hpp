@@ -3,9 +3,9 @@
 // (Section 3) on the augmented matrix of Equation (1), one column at a time
 // per workgroup.
 //
-// Workgroup g takes columns g, g + G, ... of [A b].  It loads column c once,
-// applies the projections k = 0, 1, ..., c-1 in order as they become
-// available, and writes it once.  The columns handed on are the
+// A workgroup takes the next column of [A b] that nobody has taken (a counter),
+// loads it once, applies the projections k = 0, 1, ..., c-1 in order as they
+// become available, writes it once, and takes another.  The columns handed on are the
 // unnormalised ones: u_k is column k after its last projection, and
 //   r_kj = (u_k^H a_j) / r_kk,   a_j -= ((u_k^H a_j) / ||u_k||^2) u_k,
 // equal to q_k^H a_j and r_kj q_k in exact arithmetic, so neither the square
@@ -30,13 +30,21 @@
 // wave's stores are complete (wave w of every workgroup holds the same rows,
 // so no barrier is needed on either side either way).  Every wait is
 // bounded by a wall-clock limit and ends through the abort flag that all
-// waits observe; the launch is cooperative (every workgroup resident), and
-// the lowest unfinished column never waits for a later one.
+// waits observe.  Column c waits only for columns before it, and those were
+// taken before it, by workgroups that run or have finished: so the launch
+// needs no more than one workgroup on the card at a time to end, and is an
+// ordinary one.  (Columns dealt by workgroup number wait for workgroups that
+// may not have started, e.g. behind another stream's kernel, and need a
+// cooperative launch; those do not run beside each other.)
 #pragma once
 #include "../../include/mgsqr.h"
 #include "batched_kernels.hpp"
 
 namespace mgsq {
+
+// Words of LeftArgs::sync: the next column to take, the workgroups that have
+// met, and what came of it (0 open, 1 all met, 2 not).
+constexpr int LEFT_NEXT = 192, LEFT_MET = 208, LEFT_MODE = 224;
 
 struct LeftArgs {
   int m, n, ncols;  // ncols = n + 1 when b is augmented
@@ -54,8 +62,8 @@ struct LeftArgs {
   double *rho;
   int *info;
   double *rec;         // per column k: 1 / ||u_k||^2, then 1 / r_kk (L doubles each)
-  unsigned int *sync;  // RES_SYNC_WORDS words: per-wave counters and the abort flag
-  int G;
+  unsigned int *sync;  // RES_SYNC_WORDS words: per-wave counters (up to 8), LEFT_NEXT, _MET, _MODE, the abort flag
+  int meet;  // several workgroups share a compute unit: 50 us on the wall clock; else 0
   int marked;            // Q holds the empty marker at the start (Q is not A)
   long long spin_ticks;  // wall-clock limit of one wait
   unsigned jitter;       // race checks: seed of the timing jitter (0: none)
@@ -93,6 +101,7 @@ mgs_left_kernel(LeftArgs a) {
   __shared__ double xch[2][2][H][NW];  // wave totals, [buffer][part][word][wave]
   __shared__ double lrec[2][L];        // 1 / ||u_k||^2 of the step
   __shared__ int emax;                 // a large column's exponent
+  __shared__ int taken;                // the workgroup's column
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int buf = 0, seen = 0;
   unsigned step = 0;
@@ -161,7 +170,39 @@ mgs_left_kernel(LeftArgs a) {
     if (wave == 0 && (lane & 31) == 0) P::store_real(p + (lane >> 5) * plane, 2 * plane, v);
   };
 
-  for (int c = blockIdx.x; c < a.ncols; c += a.G) {
+  // Columns that share a compute unit should be far apart, so where several
+  // workgroups share one they meet first, and once all are on the card the
+  // columns are dealt by workgroup number (workgroups i and i + 256 share a
+  // unit: 1024 x 288 4.5 ms, by the counter alone 6.1).  If they have not met
+  // after a.meet (50 us), one of them decides for the counter.
+  bool dealt = false;
+  if (a.meet > 0) {
+    if (tid == 0) {
+      unsigned int *mode = a.sync + LEFT_MODE, now;
+      if (__hip_atomic_fetch_add(a.sync + LEFT_MET, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x)
+        atomicCAS(mode, 0u, 1u);
+      const long long t0 = wall_clock64();
+      while ((now = __hip_atomic_load(mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u) {
+        if (wall_clock64() - t0 > a.meet) atomicCAS(mode, 0u, 2u);
+        __builtin_amdgcn_s_sleep(2);
+      }
+      taken = (int)now;
+    }
+    __syncthreads();
+    dealt = __builtin_amdgcn_readfirstlane(taken) == 1;
+    __syncthreads();
+  }
+  for (int c = dealt ? (int)blockIdx.x - (int)gridDim.x : -1; c != a.ncols - 1;) {
+    if (dealt) {
+      c += gridDim.x;
+    } else {
+      // (every wave has read the last number before its sums' barriers)
+      if (tid == 0)
+        taken = (int)__hip_atomic_fetch_add(a.sync + LEFT_NEXT, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      c = __builtin_amdgcn_readfirstlane(taken);
+    }
+    if (c >= a.ncols) break;
     const bool isb = c == a.n;
     {
       const double *src = isb ? a.b : a.A + (size_t)c * a.lda;

@@ -622,41 +622,29 @@ int res_launch(const StepArgs &s, void *sync, double *u, hipStream_t st) {
 }
 
 // ------------------------------------------------ left-looking qd ------
-// Returns 1 when it does not apply (the caller then takes the per-panel
-// schedule).  Workspace: the records (2 L n doubles, in the place of the
-// working copy of b, 2 L m doubles) and the synchronisation words.
+// Workspace: the records (2 L n doubles, in the place of the working copy of
+// b, 2 L m doubles) and the synchronisation words.  PC workgroups per compute
+// unit, no more than columns.
 template <class P, int RPT, int NW, int PC>
-int left_launch_shape(LeftArgs a, int cus, hipStream_t st) {
-  auto kern = mgs_left_kernel<P, RPT, NW, PC>;
-  // no private (scratch) memory in a cooperative launch
-  hipFuncAttributes fa;
-  if (hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(kern)) != hipSuccess || fa.localSizeBytes != 0)
-    return 1;
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern), 64 * NW, 0) !=
-          hipSuccess ||
-      per_cu < 1)
-    return 1;
-  if (per_cu > PC) per_cu = PC;
-  a.G = a.ncols < per_cu * cus ? a.ncols : per_cu * cus;
+int left_launch_shape(LeftArgs a, int cus, int khz, hipStream_t st) {
+  const int G = a.ncols < PC * cus ? a.ncols : PC * cus;
+  a.meet = G > cus ? khz / 20 : 0;
   const int nrec = 2 * P::L * a.n;
   hipLaunchKernelGGL(left_init_kernel, dim3(a.marked ? ceil_div(a.m, 256) : 1, a.n), dim3(256), 0, st, a.sync, a.info,
                      a.rec, nrec, a.m, a.n, a.Q, a.ldq, a.planeQ, a.marked ? 2 * P::L : 0);
   if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
-  void *args[] = {&a};
-  if (hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kern), dim3(a.G), dim3(64 * NW), args, 0, st) !=
-      hipSuccess) {
-    (void)hipGetLastError();
-    return 1;
-  }
+  hipLaunchKernelGGL((mgs_left_kernel<P, RPT, NW, PC>), dim3(G), dim3(64 * NW), 0, st, a);
+  if (hipGetLastError() != hipSuccess) return MGS_ERR_LAUNCH;
   hipLaunchKernelGGL((left_finish_kernel<P>), dim3(a.n), dim3(256), 0, st, a.m, a.n, a.Q, a.ldq, a.planeQ, a.R, a.ldr,
                      a.planeR, a.rec);
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
+// m <= 1024.
 int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
   using P = PrecQD;
   DevInfo d;
-  if (!dev_info(d) || d.cus <= 0) return 1;
+  const bool have = dev_info(d);
+  const int cus = have && d.cus > 0 ? d.cus : 256;
   LeftArgs a;
   a.m = s.m;
   a.n = s.n;
@@ -677,7 +665,8 @@ int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
   a.rec = static_cast<double *>(work);
   a.sync = reinterpret_cast<unsigned int *>(static_cast<char *>(work) + qr_w_bytes(s.m, P::L));
   a.marked = s.Q != s.A;
-  const WaitArgs wait = wait_args(d.wclk_khz);
+  const int khz = have ? (int)d.wclk_khz : 100000;
+  const WaitArgs wait = wait_args(khz);
   a.spin_ticks = wait.ticks;
   a.jitter = wait.jitter;
   // One column per workgroup (up to an eighth more: a workgroup's first
@@ -687,14 +676,13 @@ int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
   // halves the sums' share, and several workgroups per compute unit to fill
   // each other's waits (500 x 500 5.4 ms against 6.0; 1024 x 1024 31.0 ms
   // against 34.5 with 8 waves of 2 rows, one workgroup).
-  const bool single = s.ncols <= d.cus + d.cus / 8;
-  if (s.m <= 64) return left_launch_shape<P, 1, 1, 1>(a, d.cus, st);
-  if (s.m <= 128) return left_launch_shape<P, 1, 2, 1>(a, d.cus, st);
-  if (s.m <= 256) return left_launch_shape<P, 1, 4, 1>(a, d.cus, st);
+  const bool single = s.ncols <= cus + cus / 8;
+  if (s.m <= 64) return left_launch_shape<P, 1, 1, 1>(a, cus, khz, st);
+  if (s.m <= 128) return left_launch_shape<P, 1, 2, 1>(a, cus, khz, st);
+  if (s.m <= 256) return left_launch_shape<P, 1, 4, 1>(a, cus, khz, st);
   if (s.m <= 512)
-    return single ? left_launch_shape<P, 1, 8, 1>(a, d.cus, st) : left_launch_shape<P, 2, 4, 3>(a, d.cus, st);
-  if (s.m <= 1024) return left_launch_shape<P, 4, 4, 2>(a, d.cus, st);
-  return 1;
+    return single ? left_launch_shape<P, 1, 8, 1>(a, cus, khz, st) : left_launch_shape<P, 2, 4, 3>(a, cus, khz, st);
+  return left_launch_shape<P, 4, 4, 2>(a, cus, khz, st);
 }
 
 // Small systems: one workgroup per system (returns MGS_ERR_DIMS when the
@@ -1033,10 +1021,7 @@ int mgs_qr_schedule(int m, int n, int prec, const double *A, int lda, double *Q,
     if (rc != 1) return rc;
     if (mode == MGS_SCHED_RESIDENT) return MGS_ERR_DIMS;
   }
-  if (mode == MGS_SCHED_AUTO && prec == 4) {
-    const int rc = left_launch_qd(a, work, st);
-    if (rc != 1) return rc;
-  }
+  if (mode == MGS_SCHED_AUTO && prec == 4 && m <= 1024) return left_launch_qd(a, work, st);
   if (prec == 1) return dispatch_shape<PrecD>(a, sh, st);
   if (prec == 2) return dispatch_shape<PrecDD>(a, sh, st);
   return dispatch_shape<PrecQD>(a, sh, st);
