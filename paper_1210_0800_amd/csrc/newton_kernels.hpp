@@ -22,8 +22,8 @@ constexpr int NT_MAX_VARS = 63;  // variables (columns of [J -f] <= 64)
 constexpr int NT_MAX_VPM = 8;    // variables per monomial
 constexpr int NT_MAX_DEG = 16;   // exponent bound
 
-// Powers x_j^d, d = 1..NT_TAB, kept per point; a higher one is continued by
-// repeated products.
+// Powers x_j^d, d = 1..NT_TAB, kept per point; a higher one is a product of
+// two or three of them.
 constexpr int NT_TAB = 6;
 
 template <class P>
@@ -35,9 +35,9 @@ __device__ __forceinline__ typename P::C nt_mul(const typename P::C &a, const ty
 }
 
 // Dynamic LDS of poly_eval_kernel: the power table, then per wave the
-// derivatives of its 64 lanes' monomials.
+// derivatives of its 64 lanes' monomials and a list of monomials per lane.
 constexpr size_t nt_table_doubles(int L, int nvar) { return (size_t)2 * L * NT_TAB * nvar; }
-constexpr size_t nt_wave_doubles(int L, int nvpm) { return (size_t)2 * L * 64 * nvpm; }
+constexpr size_t nt_wave_doubles(int L, int nvpm) { return (size_t)2 * L * 64 * nvpm + 64; }
 
 // One workgroup evaluates neqb equations at one point; its waves take them
 // HALF ? two at a time (nmon <= 32: a lane per monomial, an equation per half
@@ -47,14 +47,19 @@ constexpr size_t nt_wave_doubles(int L, int nvpm) { return (size_t)2 * L * 64 * 
 // products (kept in the derivatives' places in LDS) and a running prefix
 // product, so nothing but the current products is held in registers.  f_e is
 // a sum over the lanes (fixed tree).  J(e, j) is summed by the lane of
-// variable j in monomial order: ballots give each lane the monomials (and
-// factors) that hold its variable, and all lanes walk their lists at once.
+// variable j in monomial order: every lane enters its monomial in the lists
+// (bits in LDS) of its factors' variables, and all lanes walk their variable's
+// lists at once.
 // f_e (-f_e when negate) goes to b, J to A, both in the batched
 // least-squares layout.
 //
 // Bound by the products: qd, 32 equations of 32 monomials of 5 variables at
 // 1024 points took 3.1 ms with a power per factor, half the lanes idle and
-// 1.7 KB of scratch per lane.
+// 1.7 KB of scratch per lane.  With a ballot per variable and factor in place
+// of the lists in LDS (64 variables and 8 factors: 4000 instructions an
+// equation) calls took 1.1 to 2.4 times as long (200 points, 63 variables, 64
+// monomials of 8 factors: double 229 -> 97, dd 509 -> 264, qd 2285 -> 1841 us;
+// 32 monomials of 5 factors: 33 -> 19, 45 -> 31, 256 -> 227).
 template <class P, bool HALF>
 __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int nmon, int nvpm, const int *vars,
                                                         const int *exps, const double *coef, const double *x,
@@ -70,6 +75,7 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
   const size_t tabp = (size_t)NT_TAB * nvar, dsp = (size_t)64 * nvpm;  // plane strides
   double *tab = lds;                                                      // [plane][d - 1][variable]
   double *ds = lds + nt_table_doubles(P::L, nvar) + wave * nt_wave_doubles(P::L, nvpm);  // [plane][lane * nvpm + t]
+  unsigned long long *lists = reinterpret_cast<unsigned long long *>(ds + (size_t)2 * P::L * 64 * nvpm);  // [lane]
   const double *xp = x + (size_t)s * NP * nvar;
   if (tid < nvar) {
     const C v = P::load(xp + tid, (size_t)nvar);
@@ -90,11 +96,9 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
       p = P::czero();
       p.re = P::rone();
     }
-    if (d > NT_TAB) {
-      const C xv = P::load(tab + v, tabp);
 #pragma unroll 1
-      for (int i = NT_TAB; i < d; ++i) p = nt_mul<P>(p, xv);
-    }
+    for (int i = d - NT_TAB; i > 0; i -= NT_TAB)
+      p = nt_mul<P>(p, P::load(tab + (size_t)((i < NT_TAB ? i : NT_TAB) - 1) * nvar + v, tabp));
     return p;
   };
   const int seg = HALF ? lane >> 5 : 0, ml = lane & (SEG - 1);  // the lane's equation and monomial
@@ -166,21 +170,23 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
     }
     lds_wait();  // the derivatives of the other lanes
     // J(e, j): the lanes of an equation take SEG variables at a time
+    const int slot = seg * SEG;
 #pragma unroll 1
     for (int j0 = 0; j0 < nvar; j0 += SEG) {
       unsigned long long has[NT_MAX_VPM];  // monomials whose factor t is this lane's variable
+      // (one list serves all factors: a wave's LDS operations run in order)
 #pragma unroll
-      for (int t = 0; t < NT_MAX_VPM; ++t) has[t] = 0;
-      const int jn = min(SEG, nvar - j0);
-#pragma unroll 1
-      for (int jj = 0; jj < jn; ++jj) {
-#pragma unroll
-        for (int t = 0; t < NT_MAX_VPM; ++t) {
-          if (t < nvpm) {
-            const unsigned long long m = __ballot(live && vt[t] == j0 + jj);
-            const unsigned long long mine = HALF ? (seg ? m >> 32 : m & 0xffffffffull) : m;
-            has[t] = ml == jj ? mine : has[t];
-          }
+      for (int t = 0; t < NT_MAX_VPM; ++t) {
+        has[t] = 0;
+        if (t < nvpm) {
+          const int j = vt[t] - j0;
+          lists[lane] = 0;
+          asm volatile("" ::: "memory");
+          if (live && j >= 0 && j < SEG)
+            __hip_atomic_fetch_or(&lists[slot + j], 1ull << ml, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          asm volatile("" ::: "memory");
+          has[t] = lists[lane];
+          asm volatile("" ::: "memory");
         }
       }
       Acc aj;
@@ -203,7 +209,7 @@ __global__ __launch_bounds__(256) void poly_eval_kernel(int neq, int nvar, int n
             found = found || hit;
           }
           Acc d1;
-          P::acc_set(d1, P::load(ds + (seg * SEG + m) * nvpm + ts, dsp));
+          P::acc_set(d1, P::load(ds + (slot + m) * nvpm + ts, dsp));
           P::acc_merge(aj, d1);
         }
       }
