@@ -18,11 +18,11 @@
 // from 1 is divided by a power of two, so that products with it have the
 // range of products with q_k.
 //
-// A wave is a grid of 16 row groups x 4 columns: lane 4 g + c holds rows
-// g, g + 16, ... (RPL of them) of one column per slot, so that a wave works
-// on 4 columns at a time with every lane busy (a column per wave left half
-// the lanes idle at 32 rows) and an inner product is summed over only 16
-// lanes.  The columns are dealt from the last one (b) on, 4 per wave and
+// A wave is a grid of 16 row groups x 4 columns (32 x 2 or 64 x 1 for few
+// columns of many rows, below): lane 4 g + c holds rows g, g + 16, ... (RPL of
+// them) of one column per slot, so that a wave works on 4 columns at a time
+// with every lane busy (a column per wave left half the lanes idle at 32
+// rows) and an inner product is summed over only 16 lanes.  The columns are dealt from the last one (b) on, 4 per wave and
 // slot, so that the slots empty from the top as k grows; column 1, which
 // never receives a projection, has no slot.  Sums: the two halves of the
 // wave exchange so that one half carries on with the real and one with the
@@ -30,8 +30,9 @@
 // or with the norm (permlane32_swap / permlane16_swap), then two rotations
 // within a row: 5 merges of real accumulators for two complex sums (6 + 6
 // each way in a scan of 64 lanes).  The tree of a sum and every later
-// operation is the same whatever the wave count and the slot, so a system's
-// results do not depend on the shape.
+// operation is the same whatever the wave count and the slot, and the lane
+// grid goes by the system's own size, so a system's results do not depend on
+// the batch.
 //
 // One wave per system (NW = 1, large batches) needs no synchronisation at
 // all.  With several waves (a short chain for few systems) u_k passes
@@ -50,8 +51,6 @@ namespace mgsq {
 constexpr int BAT_MAX_ROWS = 64;
 constexpr int BAT_MAX_COLS = 64;          // columns of [A b]
 constexpr size_t BAT_LDS_BYTES = 160 * 1024 - 1024;  // bound on 16 L m n, the size limit of the entry points
-constexpr int BAT_CG = 4;                 // columns of a wave's lane grid
-constexpr int BAT_RG = 64 / BAT_CG;       // row groups
 
 struct BatArgs {
   int batch, m, n, ncols;  // ncols = n + 1 when b is given
@@ -78,18 +77,19 @@ constexpr bool bat_unnormalised() {
   return P::L <= 2 && P::L * RPL <= 4;
 }
 
-// RPL rows per lane (m <= 16 RPL), SL slots (columns 2, 3, ... of [A b]: at
-// most 4 NW SL), NW waves, at least WPE waves per SIMD (the register
-// budget).
-template <class P, int RPL, int SL, int NW, int WPE>
+// A lane grid of CG columns, RPL rows per lane (m <= 64 / CG RPL), SL slots
+// (columns 2, 3, ... of [A b]: at most CG NW SL), NW waves, at least WPE waves
+// per SIMD (the register budget).
+template <class P, int RPL, int SL, int NW, int WPE, int CG>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void mgs_batched_kernel(BatArgs a) {
   using C = typename P::C;
   using Acc = typename P::Acc;
   using Rl = typename P::R;
   using G = GridSum<P>;
   constexpr int L = P::L, NP = 2 * L;       // limbs, planes of a complex element
-  constexpr int MP = BAT_RG * RPL;          // padded rows
-  constexpr int STEP = BAT_CG * NW;         // columns per slot
+  constexpr int RG = 64 / CG;               // row groups
+  constexpr int MP = RG * RPL;              // padded rows
+  constexpr int STEP = CG * NW;             // columns per slot
   constexpr int RING = NW == 1 ? 2 : 8;     // u vectors kept
   constexpr bool UF = bat_unnormalised<P, RPL>();  // u_k is column k unnormalised
   constexpr bool LATE = UF && NW > 1;       // R and y are divided by r_kk at the end
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   __shared__ int status;                    // this system's info
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int cg = lane & (BAT_CG - 1), rg = lane / BAT_CG;
+  const int cg = lane & (CG - 1), rg = lane / CG;
   const int sys = blockIdx.x;
   const int m = a.m, n = a.n, last = a.ncols - 1;
   const size_t planeA = (size_t)a.lda * n, planeQ = (size_t)a.ldq * n, planeR = (size_t)a.ldr * n;
@@ -118,11 +118,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     if constexpr (UF) far = 0;
   }
   if (tid < NW) done[tid] = 0;
-  const int first = last - (BAT_CG * w + cg);  // this lane's column in slot 0; slot s: first - STEP s
+  const int first = last - (CG * w + cg);  // this lane's column in slot 0; slot s: first - STEP s
   auto load_col = [&](int j, C (&v)[RPL]) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
-      const int i = rg + BAT_RG * r;
+      const int i = rg + RG * r;
       v[r] = P::czero();
       if (i < m && j >= 0) {
         if (j < n)
@@ -136,13 +136,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   auto put_u = [&](int c, const C (&v)[RPL]) __attribute__((always_inline)) {
     double *dst = &us[c & (RING - 1)][0][0];
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) P::store(dst + rg + BAT_RG * r, (size_t)MP, v[r]);
+    for (int r = 0; r < RPL; ++r) P::store(dst + rg + RG * r, (size_t)MP, v[r]);
     if constexpr (UF) {
       // (rare; in LDS, so that it costs the others no registers)
       if (wide && ups[c] != 1.0) {
         const double f = pow2_inverse(ups[c]);
 #pragma unroll 1
-        for (int i = 0; i < NP * RPL; ++i) dst[rg + BAT_RG * i] *= f;
+        for (int i = 0; i < NP * RPL; ++i) dst[rg + RG * i] *= f;
       }
     }
   };
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       double f = 1.0;
       if (__any(out(big))) {
 #pragma unroll
-        for (int k = BAT_CG; k < 64; k *= 2) big = fmax(big, __shfl_xor(big, k));
+        for (int k = CG; k < 64; k *= 2) big = fmax(big, __shfl_xor(big, k));
         int e = out(big) && big < INFINITY ? ilogb(big) : 0;
         if (j == n && e > 0) e -= 767;
         e = e > 1000 ? 1000 : (e < -1000 ? -1000 : e);
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   auto normalise = [&](int c, int g1, C (&v)[RPL]) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
-      const int i = rg + BAT_RG * r;
+      const int i = rg + RG * r;
       v[r] = P::scale(v[r], inv);
       if (cg == g1 && i < m) P::store(Q + (size_t)c * a.ldq + i, planeQ, v[r]);
     }
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     range(cg == 0 ? 0 : -1, u);
     if constexpr (UF) lds_wait();  // ups[0], of one lane, for all
     if constexpr (!UF) {
-      s2 = G::real_sum(norm(u));
+      s2 = G::template real_sum<CG>(norm(u));
       root_and_inverse<P>(s2, rkk, inv);
       normalise(0, 0, u);
     }
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // several waves it is u_k^H a_j, to be divided by r_kk at the end: the
   // square root stays off the chain.
   auto store_r = [&](int k, int j, const Rl &v) __attribute__((always_inline)) {
-    if ((rg & 3) == 0 && j > k) {
+    if ((lane & 15) < CG && j > k) {
       double t[L];
       P::store_real(t, 1, v);
       const int part = lane >> 5;
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       }
     });
     if constexpr (!UF) {
-      s2 = G::real_sum(norm(v));
+      s2 = G::template real_sum<CG>(norm(v));
       root_and_inverse<P>(s2, rkk, inv);
       normalise(c, g1, v);
     }
@@ -333,7 +333,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   for (int k = 0; k < n; ++k) {
     // slots holding a column past k: the largest column of slot s is
     // last - 4 w - STEP s; the first wave goes on to normalise
-    const int above = last - BAT_CG * w - k;
+    const int above = last - CG * w - k;
     if (above <= 0 && (!UF || w > 0)) break;
     const int nact = above > 0 ? (above + STEP - 1) / STEP : 0;
     res_jitter(a.jitter, (unsigned)k);
@@ -347,20 +347,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       asm volatile("" ::: "memory");
     }
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) u[r] = P::load(&us[k & (RING - 1)][0][rg + BAT_RG * r], (size_t)MP);
+    for (int r = 0; r < RPL; ++r) u[r] = P::load(&us[k & (RING - 1)][0][rg + RG * r], (size_t)MP);
     if constexpr (NW > 1) {
       lds_wait();
       if (lane == 0) __hip_atomic_store(&done[w], k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     // position of column k + 1 among the slots (its slot, wave and group)
     const int pos = last - (k + 1);
-    const int s1 = pos / STEP, g1 = pos & (BAT_CG - 1);
-    const bool own = k + 1 < n && (pos - s1 * STEP) / BAT_CG == w;
+    const int s1 = pos / STEP, g1 = pos & (CG - 1);
+    const bool own = k + 1 < n && (pos - s1 * STEP) / CG == w;
     mine = own;
     if constexpr (NW == 1) {
       Rl iw;
       if constexpr (UF) {
-        s2 = G::real_sum(norm(u));
+        s2 = G::template real_sum<CG>(norm(u));
         iw = P::recip(s2);
         root_and_inverse<P>(s2, rkk, inv);
       }
@@ -369,14 +369,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
         constexpr int s = 2 * decltype(pI)::value;
         const int j0 = first - STEP * s, j1 = first - STEP * (s + 1);
         if (s + 1 < nact) {
-          const Rl v = G::sum2(dot(col[s]), dot(col[s + 1]));
+          const Rl v = G::template sum2<CG>(dot(col[s]), dot(col[s + 1]));
           store_r(k, (lane >> 4) & 1 ? j1 : j0, times(v, inv));
           Rl t0 = times(v, iw), t1;
           G::unpack16(t0, t1);
           update(k, j0, t0, col[s]);
           update(k, j1, t1, col[s + 1]);
         } else if (s < nact) {
-          const Rl v = G::sum(dot(col[s]));
+          const Rl v = G::template sum<CG>(dot(col[s]));
           if (((lane >> 4) & 1) == 0) store_r(k, j0, times(v, inv));
           update(k, j0, times(v, iw), col[s]);
         }
@@ -392,11 +392,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
           constexpr int s = decltype(sI)::value;
           if (s == sf) {
             if constexpr (UF) {
-              vf = G::sum_and_real(dot(col[s]), norm(u), s2);
+              vf = G::template sum_and_real<CG>(dot(col[s]), norm(u), s2);
               iw = P::recip(s2);
               update(k, first - STEP * s, P::rmul(vf, iw), col[s]);
             } else {
-              vf = G::sum(dot(col[s]));
+              vf = G::template sum<CG>(dot(col[s]));
               update(k, first - STEP * s, vf, col[s]);
             }
           }
@@ -406,13 +406,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
         static_for<SL>([&](auto sI) __attribute__((always_inline)) {
           constexpr int s = decltype(sI)::value;
           if (s < nact && s != sf) {
-            const Rl v = G::sum(dot(col[s]));
+            const Rl v = G::template sum<CG>(dot(col[s]));
             update(k, first - STEP * s, UF ? P::rmul(v, iw) : v, col[s]);
             if (((lane >> 4) & 1) == 0) store_r(k, first - STEP * s, v);
           }
         });
       } else if constexpr (UF) {
-        s2 = G::real_sum(norm(u));
+        s2 = G::template real_sum<CG>(norm(u));
       }
       if constexpr (UF) {
         if (w == 0) root_and_inverse<P>(s2, rkk, inv);
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     P::acc_zero(t);
 #pragma unroll
     for (int r = 0; r < RPL; ++r) P::acc_abs2(t, col[0][r]);
-    const Rl s2 = G::real_sum(t);
+    const Rl s2 = G::template real_sum<CG>(t);
     if (lane == 0) {
       double t2[L];
       P::store_real(t2, 1, P::ok_norm(s2) ? P::sqrt_(s2) : P::rzero());

@@ -687,11 +687,11 @@ int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
 
 // Small systems: one workgroup per system (returns MGS_ERR_DIMS when the
 // columns do not fit the shape's slots).
-template <class P, int RPL, int SL, int NW, int WPE>
+template <class P, int RPL, int SL, int NW, int WPE, int CG = 4>
 int batched_launch(const BatArgs &a, hipStream_t st) {
-  if (a.m > BAT_RG * RPL || a.ncols - 1 > BAT_CG * NW * SL) return MGS_ERR_DIMS;
+  if (a.m > 64 / CG * RPL || a.ncols - 1 > CG * NW * SL) return MGS_ERR_DIMS;
   if (a.batch == 0) return MGS_OK;
-  hipLaunchKernelGGL((mgs_batched_kernel<P, RPL, SL, NW, WPE>), dim3(a.batch), dim3(64 * NW), 0, st, a);
+  hipLaunchKernelGGL((mgs_batched_kernel<P, RPL, SL, NW, WPE, CG>), dim3(a.batch), dim3(64 * NW), 0, st, a);
   return hipGetLastError() == hipSuccess ? MGS_OK : MGS_ERR_LAUNCH;
 }
 // The shape by batch size, all with the same results.  While the systems
@@ -735,13 +735,44 @@ int batched_shape(const BatArgs &a, int cus, hipStream_t st) {
     return two ? batched_launch<P, RPL, 1, 8, 2>(a, st) : batched_launch<P, RPL, 8, 1, 2>(a, st);
   }
 }
+// Few slotted columns on many rows: a grid of fewer columns, so that a column's
+// rows are spread over more lanes (RPL 1 or 2 in place of 2 to 4) and each wave
+// of a small batch holds one or two columns.  The grid goes by the system's
+// size alone (its bits do not depend on the batch).  us per call, 16 x 4 / now:
+//   at most 8 columns, more than 32 rows, 64 x 1 (64 x 4): double 10.3 / 8.9 at 1,
+//   26.7 / 16.9 at 4000; dd 14.0 / 9.1, 71 / 37; qd 85 / 38, 273 / 127 at 1500;
+//   at most 8, 17 to 32 rows, 32 x 2 (20 x 8): double 11.2 / 10.3, 32.2 / 27.8; dd
+//   19.2 / 16.0, 73 / 65; qd 104 / 73, 269 / 221 at 1500;
+//   9 to 16, more than 32 rows, 32 x 2 (48 x 10): double 15.0 / 13.3, 51.9 / 44;
+//   dd 26.1 / 24.6, 158 / 119; qd 154 / 134, 528 / 505 at 1500.
+// 9 to 16 on 17 to 32 rows gain alone (28 x 16 double 19.7 -> 17.8) but lose in
+// batches (34.5 -> 36.4 at 1500): 16 x 4.  9 to 16 on 64 x 1 likewise (48 x 10
+// double 13.3 -> 11.9 with 16 waves, 15.9 -> 21.8 at 257).
+template <class P>
+int batched_few(const BatArgs &a, int cus, hipStream_t st) {
+  const bool one = a.batch <= cus, two = a.batch <= 2 * cus;
+  if (a.ncols - 1 <= 8) {
+    if (a.m <= 32) return two ? batched_launch<P, 1, 1, 4, 1, 2>(a, st) : batched_launch<P, 1, 4, 1, 1, 2>(a, st);
+    if constexpr (P::L == 4)
+      return two ? batched_launch<P, 1, 2, 4, 1, 1>(a, st) : batched_launch<P, 1, 8, 1, 1, 1>(a, st);
+    return two ? batched_launch<P, 1, 1, 8, 2, 1>(a, st) : batched_launch<P, 1, 8, 1, 2, 1>(a, st);
+  }
+  if constexpr (P::L == 4) {
+    if (one) return batched_launch<P, 2, 2, 4, 1, 2>(a, st);
+    return two ? batched_launch<P, 2, 4, 2, 1, 2>(a, st) : batched_launch<P, 2, 8, 1, 1, 2>(a, st);
+  } else {
+    if (one || (two && P::L == 1)) return batched_launch<P, 2, 1, 8, 2, 2>(a, st);
+    return two ? batched_launch<P, 2, 2, 4, 2, 2>(a, st) : batched_launch<P, 2, 8, 1, 2, 2>(a, st);
+  }
+}
 template <class P>
 int batched_dispatch(const BatArgs &a, hipStream_t st) {
   DevInfo d;
   const int cus = dev_info(d) && d.cus > 0 ? d.cus : 256;
-  if (a.m <= BAT_RG) return batched_shape<P, 1>(a, cus, st);
-  if (a.m <= 2 * BAT_RG) return batched_shape<P, 2>(a, cus, st);
-  if (a.m <= 3 * BAT_RG) return batched_shape<P, 3>(a, cus, st);
+  if ((a.m > 16 && a.ncols - 1 <= 8) || (a.m > 32 && a.ncols - 1 <= 16)) return batched_few<P>(a, cus, st);
+  if (a.m <= 16) return batched_shape<P, 1>(a, cus, st);
+  if (a.m <= 32) return batched_shape<P, 2>(a, cus, st);
+  if (a.m <= 48) return batched_shape<P, 3>(a, cus, st);
   return batched_shape<P, 4>(a, cus, st);
 }
 int batched_dispatch(int prec, const BatArgs &a, hipStream_t st) {

@@ -341,11 +341,14 @@ struct GridSum {
     rot<0x121>(v);  // row_ror:1
     return v;
   }
-  // The rest of a sum over the row groups of a 16 x 4 lane grid, within rows
-  // of 16 lanes (4 row groups).
+  // The rest of a sum over the row groups of a lane grid of CG columns, within
+  // rows of 16 lanes (16 / CG row groups).
+  template <int CG>
   __device__ static __forceinline__ Rl finish(RAcc v) {
-    rot<0x128>(v);  // row_ror:8
-    rot<0x124>(v);  // row_ror:4
+    rot<0x128>(v);                          // row_ror:8
+    rot<0x124>(v);                          // row_ror:4
+    if constexpr (CG <= 2) rot<0x122>(v);  // row_ror:2
+    if constexpr (CG <= 1) rot<0x121>(v);  // row_ror:1
     return P::racc_value(v);
   }
   template <int CTRL>
@@ -371,23 +374,27 @@ struct GridSum {
 
   // Packed sums: the real part in the lower half of the wave, the imaginary
   // part in the upper; t0 in the even rows of 16 lanes, t1 in the odd.
+  template <int CG>
   __device__ static __forceinline__ Rl sum2(const Acc &t0, const Acc &t1) {
-    return finish(fold16(fold32(parts(t0)[0], parts(t0)[1]), fold32(parts(t1)[0], parts(t1)[1])));
+    return finish<CG>(fold16(fold32(parts(t0)[0], parts(t0)[1]), fold32(parts(t1)[0], parts(t1)[1])));
   }
+  template <int CG>
   __device__ static __forceinline__ Rl sum(const Acc &t) {
     const RAcc u = fold32(parts(t)[0], parts(t)[1]);
-    return finish(fold16(u, u));
+    return finish<CG>(fold16(u, u));
   }
+  template <int CG>
   __device__ static __forceinline__ Rl real_sum(const Acc &t) {
     RAcc u = parts(t)[0];
     u = fold32(u, u);
-    return finish(fold16(u, u));
+    return finish<CG>(fold16(u, u));
   }
   // t in every row, and the real sum s in every lane.
+  template <int CG>
   __device__ static __forceinline__ Rl sum_and_real(const Acc &t, const Acc &s, Rl &real) {
     RAcc u = parts(s)[0];
     u = fold32(u, u);
-    Rl v = finish(fold16(fold32(parts(t)[0], parts(t)[1]), u));
+    Rl v = finish<CG>(fold16(fold32(parts(t)[0], parts(t)[1]), u));
     unpack16(v, real);
     return v;
   }
