@@ -34,9 +34,9 @@
  * Numerical status goes to the device int *info (written by the kernels):
  *   0 = success; k > 0 = column k (1-based) had a zero or non-finite norm
  *   (MGS does not pivot, Section 4), outputs from column k on are then
- *   unspecified; MGS_INFO_SYNC_TIMEOUT = a wait between workgroups of the
- *   single-launch factorisation exceeded its time limit (outputs
- *   unspecified; not expected in normal operation).
+ *   unspecified; MGS_INFO_SYNC_TIMEOUT = a wait between waves or workgroups
+ *   of one launch exceeded its time limit (outputs unspecified; not expected
+ *   in normal operation).
  * ------------------------------------------------------------------------
  */
 #ifndef MGSQR_H
@@ -63,7 +63,7 @@ enum {
   MGS_ERR_UNSUPPORTED = -6  /* unknown operation code or schedule */
 };
 
-/* *info value of a factorisation whose inter-workgroup wait timed out. */
+/* *info value of a call one of whose bounded waits timed out. */
 #define MGS_INFO_SYNC_TIMEOUT (-9)
 
 enum { MGS_OP_QR = 0, MGS_OP_SOLVE = 1, MGS_OP_ADJOINT = 2, MGS_OP_REFINE = 3, MGS_OP_QR64 = 4 };
@@ -325,7 +325,8 @@ int mgs_lstsq_batched(int batch, int m, int n, int prec, const double *A, int ld
 /*
  * mgs_poly_eval -- F = f(x) and the Jacobian J = df/dx at batch points, in
  * the working precision: monomials and their derivatives by products of
- * powers, sums over the monomials in ascending order.
+ * powers; an entry of J sums its monomials in ascending order, F_e in a
+ * fixed tree.
  *   J [out] batch neq x nvar planar with leading dimension neq (column j =
  *           d f / d x_j; point s at J + s*2*prec*neq*nvar), the A layout of
  *           mgs_lstsq_batched.

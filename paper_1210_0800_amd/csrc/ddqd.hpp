@@ -171,7 +171,6 @@ __device__ __forceinline__ qd qd_add(qd a, qd b) {
   return qd_renorm(s0, t1, t2, t3);
 }
 __device__ __forceinline__ qd qd_neg(qd a) { return {-a.x0, -a.x1, -a.x2, -a.x3}; }
-__device__ __forceinline__ qd qd_sub(qd a, qd b) { return qd_add(a, qd_neg(b)); }
 
 // The sum of the level-3 terms of a b and of its level-4 products in plain
 // FP64, the smallest first.

@@ -5,8 +5,8 @@
 //
 // A workgroup takes the next column of [A b] that nobody has taken (a counter),
 // loads it once, applies the projections k = 0, 1, ..., c-1 in order as they
-// become available, writes it once, and takes another.  The columns handed on are the
-// unnormalised ones: u_k is column k after its last projection, and
+// become available, writes it once, and takes another.  The columns handed on
+// are the unnormalised ones: u_k is column k after its last projection, and
 //   r_kj = (u_k^H a_j) / r_kk,   a_j -= ((u_k^H a_j) / ||u_k||^2) u_k,
 // equal to q_k^H a_j and r_kj q_k in exact arithmetic, so neither the square
 // root nor the normalisation is on the chain from column to column: a link
@@ -17,9 +17,9 @@
 // the columns', uses q_k = u_k / r_kk itself.
 //
 // What bounds it: up to one column per workgroup, the chain (5.5 us a link at
-// 80 rows, 8.6 at 320, where one launch per column took 16 and 24); beyond,
+// 80 rows, 8.1 at 320, where one launch per column took 16 and 24); beyond,
 // the issue of the qd operations (1024 x 1024: 1.08e10 wave instructions,
-// 17.5 ms of 30.8; one launch per column 71.5) and waiting at the chain.
+// 17.5 ms of 30.2; one launch per column 71.5) and waiting at the chain.
 // Equal work per compute unit by dealing the second workgroup of each its
 // columns in reverse was slower (42.7 ms against 32.6 a solve), as was a
 // raised wave priority near the chain at 300 columns (5.2 against 4.7 ms).

@@ -670,12 +670,12 @@ int left_launch_qd(const StepArgs &s, void *work, hipStream_t st) {
   a.spin_ticks = wait.ticks;
   a.jitter = wait.jitter;
   // One column per workgroup (up to an eighth more: a workgroup's first
-  // column is soon done): one row per thread, the shortest link (n = 80
-  // 5.9 us a column, 320 x 256 8.3 us against 9.4 with 2 rows per thread on
-  // half the waves).  More columns than that: fewer, fuller waves, which
-  // halves the sums' share, and several workgroups per compute unit to fill
-  // each other's waits (500 x 500 5.4 ms against 6.0; 1024 x 1024 31.0 ms
-  // against 34.5 with 8 waves of 2 rows, one workgroup).
+  // column is soon done): one row per thread, the shortest link (80 x 80 5.5 us
+  // a column, 320 x 256 8.1; with 2 rows per thread on half the waves 1.13
+  // times that).  More columns than that: fewer, fuller waves, which halves
+  // the sums' share, and several workgroups per compute unit to fill each
+  // other's waits (500 x 500 5.2 ms, 1.11 times that with one; 1024 x 1024 30.2
+  // ms, 1.11 times that with 8 waves of 2 rows, one workgroup).
   const bool single = s.ncols <= cus + cus / 8;
   if (s.m <= 64) return left_launch_shape<P, 1, 1, 1>(a, cus, khz, st);
   if (s.m <= 128) return left_launch_shape<P, 1, 2, 1>(a, cus, khz, st);

@@ -165,9 +165,6 @@ __device__ __forceinline__ double pow2_inverse(double f) {
   return __longlong_as_double(0x7FE0000000000000LL - __double_as_longlong(f));
 }
 
-// Widest panel the resident schedule factors.
-constexpr int RES_BWMAX = 4;
-
 // Device-scope (coherent across XCDs) relaxed loads and stores of one
 // double: the q vectors exchanged between workgroups.
 __device__ __forceinline__ void coh_store(double *p, double v) {
@@ -460,8 +457,9 @@ struct Resident {
 
   // Block reductions: every thread stores its partial sum of slot s, then
   // (after a barrier) wave s mod NW alone reduces it: lane l merges the partials
-  // of threads l, l+64, ..., l+64(NW-1) in a pairwise tree, then a DPP scan
-  // brings the total to lane 63, which writes rsum[s].  A second barrier
+  // of threads l, l+64, ..., l+64(NW-1) in a pairwise tree, then the wave folds
+  // its halves (real part below, imaginary part above) and rows and rotates
+  // within them, and one lane of either half writes rsum[s].  A second barrier
   // makes rsum visible.  The merge tree is fixed, so results are
   // reproducible, and each partial is merged once (not once per wave).
   __device__ __forceinline__ void put(int s, const Acc &v) {
