@@ -45,7 +45,7 @@ F_DD = dict(cmulc=60, upd=66, abs2=28, scale=20, merge=16)
 # policies (not the qd functions, which it does not use), of mgs_kernels.hpp
 # the helpers it uses, of mgsqr.hip the part that plans and launches the
 # single-launch factorisation); reported as null otherwise.
-TRAFFIC = dict(fetch_bytes=2.0 * 1.590e5 * 1024, write_bytes=1.690e5 * 1024, sources="1c2b350fcfbc41fc")
+TRAFFIC = dict(fetch_bytes=2.0 * 1.591e5 * 1024, write_bytes=1.696e5 * 1024, sources="e885d56a78fc4777")
 KERNEL_SOURCES = ["paper_1210_0800_amd/csrc/resident_kernels.hpp",
                   ("paper_1210_0800_amd/csrc/ddqd.hpp", "// Device arithmetic", "// " + "-" * 67 + " qd --"),
                   ("paper_1210_0800_amd/csrc/ddqd.hpp", "// " + "-" * 57 + " precisions ----", None),
